@@ -44,6 +44,8 @@ struct Mesh {
   std::vector<int> cel_ptr_h, csl_ptr_h;   // per-colour dirty element / slot list offsets
   int *d_bvert = nullptr, *d_bpos = nullptr, *d_bqcnt = nullptr, *d_hqslot = nullptr;
   void* hq = nullptr;
+  float* tb = nullptr;             // tile records and their index arrays (MeshView::tb)
+  int *d_tbslot = nullptr, *d_tboff[cc::TILE_N] = {};
   int qmax = 0, band_w = 0;
 
   double *dinv_d = nullptr, *vol_d = nullptr, *mass = nullptr;
@@ -87,6 +89,9 @@ struct Mesh {
     v.bvert = d_bvert; v.bpos = d_bpos; v.bq_cnt = d_bqcnt; v.hq_slot = d_hqslot;
     v.hq = dense ? hq : nullptr;   // the assembly writes the band copy only for dense bases
     v.qmax = qmax; v.band_w = band_w;
+    v.tb = dense ? tb : nullptr;
+    v.tb_slot = d_tbslot; 
+    for (int c = 0; c < cc::TILE_N; ++c) v.tb_off[c] = d_tboff[c];
     v.sptr = sptr; v.sidx = sidx; v.U_d = U_d; v.U_f = U_f; v.dense_supp = dense;
     v.smap = smap; v.smap_words = smap_words; v.smap_supp = smap_supp;
     v.sorder = d_sorder;
@@ -116,6 +121,8 @@ struct ApiError {
 // Exact bases keep a float64 copy (for CC_FP64 steps) while it takes at most
 // this many bytes; larger ones are stored in float32 only.
 constexpr size_t DENSE_F64_MAX_BYTES = size_t(4) << 30;
+// Floats past a float32 dense basis: the look-ahead of the last row's copy ends there.
+constexpr size_t DENSE_F32_PAD = 4096;
 // Unknowns per level of the block-tridiagonal exact-basis build.
 constexpr int LEVEL_DOFS = 768;
 
@@ -153,6 +160,8 @@ void free_mesh(Mesh& M) {
   dfree(M.ev); dfree(M.star_ptr); dfree(M.star); dfree(M.d_rowptr); dfree(M.d_colidx);
   dfree(M.blkrow); dfree(M.cptr); dfree(M.centry); dfree(M.d_vperm); dfree(M.d_vinv);
   dfree(M.d_bvert); dfree(M.d_bpos); dfree(M.d_bqcnt); dfree(M.d_hqslot); dfree(M.hq);
+  dfree(M.tb); dfree(M.d_tbslot); 
+  for (int*& o : M.d_tboff) dfree(o);
   dfree(M.d_eperm); dfree(M.d_sorder); dfree(M.d_aorder);
   dfree(M.d_cel_ptr); dfree(M.d_cel); dfree(M.d_csl_ptr); dfree(M.d_csl); dfree(M.dinv_d); dfree(M.vol_d); dfree(M.mass); dfree(M.dinv_f); dfree(M.vol_f);
   free_basis(M);
@@ -664,6 +673,27 @@ void build_mesh(cc_ctx* ctx, Mesh& M) {
     const size_t hqb = (size_t)std::max(M.qmax, 1) * std::max(nf, 1) * rec;
     M.hq = dalloc<double>(hqb / sizeof(double));
     HIPC(hipMemsetAsync(M.hq, 0, hqb, s));
+    if (D == 3 && nf >= 2 && M.qmax <= cc::TILE_Q) {
+      // tile records (zero where a row has fewer blocks and past the last
+      // row) and, for each chunk size, the ring offsets of their columns
+      constexpr int Q = cc::TILE_Q;
+      const size_t rows = (size_t)nf + cc::TILE_PAD;
+      std::vector<int> tslot(M.nnzb, -1), off(rows * Q);
+      for (int p = 0; p < nf; ++p)
+        for (int q = 0; q < cnt[p]; ++q) tslot[up[p][q].second] = p * Q + q;
+      M.d_tbslot = dupload(tslot, s);
+      for (int c = 0; c < cc::TILE_N; ++c) {
+        const int R = cc::tile_ring(c + 1, nf, M.band_w);
+        for (size_t p = 0; p < rows; ++p)
+          for (int q = 0; q < Q; ++q) {
+            const int row = std::min((int)p, nf - 1);
+            off[p * Q + q] = ((int)p < nf && q < cnt[p] ? up[p][q].first : row) % R * 36;
+          }
+        M.d_tboff[c] = dupload(off, s);
+      }
+      M.tb = dalloc<float>(rows * Q * 12);
+      HIPC(hipMemsetAsync(M.tb, 0, rows * Q * 48, s));
+    }
   }
   M.cptr = dupload(cptr, s);
   M.centry = dupload(centry, s);
@@ -871,6 +901,7 @@ void upload_basis(cc_ctx* ctx, Mesh& M, const int64_t* ptr, const int32_t* idx, 
         std::memcpy(&band[((size_t)i * nf + M.bpos_h[sidx[q]]) * DD], &Ud[(size_t)q * DD], DD * sizeof(double));
     if (blocks * DD * sizeof(double) <= DENSE_F64_MAX_BYTES) M.U_d = dupload(band, s);
     std::vector<float> Uf(band.begin(), band.end());
+    Uf.resize(Uf.size() + DENSE_F32_PAD, 0.f);
     M.U_f = dupload(Uf, s);
     M.dense = 1;
   } else {
@@ -942,7 +973,7 @@ void build_basis(cc_ctx* ctx, Mesh& M, int radius, double dt, int quasi, const d
   mat.s_el = quasi ? 1.0 : dt * dt;
   MeshView mv = M.view();
   cc::launch_elem_hess(mv, 0, M.x, mat, mat.s_el, M.estore, s);
-  cc::launch_assemble(mv, 0, M.estore, mat, M.hb, s);
+  cc::launch_assemble(mv, 0, M.estore, mat, M.hb, nullptr, s);
   if (radius == 0) {  // exact basis from the block-tridiagonal factorisation of H (band order)
     const size_t blocks = (size_t)nf * nf;
     // breadth-first levels merged until each holds at least LEVEL_DOFS unknowns
@@ -955,7 +986,8 @@ void build_basis(cc_ctx* ctx, Mesh& M, int radius, double dt, int quasi, const d
     double* Ud = nullptr;
     float* Uf = nullptr;
     try {
-      Uf = dalloc<float>(blocks * DD);
+      Uf = dalloc<float>(blocks * DD + DENSE_F32_PAD);
+      HIPC(hipMemsetAsync(Uf + blocks * DD, 0, DENSE_F32_PAD * sizeof(float), s));
       if (blocks * DD * sizeof(double) <= DENSE_F64_MAX_BYTES) Ud = dalloc<double>(blocks * DD);
     } catch (...) {
       dfree(Ud); dfree(Uf);
@@ -1137,10 +1169,10 @@ struct Stepper {
       cc::launch_elem_hess_list(mv, p.precision, x, mat, mat.s_el, M.estore, s, el, ne);
     });
     ctx->timed(CC_K_ASSEMBLE, [&] {
-      cc::launch_assemble_list(mv, p.precision, M.estore, mat, M.hb, s, sl, ns);
+      cc::launch_assemble_list(mv, p.precision, M.estore, mat, M.hb, mv.tile ? M.g : nullptr, s, sl, ns);
       // a partial assembly leaves band records of unchanged blocks whose
       // rotations did change
-      if (colour >= 0 && mv.rot != nullptr) cc::launch_band_copy(mv, p.precision, M.hb, s);
+      if (colour >= 0 && mv.rot != nullptr) cc::launch_band_copy(mv, p.precision, M.hb, mv.tile ? M.g : nullptr, s);
     });
   }
   void prep(int method, int v0, int v1) {
@@ -1168,8 +1200,8 @@ struct Stepper {
   void sweep(const double* x, double* out, int method, int sweep_kind = -1) {
     const int nd = M.D * M.n;
     if ((sweep_kind < 0 ? p.sweep : sweep_kind) == CC_SWEEP_JACOBI) {
+      gradient_only(x);              // before the assembly, which may store it with its records
       hessian(x);
-      gradient_only(x);
       if (!prep_direction(method, M.dvec)) update(method, 0, M.nf, M.dvec, 0);
       cc::launch_axpy(nd, x, M.dvec, 1.0, out, s);
       return;
@@ -1181,10 +1213,11 @@ struct Stepper {
       if (v1 <= v0) continue;
       if (p.hess_refresh == CC_HESS_PER_COLOR) {
         // every Hessian at the sweep's start, then only what the previous
-        // colour's moves changed
+        // colour's moves changed; the gradient first, which the assembly may
+        // store with its records
+        gradient_only(out);
         hessian(out, moved);
         moved = c;
-        gradient_only(out);
         // a dense basis forms b_i from this gradient and moves the colour's
         // vertices in the finish kernel; other bases take the update kernel
         bool done = false;
@@ -1545,6 +1578,7 @@ cc_status cc_step(cc_ctx* ctx, int32_t mesh_id, double* x, double* v, const doub
     for (int c = 0; c < 3; ++c) mat.grav[c] = p.gravity[c];
     const double h = p.quasistatic ? 1.0 : dt;
     Stepper S{ctx, M, M.view(), mat, p, s};
+    S.mv.tile = cc::tile_usable(S.mv, p.precision, ctx->dense_rows, ctx->dense_chunk);
     HIPC(hipMemsetAsync(M.bad, 0, sizeof(int), s));
     HIPC(hipMemsetAsync(M.fb, 0, 4 * sizeof(unsigned long long), s));
     cc::launch_predict(S.mv, M.d_vperm, x, v, x_bc, h, p.quasistatic, M.x, M.xt, M.x0, M.bad, s);
@@ -1716,6 +1750,7 @@ cc_status cc_probe_sweep(cc_ctx* ctx, int32_t mesh_id, const double* x, const do
     mat.s_el = p.quasistatic ? 1.0 : dt * dt;
     for (int c = 0; c < 3; ++c) mat.grav[c] = p.gravity[c];
     Stepper S{ctx, M, M.view(), mat, p, s};
+    S.mv.tile = cc::tile_usable(S.mv, p.precision, 0, 0);
     cc::launch_gather_user(S.mv, M.d_vinv, x, M.x, s);
     cc::launch_gather_user(S.mv, M.d_vinv, x_tilde, M.xt, s);
     if (energy) *energy = S.energy(M.x);
@@ -1850,6 +1885,7 @@ static void batch_host_fallback(cc_ctx* ctx, Mesh& M, cc::BatchItem& it, cc::Bat
   M.x = it.x;
   M.xtrial = it.xtrial;
   Stepper S{ctx, M, M.view(), it.mat, p, s};
+  S.mv.tile = cc::tile_usable(S.mv, p.precision, ctx->dense_rows, ctx->dense_chunk);
   const int nd = M.D * M.n;
   const double tau = 1e-12 * std::max(std::fabs(c.E_cur), 1.0);
   // a Jacobi sweep of the same method (coloured sweeps of CC or JGS2), then
@@ -1924,6 +1960,7 @@ cc_status cc_step_batch(cc_ctx* ctx, int32_t n, const int32_t* mesh_ids, double*
       items[i] = make_item(M, mat);
       items[i].prep_dense = (p.method != CC_METHOD_CD && use_dense_band(ctx, M, p.precision)) ? 1 : 0;
       items[i].mv.rot = p.corotate ? M.rot : nullptr;
+      items[i].mv.tile = items[i].prep_dense && cc::batch_tile(plan) > 0;
       items[i].feat_off = 0;
       for (int q = 0; q < i; ++q) items[i].feat_off += ms[q]->nf;
       items[i].xu = x[i];

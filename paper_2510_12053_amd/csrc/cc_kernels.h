@@ -40,6 +40,19 @@ struct MeshView {
   const int* hq_slot;
   void* hq;
   int qmax, band_w;
+  // Tile records (float32 3D dense bases whose rows hold at most TILE_Q upper
+  // blocks; null otherwise): the same blocks as hq in the operand layout of
+  // the matrix-core condensation, tb[(p * TILE_Q + q) * 12 + s * 4 + r] =
+  // entry (r, s) of the q-th upper block of band row p, with row r = 3 of the
+  // diagonal block holding R_j^T g_j.  tb_slot[t] = p * TILE_Q + q for an
+  // upper slot t of hb, -1 otherwise; tb_off[c][p * TILE_Q + q] = byte offset
+  // of that block's column in the LDS ring of configuration c + 1.
+  // tile: 1 when the coming condensation reads tb (the assembly then writes
+  // tb), 0 when it reads hq.
+  float* tb;
+  const int* tb_slot;
+  const int* tb_off[3];
+  int tile;
   // perturbation basis, internal ids.  Sparse bases: CSR rows sorted by
   // internal id (sptr, sidx).  Dense (exact) bases: row i holds nf blocks
   // at (i * nf + p) * D*D, column p = band position, the block at the
@@ -103,19 +116,21 @@ void launch_finalize(const MeshView& mv, const int* vperm, const double* x, cons
                      double h, int quasi, double* x_user, double* v_user, hipStream_t s);
 void launch_elem_hess(const MeshView& mv, int prec, const double* x, const Material& mat,
                       double scale, void* estore, hipStream_t s);
+// g (may be null): the gradient at the Hessian's positions, stored with the
+// tile records of a mesh with mv.tile set.
 void launch_assemble(const MeshView& mv, int prec, const void* estore, const Material& mat,
-                     void* hb, hipStream_t s);
+                     void* hb, const double* g, hipStream_t s);
 // The same over a list of `count` elements / block slots (device ints; null:
 // the first `count` of all), e.g. the ones a colour's moves change
 // (MeshView::cel, csl).
 void launch_elem_hess_list(const MeshView& mv, int prec, const double* x, const Material& mat,
                            double scale, void* estore, hipStream_t s, const int* elist, int count);
 void launch_assemble_list(const MeshView& mv, int prec, const void* estore, const Material& mat, void* hb,
-                          hipStream_t s, const int* slist, int count);
+                          const double* g, hipStream_t s, const int* slist, int count);
 // Rewrites every BandRec of a dense-basis mesh (hq set) from the block rows
 // hb and the current rotations: after a partial assembly whose rotations
 // changed everywhere (a coloured sweep of a corotated mesh).
-void launch_band_copy(const MeshView& mv, int prec, const void* hb, hipStream_t s);
+void launch_band_copy(const MeshView& mv, int prec, const void* hb, const double* g, hipStream_t s);
 void launch_gradient(const MeshView& mv, const double* x, const double* xt, const Material& mat,
                      double* g, double* partials, int* nparts, hipStream_t s);
 // Condensation of vertices [v0, v1).  With g and dout given (g the gradient
@@ -202,6 +217,34 @@ struct DenseCfg {
 DenseCfg dense_config(const int* nf, const int* band_w, int count, int D, int prec, int cap = 0,
                       int chunk = 0);
 
+// ---- matrix-core condensation of float32 3D dense bases (prep_tile_body) ----
+constexpr int TILE_Q = 8;                    // upper blocks per band row it handles
+// Configurations (index + 1; 0: none): 1, ten vertices per workgroup of eight
+// waves, chunks of 64 band positions, for band widths up to TILE_RING - 64;
+// 2, five vertices per workgroup of sixteen waves, chunks of 256; 3, five
+// vertices per workgroup of eight waves, chunks of 128.
+constexpr int TILE_N = 3;
+constexpr int TILE_G[TILE_N] = {2, 1, 1};            // groups of five vertices
+constexpr int TILE_CH[TILE_N] = {64, 256, 128};      // chunks of band positions
+constexpr int TILE_WAVES[TILE_N] = {8, 16, 8};
+constexpr int TILE_RING = 192;               // ring of the first configuration
+constexpr int TILE_PAD = 1024;               // zero band rows after the last one (look-ahead reads)
+// LDS ring length (positions, a multiple of the chunk, so that no refill
+// wraps), nine words each; the vertices' rings are tile_stride words apart:
+// 3 mod 16, so that the 15 columns a row of 16 lanes reads fall into 15
+// consecutive banks (mod 16).
+__host__ __device__ inline int tile_ring(int cfg, int nf, int band_w) {
+  if (cfg == 1) return TILE_RING;
+  const int ch = TILE_CH[cfg - 1], need = nf < ch + band_w ? nf : ch + band_w;
+  return (need + ch - 1) / ch * ch;
+}
+__host__ __device__ inline constexpr int tile_stride(int ring) { return ring * 9 + 3; }
+int tile_config(const int* nf, const int* band_w, const int* rows, int count);
+size_t tile_lds_bytes(int cfg, int nf, int band_w);
+// Whether a mesh's dense condensation in precision prec takes it (the caller
+// sets MeshView::tile): no forced rows or chunk, tile records, a ring that fits.
+bool tile_usable(const MeshView& mv, int prec, int tv_cap, int chunk);
+
 // Exact basis U_i[j] = (H^{-1})_ji ((H^{-1})_ii)^{-1} from float64 block rows
 // hb (cc_basis.hip), through the block-tridiagonal structure of H in band
 // order: loff (host, L+1 band positions) splits the band order into levels
@@ -276,6 +319,7 @@ struct BatchConfig {
 BatchPlan* batch_plan_create(const BatchItem* items_host, int nmesh, const BatchConfig& cfg,
                              hipStream_t s);
 void batch_plan_destroy(BatchPlan* p);
+int batch_tile(BatchPlan* p);   // > 0: the plan's dense meshes use tile records (MeshView::tile)
 BatchItem* batch_items_dev(BatchPlan* p);
 BatchCtl* batch_ctl_dev(BatchPlan* p);
 // Start of a step: predictor, initial gradient norm and energy, control reset.

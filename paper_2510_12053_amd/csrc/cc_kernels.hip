@@ -15,6 +15,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "cc_device.h"
@@ -129,14 +130,33 @@ __global__ void __launch_bounds__(elem_threads<T>()) k_elem_hess(MeshView mv, co
   elem_hess_split<T, D>(mv, blockIdx.x * EWG, x, mu, lam, FCR ? model : MAT_SNH, scale, out, elist, ecount);
 }
 
-// Block rows: every slot sums its element contributions (fixed order), plus
-// the mass on the diagonal.
-// The BandRec of block slot t (row j) of a dense-basis mesh, when t is an
-// upper slot: w R_j^T H_jk R_k and the band position of k.
+// R_j^T g_j (g itself without rotations), rounded to T once.
 template <typename T, int D>
-__device__ __forceinline__ void band_rec_write(const MeshView& mv, int t, int j, const T* blk) {
+__device__ __forceinline__ void rotate_transpose(const double* rot, int j, const double (&gd)[D], T (&gj)[D]) {
+  if (rot != nullptr) {
+    const auto* Rj = gptr(rot) + (size_t)j * D * D;
+#pragma unroll
+    for (int c = 0; c < D; ++c) {
+      double acc = 0.0;
+#pragma unroll
+      for (int l = 0; l < D; ++l) acc += Rj[l * D + c] * gd[l];
+      gj[c] = T(acc);
+    }
+  } else {
+#pragma unroll
+    for (int c = 0; c < D; ++c) gj[c] = T(gd[c]);
+  }
+}
+
+// The band record of block slot t (row j) of a dense-basis mesh, when t is an
+// upper slot: w R_j^T H_jk R_k, as a BandRec with the band position of k, or
+// (mv.tile) as a tile record, whose diagonal block carries R_j^T g_j in its
+// fourth row when g is given.
+template <typename T, int D>
+__device__ __forceinline__ void band_rec_write(const MeshView& mv, int t, int j, const T* blk, const double* g) {
   constexpr int DD = D * D;
-  const int qp = mv.hq_slot[t];
+  const bool tile = sizeof(T) == 4 && D == 3 && mv.tile;
+  const int qp = tile ? mv.tb_slot[t] : mv.hq_slot[t];
   if (qp < 0) return;
   const int k = mv.colidx[t];
   const T w = k == j ? T(0.5) : T(1);
@@ -169,16 +189,34 @@ __device__ __forceinline__ void band_rec_write(const MeshView& mv, int t, int j,
         b[r * D + c] = acc;
       }
   }
+  if constexpr (sizeof(T) == 4 && D == 3) {
+    if (tile) {
+      float gj[3] = {0.f, 0.f, 0.f};
+      if (k == j && g != nullptr) {
+        double gd[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) gd[c] = g[(size_t)c * mv.n + j];
+        rotate_transpose<T, D>(mv.rot, j, gd, gj);
+      }
+      typedef float f4 __attribute__((ext_vector_type(4)));
+      f4* rec = reinterpret_cast<f4*>(mv.tb) + (size_t)qp * 3;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) rec[c] = f4{b[c], b[3 + c], b[6 + c], gj[c]};
+      return;
+    }
+  }
   auto* rec = reinterpret_cast<BandRec<T, D>*>(mv.hq) + qp;
 #pragma unroll
   for (int r = 0; r < DD; ++r) rec->h[r] = b[r];
   rec->pos = mv.bpos[k];
 }
 
+// Block rows: every slot sums its element contributions (fixed order), plus
+// the mass on the diagonal.
 template <typename T, int D>
 __device__ __forceinline__ void assemble_body(const MeshView& mv, int tt, const T* __restrict__ est,
-                                              T w_in, T* __restrict__ hb, const int* slist = nullptr,
-                                              int scount = 0) {
+                                              T w_in, T* __restrict__ hb, const double* g,
+                                              const int* slist = nullptr, int scount = 0) {
   constexpr int K = D + 1, DD = D * D;
   if (tt >= (slist ? scount : mv.nnzb)) return;
   // slots row by row in caller order of the rows: neighbouring threads then
@@ -236,19 +274,20 @@ __device__ __forceinline__ void assemble_body(const MeshView& mv, int tt, const 
   }
 #pragma unroll
   for (int r = 0; r < DD; ++r) hb[(size_t)t * DD + r] = acc[r];
-  if (mv.hq != nullptr) band_rec_write<T, D>(mv, t, j, acc);
+  if (mv.hq != nullptr) band_rec_write<T, D>(mv, t, j, acc, g);
 }
 
 template <typename T, int D>
-__global__ void __launch_bounds__(EWG) k_band_copy(MeshView mv, const T* __restrict__ hb) {
+__global__ void __launch_bounds__(EWG) k_band_copy(MeshView mv, const T* __restrict__ hb, const double* g) {
   const int t = blockIdx.x * EWG + threadIdx.x;
-  if (t < mv.nnzb) band_rec_write<T, D>(mv, t, mv.blkrow[t], hb + (size_t)t * D * D);
+  if (t < mv.nnzb) band_rec_write<T, D>(mv, t, mv.blkrow[t], hb + (size_t)t * D * D, g);
 }
 
 template <typename T, int D>
 __global__ void __launch_bounds__(EWG) k_assemble(MeshView mv, const T* __restrict__ est, T w_in,
-                                                  T* __restrict__ hb, const int* slist, int scount) {
-  assemble_body<T, D>(mv, blockIdx.x * EWG + threadIdx.x, est, w_in, hb, slist, scount);
+                                                  T* __restrict__ hb, const double* g, const int* slist,
+                                                  int scount) {
+  assemble_body<T, D>(mv, blockIdx.x * EWG + threadIdx.x, est, w_in, hb, g, slist, scount);
 }
 
 // Vertex of gradient slot idx: the free vertices in caller order, so that
@@ -649,6 +688,62 @@ struct SlotRegs {
   }
 };
 
+// The end of a dense condensation's workgroup: per vertex, A_i from its basis
+// row in global memory (one wave per vertex), and A_i, Ht_i = Y + Y^T and b_i
+// from the workgroup's sums tot ([vertex][Y, then b]).
+template <typename T, int D>
+__device__ __forceinline__ void band_tail(const MeshView& mv, int i0, int nv, int w, int nw,
+                                          const T* __restrict__ hb, T* __restrict__ KL, const T* tot,
+                                          double* __restrict__ bout) {
+  constexpr int DD = D * D, NR = DD + D;
+  const T* Ub = basis_of<T>(mv);
+  const int l = threadIdx.x % 64;
+  // one wave per row (rows w, w + nw, ... when the chunk has fewer waves
+  // than rows)
+  for (int v = w; v < nv; v += nw) {
+    const int i = i0 + v;
+    T A[DD];
+#pragma unroll
+    for (int r = 0; r < DD; ++r) A[r] = T(0);
+    const int q1 = gptr(mv.rowptr)[i + 1];
+    for (int q = gptr(mv.rowptr)[i] + 1 + l; q < q1; q += 64) {
+      const int k = gptr(mv.colidx)[q];
+      T Uk[DD];
+      band_load<T, D>(mv, Ub, i, gptr(mv.bpos)[k], Uk);
+      if (mv.rot != nullptr) rotate_block<T, D>(mv.rot, k, Uk);
+      const auto* H = gptr(hb) + (size_t)q * DD;
+#pragma unroll
+      for (int r = 0; r < D; ++r)
+#pragma unroll
+        for (int c = 0; c < D; ++c) {
+          T acc = T(0);
+#pragma unroll
+          for (int t = 0; t < D; ++t) acc += H[r * D + t] * Uk[t * D + c];
+          A[r * D + c] += acc;
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < DD; ++r) A[r] = wave_sum63(A[r]);
+    if (l != 63) continue;
+    // A and Ht go to the vertex's K, L slots; dm_finish_body turns them into
+    // K and L with one thread per vertex.  b_i = U_i^T (R^T g)_C, the
+    // corotated basis's U_i^T g_C.
+    const T* Yt = tot + v * NR;
+    auto* out = gptr_w(KL) + (size_t)i * 2 * DD;
+#pragma unroll
+    for (int r = 0; r < D; ++r)
+#pragma unroll
+      for (int c = 0; c < D; ++c) {
+        out[r * D + c] = A[r * D + c];
+        out[DD + r * D + c] = Yt[r * D + c] + Yt[c * D + r];
+      }
+    if (bout != nullptr)
+#pragma unroll
+      for (int r = 0; r < D; ++r) gptr_w(bout)[(size_t)r * mv.n + i] = double(Yt[DD + r]);
+  }
+}
+
+
 template <typename T, int D, int TV, int CH>
 __device__ __forceinline__ void prep_band_body(const MeshView& mv, int method, int i0, int nv,
                                                const T* __restrict__ hb, T* __restrict__ KL, T* smem,
@@ -794,19 +889,7 @@ __device__ __forceinline__ void prep_band_body(const MeshView& mv, int method, i
         double gd[D];
 #pragma unroll
         for (int c = 0; c < D; ++c) gd[c] = gptr(g)[(size_t)c * n + j];
-        if (mv.rot != nullptr) {              // R_j^T g_j
-          const auto* Rj = gptr(mv.rot) + (size_t)j * DD;
-#pragma unroll
-          for (int c = 0; c < D; ++c) {
-            double acc = 0.0;
-#pragma unroll
-            for (int l = 0; l < D; ++l) acc += Rj[l * D + c] * gd[l];
-            gj[c] = T(acc);
-          }
-        } else {
-#pragma unroll
-          for (int c = 0; c < D; ++c) gj[c] = T(gd[c]);
-        }
+        rotate_transpose<T, D>(mv.rot, j, gd, gj);
       }
       if constexpr (!own_first) {
         sj.load(ring + (size_t)wrap(p + cshift) * SLW);
@@ -867,48 +950,292 @@ __device__ __forceinline__ void prep_band_body(const MeshView& mv, int method, i
     tot[tid] = acc;
   }
   __syncthreads();
-  // one wave per row (rows w, w + NW, ... when the chunk has fewer waves
-  // than rows)
-  for (int v = w; v < nv; v += NW) {
-    const int i = i0 + v;
-    T A[DD];
+  band_tail<T, D>(mv, i0, nv, w, NW, hb, KL, tot, bout);
+}
+
+// A_i = sum_k H_ik R_k U_i[k] of a tile workgroup's vertices, into their K slots
+// (dm_finish_body reads them): 16 lanes per vertex, four vertices per wave.
+template <int V>
+__device__ __forceinline__ void tile_rows(const MeshView& mv, int i0, int nv, int w, const float* __restrict__ hb,
+                                          float* __restrict__ KL) {
+  if (w >= (V + 3) / 4) return;
+  const int l = threadIdx.x % 64, v = w * 4 + l / 16, i = i0 + min(v, nv - 1);
+  float A[9];
 #pragma unroll
-    for (int r = 0; r < DD; ++r) A[r] = T(0);
-    const int q1 = gptr(mv.rowptr)[i + 1];
-    for (int q = gptr(mv.rowptr)[i] + 1 + l; q < q1; q += 64) {
-      const int k = gptr(mv.colidx)[q];
-      T Uk[DD];
-      band_load<T, D>(mv, Ub, i, gptr(mv.bpos)[k], Uk);
-      if (mv.rot != nullptr) rotate_block<T, D>(mv.rot, k, Uk);
-      const auto* H = gptr(hb) + (size_t)q * DD;
+  for (int r = 0; r < 9; ++r) A[r] = 0.f;
+  const int q1 = gptr(mv.rowptr)[i + 1];
+  for (int q = gptr(mv.rowptr)[i] + 1 + l % 16; q < q1; q += 16) {
+    const int k = gptr(mv.colidx)[q];
+    float Uk[9];
+    band_load<float, 3>(mv, mv.U_f, i, gptr(mv.bpos)[k], Uk);
+    if (mv.rot != nullptr) rotate_block<float, 3>(mv.rot, k, Uk);
+    const auto* H = gptr(hb) + (size_t)q * 9;
 #pragma unroll
-      for (int r = 0; r < D; ++r)
+    for (int r = 0; r < 3; ++r)
 #pragma unroll
-        for (int c = 0; c < D; ++c) {
-          T acc = T(0);
+      for (int c = 0; c < 3; ++c) {
+        float acc = 0.f;
 #pragma unroll
-          for (int t = 0; t < D; ++t) acc += H[r * D + t] * Uk[t * D + c];
-          A[r * D + c] += acc;
-        }
+        for (int t = 0; t < 3; ++t) acc += H[r * 3 + t] * Uk[t * 3 + c];
+        A[r * 3 + c] += acc;
+      }
+  }
+#pragma unroll
+  for (int r = 0; r < 9; ++r) {                      // sums over the 16 lanes
+    A[r] = dpp_add<0x128, 0xf>(A[r]);
+    A[r] = dpp_add<0x124, 0xf>(A[r]);
+    A[r] = dpp_add<0x122, 0xf>(A[r]);
+    A[r] = dpp_add<0x121, 0xf>(A[r]);
+  }
+  if (l % 16 != 0 || v >= nv) return;
+#pragma unroll
+  for (int r = 0; r < 9; ++r) gptr_w(KL)[(size_t)i * 18 + r] = A[r];
+}
+
+// Exact-basis condensation of float32 3D meshes on the matrix cores: the sums
+// of prep_band_body (W_j = sum_k w_jk H''_jk U_k over the upper blocks of row
+// j, Y = sum_j U_j^T W_j, b = sum_j U_j^T R_j^T g_j) for 5 NG vertices per
+// workgroup, CH positions of the band at a time.
+//
+// One v_mfma_f32_4x4x1 holds 16 independent 4 x 4 products.  The wave's four
+// rows of 16 lanes take four band rows j; the 15 columns of five vertices'
+// basis blocks are the lanes of a row (lane 15 idles), so that one
+// instruction forms one column s of one block: W_j[., col] += H''_jk[., s]
+// U_k[s, col].  The H'' column (four values: the block's three rows and, for
+// the diagonal block, g_j[s], which accumulates b in the fourth) is broadcast
+// to the row's four 4-lane blocks by the instruction itself (cbsz = 2), so a
+// wave reads a block as 12 floats per band row straight from the tile records.
+// Each product is a float32 FMA, as in prep_band_body; with three of four
+// rows and 15 of 16 columns used it does 180 FMAs in 8 cycles against the
+// 128 of two VALU instructions.  The U_j^T W_j products of the four band rows
+// are one v_mfma_f32_16x16x4 per component: lane row = k, so U and W are its
+// operands as they lie, and the vertices' 3 x 3 blocks lie on its diagonal.
+//
+// Position p of the basis rows lives in ring slot p mod R of its vertex, nine
+// words as in memory, so a chunk's refill is a flat copy and the records'
+// columns are LDS offsets computed once per mesh (tb_off), broadcast to a lane
+// row by a DPP addition.  The lane rows' band rows are 16 positions apart: with
+// nine words a slot and vertex strides of 3 mod 16 words, the 30 reads of a
+// half wave hit 30 banks wherever the columns keep the rows' distance, as
+// inside structured grids.  Rows past the last band row and blocks past a
+// row's count are zero records on a valid slot.
+//
+// What bounds it: the issue of the 27 matrix instructions (288 cycles) and
+// about 18 VALU ones (72) a wave spends on four band rows of five vertices; on
+// the 41x11x11 bar these are two thirds of the busy cycles, the LDS is busy
+// for half of them.  Two accumulator chains, since a dependent 4x4x1 product
+// waits longer than its 8 cycles (a phase of the loop alone: 402 against 467
+// cycles of 2.4 GHz).  The partial sums of a chunk are added up apart, which
+// keeps the rounding of the sums over up to 35,000 positions at that of
+// prep_band_body's many short ones.  Measured against prep_band_body, whole
+// launch: 41x11x11 bar 298 against 431 us, the 64-bar batch 2.94 against
+// 3.13 ms, the 81x21x21 beam's step 91 against 119 ms (from 1,024-thread
+// workgroups: one workgroup per CU fits, and eight waves took 117 ms).
+template <int NG, int NS, int CH>
+__device__ __forceinline__ void prep_tile_body(const MeshView& mv, int i0, int nv, const float* __restrict__ hb,
+                                               float* __restrict__ KL, float* smem, double* __restrict__ bout) {
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) float lds_float;
+  constexpr int V = 5 * NG, NT = 64 * NS, SEG = CH / (4 * NS), NR = 12, PHASES = SEG * NG;
+  constexpr int CFG = CH == TILE_CH[0] ? 0 : CH == TILE_CH[1] ? 1 : 2;
+  constexpr uint32_t PB = TILE_Q * 48, OB = TILE_Q * 4;   // bytes of one band row's records and offsets
+  static_assert(CH == TILE_CH[CFG] && NG == TILE_G[CFG] && NS == TILE_WAVES[CFG] && SEG * 4 * NS == CH &&
+                    PHASES % 2 == 0 && TILE_Q == 8, "configuration");
+  const int nf = mv.nf, nf9 = nf * 9;
+  const int R = CFG == 0 ? TILE_RING : tile_ring(CFG + 1, nf, mv.band_w), VS = tile_stride(R);
+  const int tid = threadIdx.x, l = tid % 64, w = __builtin_amdgcn_readfirstlane(tid / 64);
+  // A vertex's row is copied into its ring in pieces of 64 words, one word per
+  // lane.  What a piece reads past the row's end (the next row, or the padding
+  // past the last) is never used.
+  constexpr int UC = CH * 9 / 64, NP = (V * UC + NS - 1) / NS;   // pieces of a chunk per vertex, per wave
+  const __amdgpu_buffer_rsrc_t urs = buf_rsrc(mv.U_f + (size_t)i0 * nf9, (uint32_t)(nv * nf9 + 4096) * 4u);
+  const uint32_t gl4 = (uint32_t)l * 4u;
+  uint32_t wl4 = (uint32_t)(uintptr_t)(lds_float*)smem + gl4;
+  asm volatile("" : "+v"(wl4));
+  auto load_piece = [&](uint32_t at) { return __builtin_amdgcn_raw_buffer_load_b32(urs, gl4, at, 0); };
+  auto put_piece = [&](uint32_t at, uint32_t x) {
+    *(__attribute__((address_space(3))) uint32_t*)(uintptr_t)(wl4 + at) = x;
+  };
+  auto row4 = [&](int v) { return (uint32_t)((v < nv ? v : 0) * nf9) * 4u; };
+  auto ring4 = [&](int v) { return (uint32_t)(v * VS) * 4u; };
+  const int UF = R * 9 / 64, fill = V * UF;          // first fill: positions [0, R)
+  constexpr int FB = 17;                             // pieces in flight per wave
+  uint32_t first[FB];
+  auto fill_load = [&](int x0) {
+#pragma unroll
+    for (int e = 0; e < FB; ++e) {
+      const int k = min(x0 + e * NS, fill - 1);
+      first[e] = load_piece(row4(k / UF) + (uint32_t)(k % UF) * 256u);
+    }
+  };
+  fill_load(w);
+  tile_rows<V>(mv, i0, nv, w, hb, KL);               // A_i, while the fill is on its way
+  for (int x0 = w; x0 < fill; x0 += FB * NS) {
+#pragma unroll
+    for (int e = 0; e < FB; ++e) {
+      const int k = min(x0 + e * NS, fill - 1);
+      put_piece(ring4(k / UF) + (uint32_t)(k % UF) * 256u, first[e]);
+    }
+    if (x0 + FB * NS < fill) fill_load(x0 + FB * NS);
+  }
+  // the wave's pieces of a chunk: bytes from the chunk's first position in the rows and in the ring
+  uint32_t gat[NP], lat[NP];
+#pragma unroll
+  for (int e = 0; e < NP; ++e) {
+    const int x = min(w + e * NS, V * UC - 1);
+    gat[e] = row4(x / UC) + (uint32_t)(x % UC) * 256u;
+    lat[e] = ring4(x / UC) + (uint32_t)(x % UC) * 256u;
+    asm volatile("" : "+s"(gat[e]), "+s"(lat[e]));
+  }
+  const int q = l / 16, l16 = l % 16, col = min(l16, 14);
+  // LDS byte address of the lane's column in ring slot 0 (opaque, so that a
+  // read's address is one addition for every group)
+  uint32_t lbase = (uint32_t)(uintptr_t)(lds_float*)(smem + col / 3 * VS + col % 3);
+  asm volatile("" : "+v"(lbase));
+  // the lane row's first band row of a chunk: the lane rows are SP = 16 apart
+  constexpr int SP = 16, HALF = SP / SEG;            // HALF waves cover 4 SP band rows
+  const uint32_t rows = (uint32_t)(nf + TILE_PAD);
+  const __amdgpu_buffer_rsrc_t hrs = buf_rsrc(mv.tb, rows * PB);
+  const __amdgpu_buffer_rsrc_t ors = buf_rsrc(mv.tb_off[CFG], rows * OB);
+  const uint32_t lrow = (uint32_t)(w / HALF * 4 * SP + q * SP + w % HALF * SEG);
+  const uint32_t hoff = lrow * PB + (uint32_t)l16 * 4u, ooff = lrow * OB + (uint32_t)(l16 % TILE_Q) * 4u;
+  constexpr int NA = TILE_Q * 3 / 4;                 // registers of a record set: 4 of its 24 columns each
+  float A[SEG][NA], U[2][TILE_Q][3];
+  uint32_t O[SEG], at[TILE_Q];                       // O: lane r of a row holds the row's r-th block's offset
+  auto fetch_off = [&](int t, int p) { O[t] = __builtin_amdgcn_raw_buffer_load_b32(ors, ooff, (uint32_t)(p + t) * OB, 0); };
+  auto fetch_rec = [&](int t, int p) {
+#pragma unroll
+    for (int r = 0; r < NA; ++r)
+      A[t][r] = __builtin_bit_cast(
+          float, __builtin_amdgcn_raw_buffer_load_b32(hrs, hoff + 64u * r, (uint32_t)(p + t) * PB, 0));
+  };
+  auto addresses = [&](int t) {                      // row_newbcast:r
+    auto one = [&](auto rc) {
+      constexpr int r = decltype(rc)::value;
+      at[r] = lbase + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)O[t], 0x150 + r, 0xf, 0xf, true);
+    };
+    one(std::integral_constant<int, 0>()); one(std::integral_constant<int, 1>());
+    one(std::integral_constant<int, 2>()); one(std::integral_constant<int, 3>());
+    one(std::integral_constant<int, 4>()); one(std::integral_constant<int, 5>());
+    one(std::integral_constant<int, 6>()); one(std::integral_constant<int, 7>());
+  };
+  auto read_u = [&](int ub, int g) {
+#pragma unroll
+    for (int r = 0; r < TILE_Q; ++r) {
+      const lds_float* src = (const lds_float*)(uintptr_t)at[r];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) U[ub][r][c] = src[5 * tile_stride(TILE_RING) * g + 3 * c];
+    }
+  };
+  f4 Y[NG], Ysum[NG];                                // a chunk's products; the chunks before it
+  float bacc[NG], bsum[NG];
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    Ysum[g] = f4{0.f, 0.f, 0.f, 0.f};
+    bsum[g] = 0.f;
+  }
+  auto products = [&](int ub, const float (&a)[NA], int g) {
+    const float(&u)[TILE_Q][3] = U[ub];
+    // one 4-row column of H'' per instruction, column k in block k % 4 of
+    // register k / 4; two chains, since a product waits for the last one of its
+    f4 W = {0.f, 0.f, 0.f, 0.f}, X = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < 3 * TILE_Q; k += 4) {
+      W = __builtin_amdgcn_mfma_f32_4x4x1f32(a[k / 4], u[k / 3][k % 3], W, 2, 0, 0);
+      X = __builtin_amdgcn_mfma_f32_4x4x1f32(a[k / 4], u[(k + 1) / 3][(k + 1) % 3], X, 2, 1, 0);
+      W = __builtin_amdgcn_mfma_f32_4x4x1f32(a[k / 4], u[(k + 2) / 3][(k + 2) % 3], W, 2, 2, 0);
+      X = __builtin_amdgcn_mfma_f32_4x4x1f32(a[k / 4], u[(k + 3) / 3][(k + 3) % 3], X, 2, 3, 0);
+    }
+    W += X;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) Y[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(u[0][r], W[r], Y[g], 0, 0, 0);
+    bacc[g] += W[3];
+  };
+#pragma unroll
+  for (int t = 0; t < SEG; ++t) {
+    fetch_off(t, 0);
+    fetch_rec(t, 0);
+  }
+  uint32_t slot4 = 0;                                // bytes of the chunk's first ring slot
+  __syncthreads();
+  for (int p0 = 0; p0 < nf; p0 += CH) {
+    // chunk p0 + CH needs positions up to p0 + R + CH: read them ahead; they
+    // replace positions [p0, p0 + CH), which no later row reads
+    const bool refill = p0 + R < nf;
+    uint32_t pre[NP];
+    addresses(0);
+    read_u(0, 0);
+    fetch_off(0, p0 + CH);
+    if (refill) {
+      const uint32_t f4b = (uint32_t)(p0 + R) * 36u;
+#pragma unroll
+      for (int e = 0; e < NP; ++e) pre[e] = load_piece(gat[e] + f4b);
     }
 #pragma unroll
-    for (int r = 0; r < DD; ++r) A[r] = wave_sum63(A[r]);
-    if (l != 63) continue;
-    // A and Ht go to the vertex's K, L slots; dm_finish_body turns them into
-    // K and L with one thread per vertex.  b_i = U_i^T (R^T g)_C, the
-    // corotated basis's U_i^T g_C.
-    const T* Yt = tot + v * NR;
-    auto* out = gptr_w(KL) + (size_t)i * 2 * DD;
+    for (int g = 0; g < NG; ++g) {
+      Y[g] = f4{0.f, 0.f, 0.f, 0.f};
+      bacc[g] = 0.f;
+    }
+    // phases (band row t, vertex group g): the U columns one phase ahead, the
+    // next chunk's records and offsets once this one's are used up.  Loads
+    // return in order, so nothing waits for the basis pieces (from HBM)
+    // before the chunk's end.  The barriers keep the compiler from moving
+    // the reads next to their uses.
 #pragma unroll
-    for (int r = 0; r < D; ++r)
-#pragma unroll
-      for (int c = 0; c < D; ++c) {
-        out[r * D + c] = A[r * D + c];
-        out[DD + r * D + c] = Yt[r * D + c] + Yt[c * D + r];
+    for (int f = 0; f < PHASES; ++f) {
+      const int t = f / NG, g = f % NG;
+      if (f + 1 < PHASES) {
+        if (g + 1 == NG) addresses(t + 1);
+        read_u((f + 1) & 1, (f + 1) % NG);
+        if (g + 1 == NG) fetch_off(t + 1, p0 + CH);
       }
-    if (bout != nullptr)
+      __builtin_amdgcn_sched_barrier(0);
+      products(f & 1, A[t], g);
+      if (g + 1 == NG) fetch_rec(t, p0 + CH);
+      __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
-      for (int r = 0; r < D; ++r) gptr_w(bout)[(size_t)r * mv.n + i] = double(Yt[DD + r]);
+    for (int g = 0; g < NG; ++g) {
+      Ysum[g] += Y[g];
+      bsum[g] += bacc[g];
+    }
+    if (refill) {
+      __syncthreads();                               // chunk p0's ring reads are done
+#pragma unroll
+      for (int e = 0; e < NP; ++e) put_piece(lat[e] + slot4, pre[e]);
+      slot4 += (uint32_t)(CH * 36);
+      if (slot4 == (uint32_t)(R * 36)) slot4 = 0;
+      __syncthreads();
+    }
+  }
+  __syncthreads();
+  // Ht_i = Y + Y^T and b_i: sums over the waves (and for b the lane rows) in a
+  // fixed order; lane l's Y[i] is entry (4 (l / 16) + i, l % 16) of a group's
+  // 15 x 15 column products, of which the vertices' own 3 x 3 blocks are used
+  float* red = smem;                                 // [NS][NG][5][64], the ring is free now
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) red[((w * NG + g) * 5 + k) * 64 + l] = Ysum[g][k];
+    red[((w * NG + g) * 5 + 4) * 64 + l] = bsum[g];
+  }
+  __syncthreads();
+  for (int e = tid; e < nv * NR; e += NT) {
+    const int v = e / NR, k = e % NR, c3 = 3 * (v % 5);
+    float acc = 0.f, acc_t = 0.f;
+    for (int ww = 0; ww < NS; ++ww) {
+      const float* rw = red + (ww * NG + v / 5) * 5 * 64;
+      if (k < 9) {
+        const int r = c3 + k / 3, c = c3 + k % 3;
+        acc += rw[(r % 4) * 64 + (r / 4) * 16 + c];
+        acc_t += rw[(c % 4) * 64 + (c / 4) * 16 + r];
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc += rw[4 * 64 + r * 16 + c3 + k - 9];
+      }
+    }
+    if (k < 9) gptr_w(KL)[(size_t)(i0 + v) * 18 + 9 + k] = acc + acc_t;
+    else if (bout != nullptr) gptr_w(bout)[(size_t)(k - 9) * mv.n + i0 + v] = double(acc);
   }
 }
 
@@ -974,6 +1301,14 @@ __global__ void __launch_bounds__(CH) k_cc_prep_band(MeshView mv, int method, in
                                bout);
 }
 
+template <int NG, int NS, int CH>
+__global__ void __launch_bounds__(64 * NS, 4)
+k_cc_prep_tile(MeshView mv, int v0, int v1, const float* __restrict__ hb, float* __restrict__ KL,
+               double* __restrict__ bout) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const int i0 = v0 + blockIdx.x * 5 * NG;
+  prep_tile_body<NG, NS, CH>(mv, i0, min(5 * NG, v1 - i0), hb, KL, reinterpret_cast<float*>(smem_raw), bout);
+}
 
 // dx_i = -K_i (g_i - L_i U_i^T g_C); written to d (Jacobi) or added to x
 // (coloured sweep).  G lanes per vertex share its support.
@@ -1292,27 +1627,27 @@ void launch_elem_hess(const MeshView& mv, int prec, const double* x, const Mater
 }
 
 void launch_assemble(const MeshView& mv, int prec, const void* estore, const Material& mat,
-                     void* hb, hipStream_t s) {
-  launch_assemble_list(mv, prec, estore, mat, hb, s, nullptr, mv.nnzb);
+                     void* hb, const double* g, hipStream_t s) {
+  launch_assemble_list(mv, prec, estore, mat, hb, g, s, nullptr, mv.nnzb);
 }
 
-void launch_band_copy(const MeshView& mv, int prec, const void* hb, hipStream_t s) {
+void launch_band_copy(const MeshView& mv, int prec, const void* hb, const double* g, hipStream_t s) {
   if (mv.hq == nullptr || mv.nnzb <= 0) return;
   const int nb = nblocks(mv.nnzb, EWG);
-  if (prec == 0) CC_DISPATCH_D(mv.D, k_band_copy<double, D><<<nb, EWG, 0, s>>>(mv, (const double*)hb));
-  else CC_DISPATCH_D(mv.D, k_band_copy<float, D><<<nb, EWG, 0, s>>>(mv, (const float*)hb));
+  if (prec == 0) CC_DISPATCH_D(mv.D, k_band_copy<double, D><<<nb, EWG, 0, s>>>(mv, (const double*)hb, g));
+  else CC_DISPATCH_D(mv.D, k_band_copy<float, D><<<nb, EWG, 0, s>>>(mv, (const float*)hb, g));
 }
 
 void launch_assemble_list(const MeshView& mv, int prec, const void* estore, const Material& mat, void* hb,
-                          hipStream_t s, const int* slist, int count) {
+                          const double* g, hipStream_t s, const int* slist, int count) {
   if (count <= 0) return;
   const int nb = nblocks(count, EWG);
   if (prec == 0)
     CC_DISPATCH_D(mv.D, k_assemble<double, D><<<nb, EWG, 0, s>>>(mv, (const double*)estore, mat.w_in,
-                                                               (double*)hb, slist, count));
+                                                               (double*)hb, g, slist, count));
   else
     CC_DISPATCH_D(mv.D, k_assemble<float, D><<<nb, EWG, 0, s>>>(mv, (const float*)estore, (float)mat.w_in,
-                                                              (float*)hb, slist, count));
+                                                              (float*)hb, g, slist, count));
 }
 
 constexpr int GRAD_G = 16;   // lanes per vertex of the gradient: a 3D star holds about 24 elements
@@ -1423,6 +1758,45 @@ DenseCfg dense_config(const int* nf, const int* band_w, int count, int D, int pr
   return best;
 }
 
+size_t tile_lds_bytes(int cfg, int nf, int band_w) {
+  const int v = 5 * TILE_G[cfg - 1];
+  const size_t ring = (size_t)v * tile_stride(tile_ring(cfg, nf, band_w)) * 4;
+  return std::max(ring, (size_t)TILE_WAVES[cfg - 1] * v * 64 * 4);   // the final sums reuse the ring
+}
+
+// Ten vertices per workgroup share each record load and give two workgroups
+// of eight waves per CU; below 400 such workgroups (a launch that does not
+// fill the chip twice: a single bar, or one colour of a coloured sweep) five
+// vertices spread further: the 29x9x7 bar's 353 five-vertex workgroups take 67
+// us, in sixteen waves each (one per CU) 86 us.  Where the band leaves one
+// workgroup per CU (the beam: 138 KB), it has sixteen waves.
+int tile_config(const int* nf, const int* band_w, const int* rows, int count) {
+  size_t lds[TILE_N + 1] = {};
+  long long wgs = 0;
+  bool ring = true;
+  for (int m = 0; m < count; ++m) {
+    for (int c = 1; c <= TILE_N; ++c) lds[c] = std::max(lds[c], tile_lds_bytes(c, nf[m], band_w[m]));
+    ring = ring && (band_w[m] + TILE_CH[0] <= TILE_RING || nf[m] <= TILE_RING);
+    wgs += nblocks(rows[m], 10);
+  }
+  if (ring && 2 * lds[1] <= g_lds_limit && wgs >= 400) return 1;
+  if (2 * lds[3] <= g_lds_limit) return 3;
+  return lds[2] <= g_lds_limit ? 2 : lds[3] <= g_lds_limit ? 3 : 0;
+}
+
+bool tile_usable(const MeshView& mv, int prec, int tv_cap, int chunk) {
+  if (prec != 1 || mv.D != 3 || tv_cap != 0 || chunk != 0 || mv.tb == nullptr || !mv.dense_supp || mv.nf < 2)
+    return false;
+  return tile_config(&mv.nf, &mv.band_w, &mv.nf, 1) > 0;
+}
+
+#define CC_DISPATCH_TILE(cfg, ...)                                                    \
+  do {                                                                                \
+    if ((cfg) == 1) { constexpr int NG = 2, NS = 8, CH = 64; __VA_ARGS__; }           \
+    else if ((cfg) == 2) { constexpr int NG = 1, NS = 16, CH = 256; __VA_ARGS__; }    \
+    else { constexpr int NG = 1, NS = 8, CH = 128; __VA_ARGS__; }                     \
+  } while (0)
+
 #define CC_DISPATCH_TVCH(tv, ch, ...)                                                 \
   switch ((tv) * 1000 + (ch)) {                                                       \
     case 1128: { constexpr int TV = 1, CH = 128; __VA_ARGS__; } break;                \
@@ -1452,6 +1826,16 @@ static bool prep_dense(const MeshView& mv, int prec, int method, int v0, int v1,
                        void* KL, unsigned long long* fb, const double* g, double* dout, double* xmove,
                        int tv_cap, int chunk, hipStream_t s) {
   if (method == 0 || !band_ok(mv, prec)) return false;
+  if constexpr (sizeof(T) == 4 && D == 3)
+    if (mv.tile) {
+      const int rows = v1 - v0, cfg = tile_config(&mv.nf, &mv.band_w, &rows, 1);
+      CC_DISPATCH_TILE(cfg, k_cc_prep_tile<NG, NS, CH><<<nblocks(rows, 5 * NG), 64 * NS,
+                                                       tile_lds_bytes(cfg, mv.nf, mv.band_w), s>>>(
+                                mv, v0, v1, (const float*)hb, (float*)KL, g != nullptr ? dout : nullptr));
+      k_cc_dm_finish<T, D><<<nblocks(v1 - v0, WG), WG, 0, s>>>(mv, method, v0, v1, (const T*)hb, (T*)KL, fb,
+                                                              g, dout, g != nullptr ? xmove : nullptr);
+      return true;
+    }
   const DenseCfg dc = dense_config(&mv.nf, &mv.band_w, 1, D, prec, tv_cap, chunk);
   if (dc.tv == 0) return false;
   CC_DISPATCH_TVCH(dc.tv, dc.ch, k_cc_prep_band<T, D, TV, CH><<<nblocks(v1 - v0, TV), CH, dc.lds, s>>>(
@@ -1740,7 +2124,7 @@ __global__ void __launch_bounds__(EWG) kb_assemble(const BatchItem* __restrict__
   const int* sl = lst ? mv.csl + mv.csl_ptr[colour] : nullptr;
   const int cnt = lst ? mv.csl_ptr[colour + 1] - mv.csl_ptr[colour] : mv.nnzb;
   assemble_body<T, D>(mv, (bx - boff[mi]) * EWG + threadIdx.x, (const T*)it.estore,
-                      T(it.mat.w_in), (T*)it.hb, sl, cnt);
+                      T(it.mat.w_in), (T*)it.hb, mv.tile ? it.g : nullptr, sl, cnt);
 }
 
 // Every BandRec of the dense-basis meshes from their block rows and current
@@ -1758,7 +2142,7 @@ __global__ void __launch_bounds__(EWG) kb_band_copy(const BatchItem* __restrict_
   const MeshView& mv = it.mv;
   if (mv.hq == nullptr) return;
   const int t = (bx - boff[mi]) * EWG + threadIdx.x;
-  if (t < mv.nnzb) band_rec_write<T, D>(mv, t, mv.blkrow[t], (const T*)it.hb + (size_t)t * D * D);
+  if (t < mv.nnzb) band_rec_write<T, D>(mv, t, mv.blkrow[t], (const T*)it.hb + (size_t)t * D * D, mv.tile ? it.g : nullptr);
 }
 
 template <int D, int G, bool FCR>
@@ -1803,20 +2187,39 @@ __global__ void __launch_bounds__(WG) kb_prep(const BatchItem* __restrict__ item
 }
 
 // Dense-basis meshes of a batch: TV vertices per workgroup (prep_band_body).
+// Blocks boff[k] .. boff[k + 1] belong to mesh order[k]: the meshes by falling
+// nf, since a workgroup's time grows with nf and the launch ends sooner when
+// the long workgroups start first.
 template <typename T, int D, int TV, int CH>
 __global__ void __launch_bounds__(CH) kb_prep_band(const BatchItem* __restrict__ items,
                                                     const BatchCtl* __restrict__ ctl,
-                                                    const int* __restrict__ boff, int nmesh,
+                                                    const int* __restrict__ boff,
+                                                    const int* __restrict__ order, int nmesh,
                                                     int method, int colour, int fuse) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int mi = block_mesh(boff, nmesh, blockIdx.x);
+  const int slot = block_mesh(boff, nmesh, blockIdx.x), mi = order[slot];
   if (!ctl[mi].active) return;
   const BatchItem& it = items[mi];
   int v0, v1;
   vertex_range(it, colour, v0, v1);
-  const int i0 = v0 + (blockIdx.x - boff[mi]) * TV;
+  const int i0 = v0 + (blockIdx.x - boff[slot]) * TV;
   prep_band_body<T, D, TV, CH>(it.mv, method, i0, min(TV, v1 - i0), (const T*)it.hb, (T*)it.KL,
                            reinterpret_cast<T*>(smem_raw), fuse ? it.g : nullptr, fuse ? it.d : nullptr);
+}
+
+template <int NG, int NS, int CH>
+__global__ void __launch_bounds__(64 * NS, 4)
+kb_prep_tile(const BatchItem* __restrict__ items, const BatchCtl* __restrict__ ctl, const int* __restrict__ boff,
+             const int* __restrict__ order, int nmesh, int colour, int fuse) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const int slot = block_mesh(boff, nmesh, blockIdx.x), mi = order[slot];
+  if (!ctl[mi].active) return;
+  const BatchItem& it = items[mi];
+  int v0, v1;
+  vertex_range(it, colour, v0, v1);
+  const int i0 = v0 + (blockIdx.x - boff[slot]) * 5 * NG;
+  prep_tile_body<NG, NS, CH>(it.mv, i0, min(5 * NG, v1 - i0), (const float*)it.hb, (float*)it.KL,
+                             reinterpret_cast<float*>(smem_raw), fuse ? it.d : nullptr);
 }
 
 template <typename T, int D>
@@ -2160,10 +2563,13 @@ struct BatchPlan {
   Offsets eg;       // energy then gradient blocks of each mesh (kb_energy_grad)
   std::vector<Offsets> elemc, asmbc;   // element / slot blocks of colour c's dirty lists
   std::vector<Offsets> prep, prepd, fin, upd;   // index 0: all free vertices, c+1: colour c
+  std::vector<int> dorder_h;  // meshes by falling nf: the order of prepd's blocks
+  int* dorder = nullptr;
   int max_colours = 0;
   int tv = 0;       // vertices per workgroup of the dense condensation (0: no dense mesh)
   int ch = 0;       // its chunk of band positions (= workgroup size)
   size_t lds = 0;   // its dynamic LDS
+  int tile = 0;     // configuration of the matrix-core condensation (tile_config; 0: rows of tv)
   int scap = 0;     // staged support blocks per vertex of the sparse condensation (0: none)
   size_t slds = 0;  // its dynamic LDS
   double* wpart = nullptr;   // energy partials of LS_WIDTH backtracking steps
@@ -2221,7 +2627,7 @@ static void plan_vertex_offsets(BatchPlan* p, hipStream_t s) {
       else { v0 = v1 = 0; }
       const int cnt = v1 - v0;
       cp[m] = it.prep_dense ? 0 : nblocks(cnt, WG / G);
-      cd[m] = it.prep_dense ? nblocks(cnt, p->tv) : 0;
+      cd[m] = it.prep_dense ? nblocks(cnt, p->tile > 0 ? 5 * TILE_G[p->tile - 1] : p->tv) : 0;
       cf[m] = it.prep_dense ? nblocks(cnt, WG) : 0;
       // dense meshes get their direction from the fused condensation: in a
       // Jacobi sweep, and per colour in a coloured sweep with per-colour Hessians
@@ -2230,7 +2636,9 @@ static void plan_vertex_offsets(BatchPlan* p, hipStream_t s) {
       cu[m] = fused ? 0 : nblocks(cnt, WG / G);
     }
     offsets_build(p->prep[c + 1], cp, s);
-    offsets_build(p->prepd[c + 1], cd, s);
+    std::vector<int> cdo(p->nmesh);
+    for (int m = 0; m < p->nmesh; ++m) cdo[m] = cd[p->dorder_h[m]];
+    offsets_build(p->prepd[c + 1], cdo, s);
     offsets_build(p->fin[c + 1], cf, s);
     offsets_build(p->upd[c + 1], cu, s);
   }
@@ -2279,6 +2687,25 @@ BatchPlan* batch_plan_create(const BatchItem* items_host, int nmesh, const Batch
       p->lds = dc.lds;
       if (dc.tv == 0)
         for (int m = 0; m < nmesh; ++m) p->items_h[m].prep_dense = 0;
+      // float32 3D meshes with tile records, unless a row count or a chunk is
+      // forced: the matrix-core condensation
+      bool tiles = dc.tv > 0;
+      std::vector<int> rows;
+      for (int m = 0; m < nmesh; ++m)
+        if (p->items_h[m].prep_dense) {
+          const BatchItem& it = p->items_h[m];
+          tiles = tiles && tile_usable(it.mv, cfg.prec, cfg.tv_cap, cfg.chunk);
+          rows.push_back(cfg.sweep == 1 && it.ncol > 0 ? it.mv.nf / it.ncol : it.mv.nf);
+        }
+      if (tiles) {
+        p->tile = tile_config(dense_nf.data(), dense_bw.data(), rows.data(), (int)rows.size());
+        if (p->tile > 0) {
+          p->lds = 0;
+          for (size_t m = 0; m < rows.size(); ++m)
+            p->lds = std::max(p->lds, tile_lds_bytes(p->tile, dense_nf[m], dense_bw[m]));
+          for (BatchItem& it : p->items_h) it.mv.tile = it.prep_dense;
+        }
+      }
     }
   }
   int sparse_supp = 0;
@@ -2319,6 +2746,12 @@ BatchPlan* batch_plan_create(const BatchItem* items_host, int nmesh, const Batch
   offsets_build(p->axpyj, caxj, s);
   offsets_build(p->feat, cfeat, s);
   offsets_build(p->rotn, crot, s);
+  p->dorder_h.resize(nmesh);
+  for (int m = 0; m < nmesh; ++m) p->dorder_h[m] = m;
+  std::stable_sort(p->dorder_h.begin(), p->dorder_h.end(),
+                   [&](int a, int b) { return p->items_h[a].mv.nf > p->items_h[b].mv.nf; });
+  (void)hipMalloc(&p->dorder, nmesh * sizeof(int));
+  (void)hipMemcpyAsync(p->dorder, p->dorder_h.data(), nmesh * sizeof(int), hipMemcpyHostToDevice, s);
   plan_vertex_offsets(p, s);
   (void)hipMalloc(&p->items_d, nmesh * sizeof(BatchItem));
   (void)hipMalloc(&p->ctl_d, nmesh * sizeof(BatchCtl));
@@ -2339,12 +2772,14 @@ void batch_plan_destroy(BatchPlan* p) {
   for (auto& o : p->upd) offsets_free(o);
   for (auto& o : p->elemc) offsets_free(o);
   for (auto& o : p->asmbc) offsets_free(o);
+  if (p->dorder) (void)hipFree(p->dorder);
   if (p->wpart) (void)hipFree(p->wpart);
   if (p->items_d) (void)hipFree(p->items_d);
   if (p->ctl_d) (void)hipFree(p->ctl_d);
   delete p;
 }
 
+int batch_tile(BatchPlan* p) { return p->tile; }
 BatchItem* batch_items_dev(BatchPlan* p) { return p->items_d; }
 BatchCtl* batch_ctl_dev(BatchPlan* p) { return p->ctl_d; }
 
@@ -2383,8 +2818,13 @@ static void b_prep(BatchPlan* p, int colour, hipStream_t s, int fuse = 0) {
                                                   colour, p->scap);
   if (gridn(od) > 0) {
     const Offsets& of = p->fin[colour + 1];
-    CC_DISPATCH_TVCH(p->tv, p->ch, kb_prep_band<T, D, TV, CH><<<gridn(od), CH, p->lds, s>>>(
-                              p->items_d, p->ctl_d, od.d, p->nmesh, p->cfg.method, colour, fuse));
+    if (p->tile > 0) {
+      CC_DISPATCH_TILE(p->tile, kb_prep_tile<NG, NS, CH><<<gridn(od), 64 * NS, p->lds, s>>>(
+                                    p->items_d, p->ctl_d, od.d, p->dorder, p->nmesh, colour, fuse));
+    } else {
+      CC_DISPATCH_TVCH(p->tv, p->ch, kb_prep_band<T, D, TV, CH><<<gridn(od), CH, p->lds, s>>>(
+                                p->items_d, p->ctl_d, od.d, p->dorder, p->nmesh, p->cfg.method, colour, fuse));
+    }
     kb_dm_finish<T, D><<<gridn(of), WG, 0, s>>>(p->items_d, p->ctl_d, of.d, p->nmesh, p->cfg.method,
                                                colour, fuse);
   }
@@ -2420,7 +2860,7 @@ static void b_hessian(BatchPlan* p, int which, hipStream_t s, int colour = -1) {
     kb_assemble<T, D><<<gridn(oa), EWG, 0, s>>>(p->items_d, p->ctl_d, oa.d, p->nmesh, colour);
     // the band records of blocks the partial assembly left alone still
     // carry the previous rotations
-    if (colour >= 0 && gridn(p->rotn) > 0 && p->tv > 0)
+    if (colour >= 0 && gridn(p->rotn) > 0 && (p->tv > 0 || p->tile > 0))
       kb_band_copy<T, D><<<gridn(p->asmb), EWG, 0, s>>>(p->items_d, p->ctl_d, p->asmb.d, p->nmesh);
     p->mark(1, 0);
   }
@@ -2444,8 +2884,7 @@ static void b_iteration(BatchPlan* p, hipStream_t s) {
     for (int col = 0; col < p->max_colours; ++col) {
       // per-colour Hessians: all of them at the sweep's start, then only the
       // elements and block slots the previous colour's moves changed
-      if (c.hess_refresh == 0) b_hessian<T, D>(p, 1, s, col == 0 ? -1 : col - 1);
-      else if (col == 0) {
+      if (c.hess_refresh != 0 && col == 0) {
         b_hessian<T, D>(p, 1, s);
         b_prep<T, D, G>(p, -1, s);
       }
@@ -2455,9 +2894,13 @@ static void b_iteration(BatchPlan* p, hipStream_t s) {
                                        p->items_d, p->ctl_d, p->grad.d, nm, 1, 0));
         p->mark(2, 0);
       }
-      // dense meshes form b_i from the fresh gradient and move the colour's
-      // vertices in the finish kernel; sparse ones take the update kernel
-      if (c.hess_refresh == 0) b_prep<T, D, G>(p, col, s, 2);
+      // dense meshes form b_i from the fresh gradient (which the assembly
+      // stores with tile records) and move the colour's vertices in the finish
+      // kernel; sparse ones take the update kernel
+      if (c.hess_refresh == 0) {
+        b_hessian<T, D>(p, 1, s, col == 0 ? -1 : col - 1);
+        b_prep<T, D, G>(p, col, s, 2);
+      }
       b_update<T, D, G>(p, col, 1, s);
     }
   }
