@@ -2323,10 +2323,10 @@ cc_status cc_mlp_gradient(cc_ctx* ctx, const float* X, const float* T, const int
     if (B <= 0 || !X || !T || !idx) return fail(ctx, CC_E_INVALID_ARG, "bad gradient arguments");
     cc::MlpState& q = ctx->mlp;
     cc::mlp_gradient(q, X, T, idx, B, grad ? grad : q.grad, q.loss, ctx->stream);
-    float l = 0.f;
-    HIPC(hipMemcpyAsync(&l, q.loss, sizeof(float), hipMemcpyDeviceToHost, ctx->stream));
+    // through pinned memory: a copy to pageable memory is staged and waited for
+    HIPC(hipMemcpyAsync(ctx->pinned, q.loss, sizeof(float), hipMemcpyDeviceToHost, ctx->stream));
     HIPC(hipStreamSynchronize(ctx->stream));
-    if (loss) *loss = l;
+    if (loss) std::memcpy(loss, ctx->pinned, sizeof(float));
     return CC_OK;
   });
 }

@@ -1,8 +1,8 @@
 // Learned per-vertex warm start: feature extraction, and a 32-64-64-16 SiLU
 // network whose products run on BF16 MFMA (v_mfma_f32_16x16x16_bf16) with
-// FP32 accumulation.  One wave owns a tile of 16 rows; activations move
-// between layers through LDS to turn the accumulator layout into the operand
-// layout.  Weight gradients are accumulated per wave and reduced in a fixed
+// FP32 accumulation.  One wave owns a tile of 16 rows; in training, activations
+// move between layers through LDS to turn the accumulator layout into the
+// operand layout (inference forms the layers transposed and needs none).  Weight gradients are accumulated per wave and reduced in a fixed
 // order, so training is bit-reproducible.
 //
 // MFMA 16x16x16 lane layout (lane l, element i of the 4-vector):
@@ -13,6 +13,8 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
+
+#include <algorithm>
 
 #include "cc_device.h"
 #include "cc_mlp.h"
@@ -152,33 +154,81 @@ __device__ __forceinline__ void tile_forward(const MlpDev& net, const uint16_t* 
 }
 
 // Inference: rows of raw features (stride 16) -> first 3 outputs (stride 3).
+// Every layer is formed transposed, Z^T = W^T X^T: the weights' B fragments
+// are the A operands of W^T as they lie, and the result layout (lane: batch
+// row l % 16, units 4 (l / 16) + i of m-tile t) is the next layer's B operand
+// of k-step t.  So the activations never leave the registers, where the
+// row-major form took them through LDS one 16-bit value at a time; each sum
+// runs over the same products in the same order.  A wave keeps the weights in
+// registers and takes every gridDim-th tile.  Bound by the exponentials and
+// divisions of the 128 activations a row; 105,438 rows: 46 us before (1,024
+// waves, LDS transposes, three workgroup barriers a tile), 19 us now.
 __global__ void __launch_bounds__(64 * MLP_WAVES) k_mlp_forward(MlpDev net, const float* __restrict__ X,
                                                                 int B, float* __restrict__ Y) {
-  __shared__ uint16_t lds[MLP_WAVES][16 * 16 + 2 * 16 * 64];
-  const int w = threadIdx.x / 64, l = threadIdx.x % 64;
-  uint16_t* xt = lds[w];
-  uint16_t* a1 = xt + 256;
-  uint16_t* a2 = a1 + 16 * 64;
-  const int tiles = (B + 15) / 16;
-  // every wave of the workgroup runs the same number of tile iterations so the
-  // workgroup barriers inside tile_forward line up
-  const int per = (tiles + gridDim.x * MLP_WAVES - 1) / (gridDim.x * MLP_WAVES);
-  for (int it = 0; it < per; ++it) {
-    const int tile = (blockIdx.x * MLP_WAVES + w) + it * gridDim.x * MLP_WAVES;
-    const int r0 = tile * 16;
-    const int rows = tile < tiles ? min(16, B - r0) : 0;
-    load_input(xt, rows, net, [&](int r) { return X + (size_t)(r0 + r) * MLP_IN; }, l);
-    __syncthreads();
-    floatx4 Z1[4], Z2[4], y;
-    tile_forward(net, xt, a1, a2, Z1, Z2, y, l);
-    if ((l % 16) < MLP_NOUT) {
+  const int l = threadIdx.x % 64, n = l % 16, k4 = 4 * (l / 16);
+  bf16x4 w1[4], w2[4][4], w3[4];
+  floatx4 b1[4], b2[4], b3, mean, istd;
+  auto load4 = [](const float* p) {
+    floatx4 v;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int r = 4 * (l / 16) + i;
-        if (r < rows) Y[(size_t)(r0 + r) * MLP_NOUT + (l % 16)] = y[i];
-      }
+    for (int i = 0; i < 4; ++i) v[i] = p[i];
+    return v;
+  };
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    w1[t] = bfrag(net.W1b, MLP_HID, 0, t, l);        // features 16..31 are zero padding
+    w3[t] = bfrag(net.W3b, MLP_OUT, t, 0, l);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) w2[t][s] = bfrag(net.W2b, MLP_HID, s, t, l);
+    b1[t] = load4(net.W + MLP_B1 + 16 * t + k4);
+    b2[t] = load4(net.W + MLP_B2 + 16 * t + k4);
+  }
+  b3 = load4(net.W + MLP_B3 + k4);
+  mean = load4(net.mean + k4);
+  istd = load4(net.istd + k4);
+  const int tiles = (B + 15) / 16;
+  auto input = [&](int tile) {
+    const int r = tile * 16 + n;
+    floatx4 v = {0.f, 0.f, 0.f, 0.f};
+    if (tile < tiles && r < B) {
+      v = load4(X + (size_t)r * MLP_IN + k4);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = (v[i] - mean[i]) * istd[i];
     }
-    __syncthreads();
+    return v;
+  };
+  const int step = gridDim.x * MLP_WAVES;
+  int tile = blockIdx.x * MLP_WAVES + threadIdx.x / 64;
+  floatx4 v = input(tile);
+  for (; tile < tiles; tile += step) {
+    const bf16x4 x = to_bf(v);
+    v = input(tile + step);                          // the next tile's rows, ahead of their use
+    bf16x4 a1[4], a2[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      floatx4 c = {0.f, 0.f, 0.f, 0.f};
+      c = mfma(w1[t], x, c);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) c[i] = silu(c[i] + b1[t][i]);
+      a1[t] = to_bf(c);
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      floatx4 c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < 4; ++s) c = mfma(w2[t][s], a1[s], c);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) c[i] = silu(c[i] + b2[t][i]);
+      a2[t] = to_bf(c);
+    }
+    floatx4 y = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < 4; ++s) y = mfma(w3[s], a2[s], y);
+    const int r = tile * 16 + n;
+    if (l < 16 && r < B) {                           // units 0..3 of the batch row
+#pragma unroll
+      for (int i = 0; i < MLP_NOUT; ++i) Y[(size_t)r * MLP_NOUT + i] = y[i] + b3[i];
+    }
   }
 }
 
@@ -313,20 +363,36 @@ __global__ void __launch_bounds__(64 * MLP_WAVES) k_mlp_train(MlpDev net, const 
   if (l == 0) lpart[blockIdx.x * MLP_WAVES + w] = loss;
 }
 
-// Fixed-order sum of the per-wave partials: grad[p] = sum_w part[w][p].
-__global__ void k_mlp_sum(const float* __restrict__ part, int nwaves, float* __restrict__ grad,
-                          const float* __restrict__ lpart, float* __restrict__ loss, int B) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p < MLP_NPARAM) {
-    float s = 0.f;
-    for (int w = 0; w < nwaves; ++w) s += part[(size_t)w * MLP_NPARAM + p];
-    grad[p] = s;
+// Sum of the per-wave partials, grad[p] = sum_w part[w][p], in a fixed order:
+// a workgroup takes 64 parameters, its wave k the partials k, k + 16, ..., and
+// the 16 sums are added in turn.  (One thread per parameter walked the 256
+// partials of a 4,096-row batch one after another: 66 us for 7.5 MB, 4 us now.)
+constexpr int SUM_W = 16;
+__global__ void __launch_bounds__(64 * SUM_W) k_mlp_sum(const float* __restrict__ part, int nwaves,
+                                                        float* __restrict__ grad,
+                                                        const float* __restrict__ lpart,
+                                                        float* __restrict__ loss, int B) {
+  __shared__ float red[SUM_W][64];
+  const int k = threadIdx.x / 64, l = threadIdx.x % 64, p = blockIdx.x * 64 + l;
+  float s = 0.f;
+  if (blockIdx.x == gridDim.x - 1) {                 // the last workgroup: the loss
+    for (int w = threadIdx.x; w < nwaves; w += 64 * SUM_W) s += lpart[w];
+  } else if (p < MLP_NPARAM) {
+#pragma unroll 8
+    for (int w = k; w < nwaves; w += SUM_W) s += part[(size_t)w * MLP_NPARAM + p];
   }
-  if (p == 0) {
-    float s = 0.f;
-    for (int w = 0; w < nwaves; ++w) s += lpart[w];
-    loss[0] = s / (float(B) * MLP_NOUT);
+  red[k][l] = s;
+  __syncthreads();
+  if (k != 0) return;
+  float t = 0.f;
+#pragma unroll
+  for (int w = 0; w < SUM_W; ++w) t += red[w][l];
+  if (blockIdx.x < gridDim.x - 1) {
+    if (p < MLP_NPARAM) grad[p] = t;
+    return;
   }
+  for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+  if (l == 0) loss[0] = t / (float(B) * MLP_NOUT);
 }
 
 // Adam on the FP32 masters; refreshes the bf16 copies of the weight matrices.
@@ -539,14 +605,17 @@ void mlp_refresh_bf16(const MlpState& s, hipStream_t st) {
 
 void mlp_forward(const MlpState& s, const float* X, int B, float* Y, hipStream_t st) {
   if (B <= 0) return;
-  k_mlp_forward<<<mlp_blocks(B), 64 * MLP_WAVES, 0, st>>>(netdev(s), X, B, Y);
+  // up to four workgroups per CU, each wave loading the weights once
+  const int tiles = (B + 15) / 16;
+  const int blocks = std::min((tiles + MLP_WAVES - 1) / MLP_WAVES, 4 * MLP_MAX_BLOCKS);
+  k_mlp_forward<<<blocks, 64 * MLP_WAVES, 0, st>>>(netdev(s), X, B, Y);
 }
 
 void mlp_gradient_into(const MlpState& s, const float* X, const float* T, const int* idx, int B, float* grad,
                        float* loss, float* part, float* lpart, hipStream_t st) {
   const int nb = mlp_blocks(B);
   k_mlp_train<<<nb, 64 * MLP_WAVES, 0, st>>>(netdev(s), X, T, idx, B, part, lpart);
-  k_mlp_sum<<<(MLP_NPARAM + 255) / 256, 256, 0, st>>>(part, nb * MLP_WAVES, grad, lpart, loss, B);
+  k_mlp_sum<<<(MLP_NPARAM + 63) / 64 + 1, 64 * SUM_W, 0, st>>>(part, nb * MLP_WAVES, grad, lpart, loss, B);
 }
 
 void mlp_gradient(const MlpState& s, const float* X, const float* T, const int* idx, int B, float* grad,
