@@ -212,6 +212,7 @@ struct cc_ctx {
   std::string err;
   std::vector<Mesh*> meshes;
   double* pinned = nullptr;  // host pinned scalars
+  cc::DeviceScratch basis_ws;  // workspace of the exact-basis build
   cc::MlpState mlp;          // learned warm start
   float *bfeat = nullptr, *bdelta = nullptr;  // batch-wide feature / output rows
   size_t bcap = 0;
@@ -993,7 +994,8 @@ void build_basis(cc_ctx* ctx, Mesh& M, int radius, double dt, int quasi, const d
       dfree(Ud); dfree(Uf);
       throw;
     }
-    const int rc = cc::exact_basis_band(mv, (const double*)M.hb, loff.data(), (int)loff.size() - 1, Ud, Uf, s);
+    const int rc = cc::exact_basis_band(mv, (const double*)M.hb, loff.data(), (int)loff.size() - 1, Ud, Uf,
+                                        ctx->basis_ws, s);
     if (rc != 0) {
       dfree(Ud); dfree(Uf);
       if (rc == 1) throw ApiError{CC_E_SUBSPACE, "step Hessian not positive definite"};
@@ -1292,6 +1294,7 @@ void cc_destroy(cc_ctx* ctx) {
   (void)hipStreamSynchronize(ctx->stream);
   for (Mesh* M : ctx->meshes)
     if (M) { free_mesh(*M); delete M; }
+  ctx->basis_ws.release();
   if (ctx->pinned) (void)hipHostFree(ctx->pinned);
   if (ctx->plan) cc::batch_plan_destroy(ctx->plan);
   ctx->harvest();

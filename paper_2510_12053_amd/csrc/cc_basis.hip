@@ -17,12 +17,12 @@
 // and X is column block q of Z = H^{-1}, from which the basis rows of level
 // q's vertices are formed directly.  The cost is O(N^2 n) for levels of n
 // DOFs instead of the O(N^3) of a dense inverse, the memory O(N n) besides
-// the basis itself.  S_l^{-1} comes from an in-place blocked Gauss-Jordan
+// the basis itself.  S_l^{-1} comes from a blocked Gauss-Jordan
 // inversion (SPD, so its diagonal pivot blocks need no pivoting):
 //
-//   for every 64-wide block K:  P = A_KK^{-1};  R = P A_K*;  C = A_*K;
-//                               A_IJ -= C_I R_J (I, J != K);  A_IK = -C_I P;
-//                               A_KJ = R_J;  A_KK = P.
+//   for every 64-wide block K:  P = A_KK^{-1};  R = P A_K*, P in column K;
+//                               C = A_*K;  A_IJ -= C_I R_J (I, J != K);
+//                               A_IK = -C_I P;  A_KJ = R_J;  A_KK = P.
 //
 // Dense matrices are row-major float64.
 
@@ -37,224 +37,294 @@
 namespace cc {
 
 constexpr int GJ_B = 64;   // pivot block width
-constexpr int GJ_T = 64;   // update tile (GJ_T x GJ_T outputs per workgroup)
+typedef double dbl4 __attribute__((ext_vector_type(4)));
 
-// P = A_KK^{-1} by Gauss-Jordan in LDS (one workgroup, b <= 64); writes P to
-// Pout (b x b) and a copy of the old column block C = A_*K to Cbuf (N x b).
-__global__ void __launch_bounds__(WG) k_gj_pivot(double* __restrict__ A, int N, int k0, int b,
-                                                 double* __restrict__ Pout, double* __restrict__ Cbuf,
-                                                 int* __restrict__ bad) {
-  __shared__ double M[GJ_B][GJ_B + 1];
-  __shared__ double piv;
-  for (int e = threadIdx.x; e < b * b; e += WG) M[e / b][e % b] = A[(size_t)(k0 + e / b) * N + k0 + e % b];
-  __syncthreads();
-  for (int p = 0; p < b; ++p) {
-    if (threadIdx.x == 0) {
-      piv = M[p][p];
-      if (!(piv > 0.0)) { atomicOr(bad, 1); piv = 1.0; }
+// v_mfma_f64_16x16x4: lane l holds A[l % 16][l / 16], B[l / 16][l % 16] and
+// C[4 i + l / 16][l % 16], i = 0..3.
+__device__ __forceinline__ dbl4 mfma64(double a, double b, dbl4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+// P = D^{-1} by Gauss-Jordan for a b x b block, b <= 64, held as a 4 x 4 piece
+// m per thread (rows 4 (tid / 16) .., columns 4 (tid % 16) ..; zero past b),
+// written to Pout (b x b).  A step passes the pivot's row and column through
+// LDS, twice buffered, so that it takes one barrier; a serial chain of b steps
+// (about 17 us for b = 64; the block in LDS with five barriers a step took
+// 174 us).  row, col: [2][GJ_B] each.
+__device__ __forceinline__ void gj_invert(double (&m)[4][4], int b, double (*row)[GJ_B], double (*col)[GJ_B],
+                                          double* __restrict__ Pout, int* __restrict__ bad) {
+  const int tr = threadIdx.x / 16, tc = threadIdx.x % 16;
+  for (int p4 = 0; 4 * p4 < b; ++p4) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int p = 4 * p4 + i;
+      if (p >= b) break;                             // uniform
+      double *rb = row[i & 1], *cb = col[i & 1];
+      if (tr == p4)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) rb[4 * tc + w] = m[i][w];
+      if (tc == p4)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) cb[4 * tr + u] = m[u][i];
+      __syncthreads();
+      double piv = rb[p];
+      if (!(piv > 0.0)) {
+        if (threadIdx.x == 0) atomicOr(bad, 1);
+        piv = 1.0;
+      }
+      // reciprocal by two Newton steps (to about 1 ulp): shorter than the division's chain
+      double ip = __builtin_amdgcn_rcp(piv);
+      ip = fma(ip, fma(-piv, ip, 1.0), ip);
+      ip = fma(ip, fma(-piv, ip, 1.0), ip);
+      double rv[4], cv[4];
+#pragma unroll
+      for (int w = 0; w < 4; ++w) rv[w] = rb[4 * tc + w] * ip;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) cv[u] = cb[4 * tr + u];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) m[u][w] -= cv[u] * rv[w];
+      if (tr == p4)                                  // the pivot's row and column
+#pragma unroll
+        for (int w = 0; w < 4; ++w) m[i][w] = rv[w];
+      if (tc == p4)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) m[u][i] = tr == p4 && u == i ? ip : -cv[u] * ip;
     }
-    __syncthreads();
-    const double ip = 1.0 / piv;
-    // scale row p, then eliminate column p from the other rows (in-place GJ)
-    if (threadIdx.x < b) M[p][threadIdx.x] = (threadIdx.x == p) ? ip : M[p][threadIdx.x] * ip;
-    __syncthreads();
-    for (int e = threadIdx.x; e < b * b; e += WG) {
-      const int r = e / b, c = e % b;
-      if (r == p) continue;
-      const double f = M[r][p];
-      if (c == p) continue;
-      M[r][c] -= f * M[p][c];
-    }
-    __syncthreads();
-    if (threadIdx.x < b && threadIdx.x != p) M[threadIdx.x][p] = -M[threadIdx.x][p] * ip;
-    __syncthreads();
-  }
-  for (int e = threadIdx.x; e < b * b; e += WG) Pout[e] = M[e / b][e % b];
-  (void)Cbuf;
-}
-
-// Copy of the old column block C = A_*K (N x b), before it is overwritten.
-__global__ void __launch_bounds__(WG) k_gj_copycol(const double* __restrict__ A, int N, int k0, int b,
-                                                   double* __restrict__ Cbuf) {
-  const size_t total = (size_t)N * b;
-  for (size_t e = (size_t)blockIdx.x * WG + threadIdx.x; e < total; e += (size_t)gridDim.x * WG) {
-    const size_t r = e / b;
-    const int c = (int)(e % b);
-    Cbuf[e] = A[r * N + k0 + c];
-  }
-}
-
-// Row block K: A_KJ <- P A_KJ for every column J outside the pivot block.
-__global__ void __launch_bounds__(WG) k_gj_rowscale(double* __restrict__ A, int N, int k0, int b,
-                                                    const double* __restrict__ P) {
-  __shared__ double Ps[GJ_B][GJ_B + 1];
-  __shared__ double Rs[GJ_B][GJ_B + 1];
-  for (int e = threadIdx.x; e < b * b; e += WG) Ps[e / b][e % b] = P[e];
-  const int c0 = blockIdx.x * GJ_B;   // column chunk
-  for (int e = threadIdx.x; e < b * GJ_B; e += WG) {
-    const int r = e / GJ_B, c = e % GJ_B;
-    Rs[r][c] = (c0 + c < N) ? A[(size_t)(k0 + r) * N + c0 + c] : 0.0;
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < b * GJ_B; e += WG) {
-    const int r = e / GJ_B, c = e % GJ_B;
-    const int col = c0 + c;
-    if (col >= N || (col >= k0 && col < k0 + b)) continue;
-    double s = 0.0;
-    for (int q = 0; q < b; ++q) s += Ps[r][q] * Rs[q][c];
-    A[(size_t)(k0 + r) * N + col] = s;
-  }
-}
-
-// Rank-b update of every tile outside the pivot row/column block:
-// A_IJ -= C_I R_J with C the saved old column block and R the scaled row block.
-__global__ void __launch_bounds__(WG) k_gj_update(double* __restrict__ A, int N, int k0, int b,
-                                                  const double* __restrict__ Cbuf) {
-  __shared__ double Cs[GJ_T][GJ_B + 1];
-  __shared__ double Rs[GJ_B][GJ_T + 1];
-  const int ti = blockIdx.y * GJ_T, tj = blockIdx.x * GJ_T;
-  for (int e = threadIdx.x; e < GJ_T * b; e += WG) {
-    const int r = e / b, q = e % b;
-    Cs[r][q] = (ti + r < N) ? Cbuf[(size_t)(ti + r) * b + q] : 0.0;
-  }
-  for (int e = threadIdx.x; e < b * GJ_T; e += WG) {
-    const int q = e / GJ_T, c = e % GJ_T;
-    Rs[q][c] = (tj + c < N) ? A[(size_t)(k0 + q) * N + tj + c] : 0.0;
-  }
-  __syncthreads();
-  // 256 threads, 4 x 4 outputs each
-  const int tr = (threadIdx.x / 16) * 4, tc = (threadIdx.x % 16) * 4;
-  double acc[4][4] = {};
-  for (int q = 0; q < b; ++q) {
-    double cr[4], rc[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) { cr[u] = Cs[tr + u][q]; rc[u] = Rs[q][tc + u]; }
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int w = 0; w < 4; ++w) acc[u][w] += cr[u] * rc[w];
   }
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int r = ti + tr + u;
-    if (r >= N || (r >= k0 && r < k0 + b)) continue;
+  for (int u = 0; u < 4; ++u)
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-      const int c = tj + tc + w;
-      if (c >= N || (c >= k0 && c < k0 + b)) continue;
-      A[(size_t)r * N + c] -= acc[u][w];
+      const int r = 4 * tr + u, c = 4 * tc + w;
+      if (r < b && c < b) Pout[r * b + c] = m[u][w];
     }
-  }
 }
 
-// Column block: A_IK = -C_I P for I outside the pivot block; A_KK = P.
-__global__ void __launch_bounds__(WG) k_gj_colfix(double* __restrict__ A, int N, int k0, int b,
-                                                  const double* __restrict__ P,
-                                                  const double* __restrict__ Cbuf) {
-  __shared__ double Ps[GJ_B][GJ_B + 1];
-  for (int e = threadIdx.x; e < b * b; e += WG) Ps[e / b][e % b] = P[e];
+// The first pivot block's inverse.
+__global__ void __launch_bounds__(WG) k_gj_first(const double* __restrict__ A, int N, int b,
+                                                 double* __restrict__ Pout, int* __restrict__ bad) {
+  __shared__ double row[2][GJ_B], col[2][GJ_B];
+  const int tr = threadIdx.x / 16, tc = threadIdx.x % 16;
+  double m[4][4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const int r = 4 * tr + u, c = 4 * tc + w;
+      m[u][w] = r < b && c < b ? A[(size_t)r * N + c] : 0.0;
+    }
+  gj_invert(m, b, row, col, Pout, bad);
+}
+
+// One pivot step out of place, 64 x 64 outputs per workgroup: with C = A_*K
+// and R = P A_K* (P itself in the pivot's columns),
+//   out_IJ = A_IJ - C_I R_J, without A_IJ in the pivot's columns; out_KJ = R_J.
+// Every workgroup forms its columns of R itself (half of its products), so the
+// whole step is one launch, every element is written once and nothing is read
+// that another workgroup writes.  Both products on the float64 matrix cores.
+// The workgroup of the next pivot block (launched first) goes on to invert it
+// (Pnext): that serial chain is the step's length, the other workgroups run
+// beside it.  A step at 780 unknowns: 34 us (17 of them the chain); as pivot,
+// row, update and column kernels with 4 x 4 outputs per thread it took 230 us.
+__global__ void __launch_bounds__(WG) k_gj_step(const double* __restrict__ A, double* __restrict__ out, int N,
+                                                int k0, int b, const double* __restrict__ P,
+                                                double* __restrict__ Pnext, int* __restrict__ bad) {
+  constexpr int T = GJ_B, LC = T + 1, LR = T + 2;    // row strides without bank conflicts
+  __shared__ double Cs[T][LC], Rs[T][LR];            // Rs: A_K*, then R
+  const int tiles = (N + T - 1) / T, next = k0 / T + 1;
+  // tile of this workgroup; the first one and the next pivot's change places
+  int t = blockIdx.x;
+  const int critical = next < tiles ? next * tiles + next : 0;
+  t = t == 0 ? critical : t == critical ? 0 : t;
+  const int i0 = t / tiles * T, j0 = t % tiles * T, tid = threadIdx.x, l = tid % 64, w = tid / 64;
+  double pf[T / 4];                                  // wave w's rows 16 w .. of P
+#pragma unroll
+  for (int q = 0; q < T / 4; ++q) {
+    const int r = 16 * w + l % 16, k = 4 * q + l / 16;
+    const double v = P[min(r, b - 1) * b + min(k, b - 1)];
+    pf[q] = r < b && k < b ? v : 0.0;
+  }
+#pragma unroll
+  for (int u = 0; u < T * T / WG; ++u) {
+    const int r = (tid + u * WG) / T, q = tid % T;
+    const double c = A[(size_t)min(i0 + r, N - 1) * N + min(k0 + q, N - 1)];
+    const double a = A[(size_t)min(k0 + r, N - 1) * N + min(j0 + q, N - 1)];
+    Cs[r][q] = i0 + r < N && q < b ? c : 0.0;
+    Rs[r][q] = r < b && j0 + q < N ? a : 0.0;
+  }
   __syncthreads();
-  const int r0 = blockIdx.x * (WG / GJ_B) * 1;
-  (void)r0;
-  const size_t total = (size_t)N * b;
-  for (size_t e = (size_t)blockIdx.x * WG + threadIdx.x; e < total; e += (size_t)gridDim.x * WG) {
-    const int r = (int)(e / b), c = (int)(e % b);
-    if (r >= k0 && r < k0 + b) {
-      A[(size_t)r * N + k0 + c] = Ps[r - k0][c];
-    } else {
-      double s = 0.0;
-      for (int q = 0; q < b; ++q) s += Cbuf[(size_t)r * b + q] * Ps[q][c];
-      A[(size_t)r * N + k0 + c] = -s;
+  dbl4 acc[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) acc[v] = dbl4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int q = 0; q < T / 4; ++q)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[v] = mfma64(pf[q], Rs[4 * q + l / 16][16 * v + l % 16], acc[v]);
+  __syncthreads();
+#pragma unroll
+  for (int v = 0; v < 4; ++v)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = 16 * w + 4 * i + l / 16, c = 16 * v + l % 16, kc = j0 + c - k0;
+      double x = acc[v][i];
+      if (kc >= 0 && kc < b && r < b) x = P[r * b + kc];
+      Rs[r][c] = x;
+      acc[v][i] = 0.0;
     }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < T / 4; ++q) {
+    const double a = Cs[16 * w + l % 16][4 * q + l / 16];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[v] = mfma64(a, Rs[4 * q + l / 16][16 * v + l % 16], acc[v]);
   }
-}
-
-// In-place inverse of the SPD matrix A (N x N); *bad set when a pivot is
-// not positive.  work: N * GJ_B + GJ_B^2 doubles.
-static void gj_inverse(double* A, int N, double* work, int* bad, hipStream_t s) {
-  double* P = work;
-  double* C = work + GJ_B * GJ_B;
-  const int tiles = (N + GJ_T - 1) / GJ_T;
-  for (int k0 = 0; k0 < N; k0 += GJ_B) {
-    const int b = (N - k0) < GJ_B ? (N - k0) : GJ_B;
-    const int cgrid = (int)std::min<size_t>(((size_t)N * b + WG - 1) / WG, 4096);
-    k_gj_pivot<<<1, WG, 0, s>>>(A, N, k0, b, P, C, bad);
-    k_gj_copycol<<<cgrid, WG, 0, s>>>(A, N, k0, b, C);
-    k_gj_rowscale<<<(N + GJ_B - 1) / GJ_B, WG, 0, s>>>(A, N, k0, b, P);
-    k_gj_update<<<dim3(tiles, tiles), WG, 0, s>>>(A, N, k0, b, C);
-    k_gj_colfix<<<cgrid, WG, 0, s>>>(A, N, k0, b, P, C);
-  }
+  const bool invert = next < tiles && i0 == next * T && j0 == next * T;   // uniform
+  __syncthreads();                                   // Cs is free
+#pragma unroll
+  for (int v = 0; v < 4; ++v)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = 16 * w + 4 * i + l / 16, c = 16 * v + l % 16, row = i0 + r, col = j0 + c;
+      double x = 0.0;
+      if (row < N && col < N) {
+        const size_t at = (size_t)row * N + col;
+        if (row >= k0 && row < k0 + b) x = Rs[row - k0][c];
+        else x = (col >= k0 && col < k0 + b ? 0.0 : A[at]) - acc[v][i];
+        out[at] = x;
+      }
+      if (invert) Cs[r][c] = x;
+    }
+  if (!invert) return;
+  __syncthreads();
+  double m[4][4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+#pragma unroll
+    for (int x = 0; x < 4; ++x) m[u][x] = Cs[4 * (tid / 16) + u][4 * (tid % 16) + x];
+  __syncthreads();
+  double(*rowb)[GJ_B] = reinterpret_cast<double(*)[GJ_B]>(&Rs[0][0]);
+  gj_invert(m, min(T, N - next * T), rowb, rowb + 2, Pnext, bad);
 }
 
 // C (M x N) = alpha op(A) op(B) + beta C, row-major float64, op = transpose
-// when TA / TB.  64 x 64 output tiles, 4 x 4 per thread, K in steps of 16
-// through LDS.  With beta = 0, C is not read.
-constexpr int MM_T = 64, MM_K = 16;
-template <bool TA, bool TB>
+// when TA / TB, on the float64 matrix cores.  A workgroup of four waves forms
+// TM x TM outputs, each wave (TM / 2)^2 of them as 16 x 16 tiles; K runs
+// through LDS in steps of 16, twice buffered, the next step's loads in flight
+// during the products.  With beta = 0, C is not read.  Bound by the matrix
+// cores' issue where the tiles fill the chip: 64-wide tiles read less, 32-wide
+// ones give four times the workgroups, so they serve outputs of fewer than 256
+// of the wide tiles (780 x 780 x 780: 169 wide tiles on 256 CUs).  At that size
+// 35 us (27 TFLOP/s); 4 x 4 outputs per thread, an LDS double read for every two
+// FMAs, took 157.
+constexpr int MM_K = 16;
+template <bool TA, bool TB, int TM>
 __global__ void __launch_bounds__(WG) k_dgemm(int M, int N, int K, double alpha,
                                               const double* __restrict__ A, int lda,
                                               const double* __restrict__ B, int ldb, double beta,
                                               double* __restrict__ C, int ldc) {
-  __shared__ double As[MM_K][MM_T + 2];
-  __shared__ double Bs[MM_K][MM_T + 2];
-  const int m0 = blockIdx.y * MM_T, n0 = blockIdx.x * MM_T, tid = threadIdx.x;
-  const int tr = (tid / 16) * 4, tc = (tid % 16) * 4;
-  double acc[4][4];
+  constexpr int NT = TM / 32, LD = TM + 2, PER = TM * MM_K / WG;   // 16-wide tiles per wave and side; loads
+  __shared__ double As[2][MM_K][LD], Bs[2][MM_K][LD];
+  const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TM, tid = threadIdx.x;
+  const int l = tid % 64, w = tid / 64, wm = w / 2 * (TM / 2), wn = w % 2 * (TM / 2);
+  double va[PER], vb[PER];
+  auto load = [&](int kk) {
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int w = 0; w < 4; ++w) acc[u][w] = 0.0;
-  for (int k0 = 0; k0 < K; k0 += MM_K) {
-#pragma unroll
-    for (int u = 0; u < MM_T * MM_K / WG; ++u) {
+    for (int u = 0; u < PER; ++u) {
       const int e = tid + u * WG;
       // consecutive threads walk the contiguous index of each operand
-      const int ma = TA ? e % MM_T : e / MM_K, ka = TA ? e / MM_T : e % MM_K;
-      const int gm = m0 + ma, gka = k0 + ka;
-      double va = 0.0;
-      if (gm < M && gka < K) va = TA ? A[(size_t)gka * lda + gm] : A[(size_t)gm * lda + gka];
-      As[ka][ma] = va;
-      const int nb = TB ? e / MM_K : e % MM_T, kb = TB ? e % MM_K : e / MM_T;
-      const int gn = n0 + nb, gkb = k0 + kb;
-      double vb = 0.0;
-      if (gn < N && gkb < K) vb = TB ? B[(size_t)gn * ldb + gkb] : B[(size_t)gkb * ldb + gn];
-      Bs[kb][nb] = vb;
+      const int ma = TA ? e % TM : e / MM_K, ka = TA ? e / TM : e % MM_K;
+      const int gm = m0 + ma, gka = kk + ka;
+      va[u] = gm < M && gka < K ? (TA ? A[(size_t)gka * lda + gm] : A[(size_t)gm * lda + gka]) : 0.0;
+      const int nb = TB ? e / MM_K : e % TM, kb = TB ? e % MM_K : e / TM;
+      const int gn = n0 + nb, gkb = kk + kb;
+      vb[u] = gn < N && gkb < K ? (TB ? B[(size_t)gn * ldb + gkb] : B[(size_t)gkb * ldb + gn]) : 0.0;
     }
-    __syncthreads();
+  };
+  auto store = [&](int buf) {
 #pragma unroll
-    for (int kk = 0; kk < MM_K; ++kk) {
-      double a[4], b[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) { a[u] = As[kk][tr + u]; b[u] = Bs[kk][tc + u]; }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int w = 0; w < 4; ++w) acc[u][w] += a[u] * b[w];
+    for (int u = 0; u < PER; ++u) {
+      const int e = tid + u * WG;
+      As[buf][TA ? e / TM : e % MM_K][TA ? e % TM : e / MM_K] = va[u];
+      Bs[buf][TB ? e % MM_K : e / TM][TB ? e / MM_K : e % TM] = vb[u];
     }
+  };
+  dbl4 acc[NT][NT];
+#pragma unroll
+  for (int u = 0; u < NT; ++u)
+#pragma unroll
+    for (int v = 0; v < NT; ++v) acc[u][v] = dbl4{0.0, 0.0, 0.0, 0.0};
+  load(0);
+  store(0);
+  __syncthreads();
+  for (int kk = 0, buf = 0; kk < K; kk += MM_K, buf ^= 1) {
+    const bool more = kk + MM_K < K;
+    if (more) load(kk + MM_K);
+#pragma unroll
+    for (int k4 = 0; k4 < MM_K; k4 += 4) {
+      double a[NT], b[NT];
+#pragma unroll
+      for (int u = 0; u < NT; ++u) {
+        a[u] = As[buf][k4 + l / 16][wm + 16 * u + l % 16];
+        b[u] = Bs[buf][k4 + l / 16][wn + 16 * u + l % 16];
+      }
+#pragma unroll
+      for (int u = 0; u < NT; ++u)
+#pragma unroll
+        for (int v = 0; v < NT; ++v) acc[u][v] = mfma64(a[u], b[v], acc[u][v]);
+    }
+    if (more) store(buf ^ 1);                        // read last before the previous barrier
     __syncthreads();
   }
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int r = m0 + tr + u;
-    if (r >= M) continue;
+  for (int u = 0; u < NT; ++u)
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const int c = n0 + tc + w;
-      if (c >= N) continue;
-      double* o = C + (size_t)r * ldc + c;
-      *o = beta == 0.0 ? alpha * acc[u][w] : alpha * acc[u][w] + beta * *o;
+    for (int i = 0; i < 4; ++i) {
+      const int r = m0 + wm + 16 * u + 4 * i + l / 16;
+      if (r >= M) continue;
+#pragma unroll
+      for (int v = 0; v < NT; ++v) {
+        const int c = n0 + wn + 16 * v + l % 16;
+        if (c >= N) continue;
+        double* o = C + (size_t)r * ldc + c;
+        const double x = acc[u][v][i];
+        *o = beta == 0.0 ? alpha * x : alpha * x + beta * *o;
+      }
     }
-  }
+}
+
+template <bool TA, bool TB>
+static void launch_dgemm(int M, int N, int K, double alpha, const double* A, int lda, const double* B, int ldb,
+                         double beta, double* C, int ldc, hipStream_t s) {
+  auto tiles = [&](int t) { return dim3((N + t - 1) / t, (M + t - 1) / t); };
+  const dim3 wide = tiles(64);
+  if (wide.x * wide.y >= 256)
+    k_dgemm<TA, TB, 64><<<wide, WG, 0, s>>>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
+  else
+    k_dgemm<TA, TB, 32><<<tiles(32), WG, 0, s>>>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
 }
 
 static void dgemm(bool ta, bool tb, int M, int N, int K, double alpha, const double* A, int lda,
                   const double* B, int ldb, double beta, double* C, int ldc, hipStream_t s) {
   if (M <= 0 || N <= 0) return;
-  const dim3 grid((N + MM_T - 1) / MM_T, (M + MM_T - 1) / MM_T);
-  if (!ta && !tb) k_dgemm<false, false><<<grid, WG, 0, s>>>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
-  else if (!ta && tb) k_dgemm<false, true><<<grid, WG, 0, s>>>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
-  else if (ta && !tb) k_dgemm<true, false><<<grid, WG, 0, s>>>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
-  else k_dgemm<true, true><<<grid, WG, 0, s>>>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
+  if (!ta && !tb) launch_dgemm<false, false>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, s);
+  else if (!ta && tb) launch_dgemm<false, true>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, s);
+  else launch_dgemm<true, false>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, s);
+}
+
+// In-place inverse of the SPD matrix A (N x N); *bad set when a pivot is not
+// positive.  tmp: N * N doubles, P: 2 GJ_B^2.  One launch a pivot block.
+static void gj_inverse(double* A, int N, double* tmp, double* P, int* bad, hipStream_t s) {
+  const int tiles = (N + GJ_B - 1) / GJ_B;
+  double *from = A, *to = tmp, *Pk = P, *Pn = P + GJ_B * GJ_B;
+  k_gj_first<<<1, WG, 0, s>>>(A, N, std::min(N, GJ_B), Pk, bad);
+  for (int k0 = 0; k0 < N; k0 += GJ_B) {
+    k_gj_step<<<tiles * tiles, WG, 0, s>>>(from, to, N, k0, std::min(N - k0, GJ_B), Pk, Pn, bad);
+    std::swap(from, to);
+    std::swap(Pk, Pn);
+  }
+  if (from != A) (void)hipMemcpyAsync(A, from, (size_t)N * N * sizeof(double), hipMemcpyDeviceToDevice, s);
 }
 
 // dst (rows x cols, leading dimension ldd) = alpha src (leading dimension lds)
@@ -361,8 +431,28 @@ __global__ void k_basis_from_panel(const double* __restrict__ X, int nq, int q0,
     }
 }
 
+bool DeviceScratch::reserve(size_t bytes) {
+  if (bytes <= n) return true;
+  release();
+  if (hipMalloc(&p, bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    p = nullptr;
+    return false;
+  }
+  n = bytes;
+  return true;
+}
+void DeviceScratch::trim() {
+  if (n > KEEP) release();
+}
+void DeviceScratch::release() {
+  if (p) (void)hipFree(p);
+  p = nullptr;
+  n = 0;
+}
+
 int exact_basis_band(const MeshView& mv, const double* hb, const int* loff_h, int L, double* Ud, float* Uf,
-                     hipStream_t s) {
+                     DeviceScratch& scratch, hipStream_t s) {
   const int D = mv.D, nf = mv.nf, N = nf * D;
   if (nf < 1) return 0;
   std::vector<int> n(L), lev(nf);
@@ -375,30 +465,24 @@ int exact_basis_band(const MeshView& mv, const double* hb, const int* loff_h, in
     oD[l + 1] = oD[l] + (size_t)n[l] * n[l];
     oB[l + 1] = oB[l] + (l > 0 ? (size_t)n[l] * n[l - 1] : 0);
   }
-  double *Dbuf = nullptr, *Bbuf = nullptr, *tmp = nullptr, *P = nullptr, *Q = nullptr, *work = nullptr;
-  size_t *oD_d = nullptr, *oB_d = nullptr;
-  int *lev_d = nullptr, *loff_d = nullptr, *bad = nullptr;
-  auto release = [&]() {
-    for (void* q : {(void*)Dbuf, (void*)Bbuf, (void*)tmp, (void*)P, (void*)Q, (void*)work, (void*)oD_d,
-                    (void*)oB_d, (void*)lev_d, (void*)loff_d, (void*)bad})
-      if (q) (void)hipFree(q);
+  // one workspace for everything, carved in 256-byte steps
+  size_t need = 0;
+  auto room = [&](size_t bytes) {
+    const size_t at = need;
+    need += (bytes + 255) / 256 * 256;
+    return at;
   };
-  bool ok = hipMalloc(&Dbuf, std::max<size_t>(oD[L], 1) * 8) == hipSuccess &&
-            hipMalloc(&Bbuf, std::max<size_t>(oB[L], 1) * 8) == hipSuccess &&
-            hipMalloc(&tmp, (size_t)nmax * nmax * 8) == hipSuccess &&
-            hipMalloc(&P, (size_t)N * nmax * 8) == hipSuccess &&
-            hipMalloc(&Q, (size_t)N * nmax * 8) == hipSuccess &&
-            hipMalloc(&work, ((size_t)nmax * GJ_B + GJ_B * GJ_B) * 8) == hipSuccess &&
-            hipMalloc(&oD_d, (L + 1) * sizeof(size_t)) == hipSuccess &&
-            hipMalloc(&oB_d, (L + 1) * sizeof(size_t)) == hipSuccess &&
-            hipMalloc(&lev_d, nf * sizeof(int)) == hipSuccess &&
-            hipMalloc(&loff_d, (L + 1) * sizeof(int)) == hipSuccess &&
-            hipMalloc(&bad, sizeof(int)) == hipSuccess;
-  if (!ok) {
-    (void)hipGetLastError();
-    release();
-    return 2;
-  }
+  const size_t aD = room(oD[L] * 8), aB = room(oB[L] * 8), aT = room((size_t)nmax * nmax * 8),
+               aP = room((size_t)N * nmax * 8), aQ = room((size_t)N * nmax * 8), aV = room(2 * GJ_B * GJ_B * 8),
+               aoD = room((L + 1) * sizeof(size_t)), aoB = room((L + 1) * sizeof(size_t)),
+               alev = room(nf * sizeof(int)), alo = room((L + 1) * sizeof(int)), abad = room(sizeof(int));
+  if (!scratch.reserve(need)) return 2;
+  char* base = static_cast<char*>(scratch.p);
+  double *Dbuf = (double*)(base + aD), *Bbuf = (double*)(base + aB), *tmp = (double*)(base + aT),
+         *P = (double*)(base + aP), *Q = (double*)(base + aQ), *pivot = (double*)(base + aV);
+  size_t *oD_d = (size_t*)(base + aoD), *oB_d = (size_t*)(base + aoB);
+  int *lev_d = (int*)(base + alev), *loff_d = (int*)(base + alo), *bad = (int*)(base + abad);
+  auto release = [&]() { scratch.trim(); };
   (void)hipMemcpyAsync(oD_d, oD.data(), (L + 1) * sizeof(size_t), hipMemcpyHostToDevice, s);
   (void)hipMemcpyAsync(oB_d, oB.data(), (L + 1) * sizeof(size_t), hipMemcpyHostToDevice, s);
   (void)hipMemcpyAsync(lev_d, lev.data(), nf * sizeof(int), hipMemcpyHostToDevice, s);
@@ -421,7 +505,7 @@ int exact_basis_band(const MeshView& mv, const double* hb, const int* loff_h, in
       dgemm(false, true, n[l], n[l], n[l - 1], -1.0, tmp, n[l - 1], Bl, n[l - 1], 1.0, Dl, n[l], s);
       scale_copy(Bl, n[l - 1], tmp, n[l - 1], n[l], n[l - 1], 1.0, s);
     }
-    gj_inverse(Dl, n[l], work, bad, s);
+    gj_inverse(Dl, n[l], tmp, pivot, bad, s);
   }
   int hbad = 0;
   (void)hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, s);

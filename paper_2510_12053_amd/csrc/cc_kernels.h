@@ -251,8 +251,19 @@ bool tile_usable(const MeshView& mv, int prec, int tv_cap, int chunk);
 // such that every block (j, k) of H couples the same or adjacent levels.
 // Ud (may be null) / Uf receive the dense band layout.  Returns 0, 1 when a
 // pivot block is not positive definite, 2 when device memory runs out.
+// The workspace is the context's: kept between builds up to KEEP bytes (a
+// restarted solve rebuilds its basis every few steps, and the allocations and
+// frees cost a 720-vertex build a third of its time), larger ones given back.
+struct DeviceScratch {
+  static constexpr size_t KEEP = size_t(256) << 20;
+  void* p = nullptr;
+  size_t n = 0;
+  bool reserve(size_t bytes);   // contents undefined; false: out of memory
+  void trim();                  // frees it when larger than KEEP
+  void release();
+};
 int exact_basis_band(const MeshView& mv, const double* hb, const int* loff_h, int L, double* Ud,
-                     float* Uf, hipStream_t s);
+                     float* Uf, DeviceScratch& scratch, hipStream_t s);
 
 // ---- batched stepping (many meshes per launch) -----------------------------
 constexpr int MAX_COLOURS = 32;
