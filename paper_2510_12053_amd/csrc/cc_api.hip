@@ -62,12 +62,12 @@ struct Mesh {
   int smap_words = 0, smap_supp = 0;
   // work buffers
   double *x = nullptr, *xt = nullptr, *x0 = nullptr, *xtrial = nullptr, *dvec = nullptr,
-         *g = nullptr, *partials = nullptr, *scal = nullptr;
+         *g = nullptr, *partials = nullptr;
   double* rot = nullptr;  // corotation: rotation of every free vertex (D*D each)
   double* corr = nullptr; // last step's correction x - x~ (MeshView::corr)
   void *estore = nullptr, *hb = nullptr, *KL = nullptr;
-  unsigned long long* fb = nullptr;
-  int* bad = nullptr;
+  unsigned long long* fb = nullptr;   // STEP_COUNTERS words
+  int* bad = nullptr;                 // = fb + 4
   // last-step info
   double last_E = 0, last_paper = 0;
   long long last_fb[3] = {0, 0, 0}, last_halvings = 0, last_sweep_fb = 0;
@@ -166,8 +166,8 @@ void free_mesh(Mesh& M) {
   dfree(M.d_cel_ptr); dfree(M.d_cel); dfree(M.d_csl_ptr); dfree(M.d_csl); dfree(M.dinv_d); dfree(M.vol_d); dfree(M.mass); dfree(M.dinv_f); dfree(M.vol_f);
   free_basis(M);
   dfree(M.x); dfree(M.xt); dfree(M.x0); dfree(M.xtrial); dfree(M.dvec); dfree(M.g);
-  dfree(M.partials); dfree(M.scal); dfree(M.estore); dfree(M.hb); dfree(M.KL); dfree(M.fb);
-  dfree(M.bad); dfree(M.rot); dfree(M.corr);
+  dfree(M.partials); dfree(M.estore); dfree(M.hb); dfree(M.KL); dfree(M.fb);
+  dfree(M.rot); dfree(M.corr);
   dfree(M.nptr); dfree(M.nidx); dfree(M.frank); dfree(M.Xr); dfree(M.feat); dfree(M.delta);
 }
 
@@ -205,6 +205,10 @@ float* scratch_of(int device) {
   return device < (int)g_scratch.size() ? g_scratch[device] : nullptr;
 }
 }  // namespace
+
+// A mesh's device counters of a step: fallbacks of three kinds, a spare word,
+// and the flag of non-finite input.
+constexpr int STEP_COUNTERS = 5;
 
 struct cc_ctx {
   int device = 0;
@@ -795,7 +799,6 @@ void build_mesh(cc_ctx* ctx, Mesh& M) {
   HIPC(hipMemsetAsync(M.dvec, 0, nd * sizeof(double), s));
   const int cap = cc::reduce_partials_capacity(M.view());
   M.partials = dalloc<double>(cap);
-  M.scal = dalloc<double>(8);
   const int NB = K * (K + 1) / 2;
   M.estore = dalloc<double>((size_t)NB * m * D * D);
   M.hb = dalloc<double>((size_t)M.nnzb * D * D);
@@ -803,8 +806,9 @@ void build_mesh(cc_ctx* ctx, Mesh& M) {
   M.rot = dalloc<double>((size_t)std::max(nf, 1) * D * D);
   M.corr = dalloc<double>((size_t)D * n);
   HIPC(hipMemsetAsync(M.corr, 0, (size_t)D * n * sizeof(double), s));
-  M.fb = dalloc<unsigned long long>(4);
-  M.bad = dalloc<int>(1);
+  M.fb = dalloc<unsigned long long>(STEP_COUNTERS);
+  M.bad = reinterpret_cast<int*>(M.fb + 4);
+  HIPC(hipMemsetAsync(M.fb, 0, STEP_COUNTERS * sizeof(unsigned long long), s));
   HIPC(hipStreamSynchronize(s));
 }
 
@@ -1131,28 +1135,49 @@ struct Stepper {
   const cc_params& p;
   hipStream_t s;
 
-  double read_scalar(const double* dptr) {
-    HIPC(hipMemcpyAsync(ctx->pinned, dptr, sizeof(double), hipMemcpyDeviceToHost, s));
+  bool g_ok = false;   // M.g holds the gradient at M.x (a swap of M.x must keep this true)
+
+  double* out() const { return ctx->pinned; }
+  // Launches the step energy (with_e) and the gradient (with_g, into M.g) at x;
+  // after a wait, out()[0] = E, out()[1] = |g|^2 and the step's counters.  Both
+  // run in one launch unless one of them is being timed by itself.
+  void eval(const double* x, bool with_e, bool with_g) {
+    int ne = 0, ng = 0;
+    if (with_g) g_ok = x == M.x;
+    if (with_e && with_g && !(ctx->prof_mask & (1 << CC_K_ENERGY | 1 << CC_K_GRADIENT))) {
+      cc::launch_energy_grad(mv, x, M.xt, mat, M.g, M.partials, &ne, &ng, s);
+    } else {
+      if (with_e) ctx->timed(CC_K_ENERGY, [&] { cc::launch_energy(mv, x, M.xt, mat, M.partials, &ne, s); });
+      if (with_g)
+        ctx->timed(CC_K_GRADIENT, [&] { cc::launch_gradient(mv, x, M.xt, mat, M.g, M.partials + ne, &ng, s); });
+    }
+    cc::launch_reduce_eg(M.partials, ne, ng, with_e ? 0 : 1, with_e + with_g, M.fb, STEP_COUNTERS, out(), s);
+  }
+  void wait() {
     HIPC(hipStreamSynchronize(s));
     ctx->harvest();
-    return ctx->pinned[0];
+  }
+  // counter i of the last eval that has been waited for
+  unsigned long long counter(int i) const {
+    unsigned long long v;
+    std::memcpy(&v, out() + 2 + i, sizeof(v));
+    return v;
   }
   double energy(const double* x) {
-    int np = 0;
-    ctx->timed(CC_K_ENERGY, [&] { cc::launch_energy(mv, x, M.xt, mat, M.partials, &np, s); });
-    cc::launch_reduce(M.partials, np, M.scal, s);
-    return read_scalar(M.scal);
+    eval(x, true, false);
+    wait();
+    return out()[0];
   }
   double grad_norm2(const double* x) {
-    int np = 0;
-    ctx->timed(CC_K_GRADIENT, [&] { cc::launch_gradient(mv, x, M.xt, mat, M.g, M.partials, &np, s); });
-    if (np == 0) return 0.0;
-    cc::launch_reduce(M.partials, np, M.scal + 1, s);
-    return read_scalar(M.scal + 1);
+    eval(x, false, true);
+    wait();
+    return out()[1];
   }
   void gradient_only(const double* x) {
+    if (g_ok && x == M.x) return;
     int np = 0;
     ctx->timed(CC_K_GRADIENT, [&] { cc::launch_gradient(mv, x, M.xt, mat, M.g, M.partials, &np, s); });
+    g_ok = x == M.x;
   }
   // Element Hessians and block rows at x: of every element (colour < 0), or
   // only of those that the moves of colour `colour`'s vertices changed.
@@ -1183,18 +1208,9 @@ struct Stepper {
                          ctx->dense_rows, ctx->dense_chunk);
     });
   }
-  // Condensation that also writes the Jacobi directions into out when the
-  // dense path can (g must hold the gradient at the same x); false: call update.
-  bool prep_direction(int method, double* out) {
-    bool done = false;
-    ctx->timed(CC_K_CC_PREP, [&] {
-      done = cc::launch_cc_prep(mv, p.precision, method, 0, M.nf, M.hb, M.KL, M.fb, s, M.g, out, nullptr,
-                                ctx->dense_rows, ctx->dense_chunk);
-    });
-    return done;
-  }
-  void update(int method, int v0, int v1, double* out, int acc) {
-    ctx->timed(CC_K_CC_UPDATE, [&] { cc::launch_cc_update(mv, p.precision, method, v0, v1, M.KL, M.g, out, acc, s); });
+  void update(int method, int v0, int v1, double* out, int acc, const double* from = nullptr) {
+    ctx->timed(CC_K_CC_UPDATE,
+               [&] { cc::launch_cc_update(mv, p.precision, method, v0, v1, M.KL, M.g, out, acc, s, from); });
   }
   // One sweep from x into out (x unchanged).  method as requested.
   // sweep_kind: CC_SWEEP_* to override p.sweep (the line search's Jacobi
@@ -1204,12 +1220,19 @@ struct Stepper {
     if ((sweep_kind < 0 ? p.sweep : sweep_kind) == CC_SWEEP_JACOBI) {
       gradient_only(x);              // before the assembly, which may store it with its records
       hessian(x);
-      if (!prep_direction(method, M.dvec)) update(method, 0, M.nf, M.dvec, 0);
-      cc::launch_axpy(nd, x, M.dvec, 1.0, out, s);
+      // the finish or update kernel writes the free entries x + d itself; the
+      // Dirichlet ones are the same in both buffers
+      bool done = false;
+      ctx->timed(CC_K_CC_PREP, [&] {
+        done = cc::launch_cc_prep(mv, p.precision, method, 0, M.nf, M.hb, M.KL, M.fb, s, M.g, M.dvec, out,
+                                  ctx->dense_rows, ctx->dense_chunk, x);
+      });
+      if (!done) update(method, 0, M.nf, out, 1, x);
       return;
     }
     HIPC(hipMemcpyAsync(out, x, (size_t)nd * sizeof(double), hipMemcpyDeviceToDevice, s));
     int moved = -1;   // the last colour that moved in this sweep
+    const double* at = x;   // where the running state's gradient is taken: x until a colour has moved
     for (int c = 0; c < M.ncol; ++c) {
       const int v0 = M.coff[c], v1 = M.coff[c + 1];
       if (v1 <= v0) continue;
@@ -1217,9 +1240,10 @@ struct Stepper {
         // every Hessian at the sweep's start, then only what the previous
         // colour's moves changed; the gradient first, which the assembly may
         // store with its records
-        gradient_only(out);
+        gradient_only(at);
         hessian(out, moved);
         moved = c;
+        at = out;
         // a dense basis forms b_i from this gradient and moves the colour's
         // vertices in the finish kernel; other bases take the update kernel
         bool done = false;
@@ -1234,7 +1258,8 @@ struct Stepper {
         hessian(out);
         prep(method, 0, M.nf);
       }
-      gradient_only(out);
+      gradient_only(at);
+      at = out;
       update(method, v0, v1, out, 1);
     }
   }
@@ -1582,20 +1607,22 @@ cc_status cc_step(cc_ctx* ctx, int32_t mesh_id, double* x, double* v, const doub
     const double h = p.quasistatic ? 1.0 : dt;
     Stepper S{ctx, M, M.view(), mat, p, s};
     S.mv.tile = cc::tile_usable(S.mv, p.precision, ctx->dense_rows, ctx->dense_chunk);
-    HIPC(hipMemsetAsync(M.bad, 0, sizeof(int), s));
-    HIPC(hipMemsetAsync(M.fb, 0, 4 * sizeof(unsigned long long), s));
-    cc::launch_predict(S.mv, M.d_vperm, x, v, x_bc, h, p.quasistatic, M.x, M.xt, M.x0, M.bad, s);
-    int bad = 0;
-    HIPC(hipMemcpyAsync(&bad, M.bad, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIPC(hipStreamSynchronize(s));
-    if (bad) return fail(ctx, CC_E_NONFINITE, "non-finite x, v or x_bc");
+    HIPC(hipMemsetAsync(M.fb, 0, STEP_COUNTERS * sizeof(unsigned long long), s));
+    cc::launch_predict(S.mv, M.d_vperm, x, v, x_bc, h, p.quasistatic, M.x, M.xt, M.x0, M.xtrial, M.bad, s);
+    // one launch, one reduction and one wait per point evaluated: the energy
+    // where the line search or the warm start compares it, the gradient
+    // always, and the flag and counters with them
+    const bool with_e = p.line_search || p.warm_start;
+    S.eval(M.x, with_e, true);
+    S.wait();
+    if ((int)S.counter(4)) return fail(ctx, CC_E_NONFINITE, "non-finite x, v or x_bc");
     // the convergence test is relative to the larger of the predictor's
     // gradient and the floor (the gravity load's part of it, s_el |m_i g| over
     // free DOFs, or 1e-8 of the elastic force scale)
-    const double gstart = std::sqrt(S.grad_norm2(M.x));
+    const double gstart = std::sqrt(S.out()[1]);
     const double g0 = std::max(gstart, load_norm(M, mat));
     const int nd = M.D * M.n;
-    double r = 0.0, Ecur = 0.0;
+    double r = 0.0, Ecur = with_e ? S.out()[0] : 0.0;
     int k = 0;
     long long halvings = 0, sweep_fb = 0;
     cc_status result = CC_OK;
@@ -1615,34 +1642,41 @@ cc_status cc_step(cc_ctx* ctx, int32_t mesh_id, double* x, double* v, const doub
         cc::mlp_forward(ctx->mlp, M.feat, M.nf, M.delta, s);
         // x~ + c + l Delta, then x~ + c alone (c: the last step's
         // correction), each kept only below the start's energy so far
-        double Ebest = S.energy(M.x);
         for (int cand = 1; cand <= 2; ++cand) {
           cc::launch_proposal(M.n, M.nf, M.xt, M.corr, M.delta, M.ell, cand == 1 ? 1.0 : 0.0, M.xtrial, s);
           const double Ep = S.energy(M.xtrial);
-          if (Ep < Ebest) {
+          if (Ep < Ecur) {
             std::swap(M.x, M.xtrial);
-            Ebest = Ep;
+            S.g_ok = false;
+            Ecur = Ep;
             warm = cand;
           }
         }
         if (warm) r = std::sqrt(S.grad_norm2(M.x)) / g0;
-        else (void)S.grad_norm2(M.x);  // g at the predictor for the first iteration
       }
-      if (p.line_search) Ecur = S.energy(M.x);
       while (r > tol && k < p.max_iters) {
         S.sweep(M.x, M.xtrial, p.method);
+        const double Eold = Ecur;
+        S.eval(M.xtrial, p.line_search, true);
+        S.wait();
         if (p.line_search) {
           const double tau = 1e-12 * std::max(std::fabs(Ecur), 1.0);
-          // displacement of this iteration
-          cc::launch_axpy(nd, M.xtrial, M.x, -1.0, M.dvec, s);
-          double alpha = 1.0, Et = S.energy(M.xtrial);
+          double Et = S.out()[0];
           int hv = 0;
-          while (!(Et <= Ecur + tau) && hv < lim0) {
-            alpha *= 0.5;
-            ++hv;
-            cc::launch_axpy(nd, M.x, M.dvec, alpha, M.xtrial, s);
-            Et = S.energy(M.xtrial);
-          }
+          // halvings of this sweep's displacement, formed at the first
+          auto backtrack = [&](int limit) {
+            double alpha = 1.0;
+            for (hv = 0; !(Et <= Ecur + tau) && hv < limit;) {
+              if (hv == 0) cc::launch_axpy(nd, M.xtrial, M.x, -1.0, M.dvec, s);
+              alpha *= 0.5;
+              ++hv;
+              cc::launch_axpy(nd, M.x, M.dvec, alpha, M.xtrial, s);
+              S.eval(M.xtrial, true, true);
+              S.wait();
+              Et = S.out()[0];
+            }
+          };
+          backtrack(lim0);
           if (!(Et <= Ecur + tau)) {
             // fallbacks: a Jacobi sweep of the same method (coloured sweeps
             // of CC or JGS2), then coordinate descent, each with the search
@@ -1650,16 +1684,10 @@ cc_status cc_step(cc_ctx* ctx, int32_t mesh_id, double* x, double* v, const doub
             for (int f = 0; f < nfb && !(Et <= Ecur + tau); ++f) {
               const bool jac = nfb == 2 && f == 0;
               S.sweep(M.x, M.xtrial, jac ? p.method : CC_METHOD_CD, jac ? CC_SWEEP_JACOBI : -1);
-              cc::launch_axpy(nd, M.xtrial, M.x, -1.0, M.dvec, s);
-              alpha = 1.0;
-              Et = S.energy(M.xtrial);
-              hv = 0;
-              while (!(Et <= Ecur + tau) && hv < p.max_halvings) {
-                alpha *= 0.5;
-                ++hv;
-                cc::launch_axpy(nd, M.x, M.dvec, alpha, M.xtrial, s);
-                Et = S.energy(M.xtrial);
-              }
+              S.eval(M.xtrial, true, true);
+              S.wait();
+              Et = S.out()[0];
+              backtrack(p.max_halvings);
             }
             if (!(Et <= Ecur + tau)) {
               result = CC_STALLED;
@@ -1671,18 +1699,25 @@ cc_status cc_step(cc_ctx* ctx, int32_t mesh_id, double* x, double* v, const doub
           Ecur = Et;
         }
         std::swap(M.x, M.xtrial);
+        S.g_ok = true;                 // taken at the accepted point
         ++k;
-        const double gn = std::sqrt(S.grad_norm2(M.x));
+        const double gn = std::sqrt(S.out()[1]);
         r = gn / g0;
         if (!std::isfinite(r)) {
           std::swap(M.x, M.xtrial);
+          S.g_ok = false;
+          Ecur = Eold;
           result = CC_STALLED;
           break;
         }
       }
       if (result == CC_OK && r > tol) result = CC_NOT_CONVERGED;
     }
-    M.last_E = S.energy(M.x);
+    // the energy at the end point is known where the line search compared it
+    if (!p.line_search) S.eval(M.x, true, false);
+    cc::launch_finalize(S.mv, M.d_vperm, M.x, M.xt, M.x0, h, p.quasistatic, x, v, s);
+    S.wait();
+    M.last_E = p.line_search ? Ecur : S.out()[0];
     M.last_halvings = halvings;
     M.last_sweep_fb = sweep_fb;
     {
@@ -1690,12 +1725,7 @@ cc_status cc_step(cc_ctx* ctx, int32_t mesh_id, double* x, double* v, const doub
       const double pm = gn / (M.volume * M.n * M.E);
       M.last_paper = p.quasistatic ? pm : pm / dt;
     }
-    unsigned long long fbh[4];
-    HIPC(hipMemcpyAsync(fbh, M.fb, sizeof(fbh), hipMemcpyDeviceToHost, s));
-    cc::launch_finalize(S.mv, M.d_vperm, M.x, M.xt, M.x0, h, p.quasistatic, x, v, s);
-    HIPC(hipStreamSynchronize(s));
-    ctx->harvest();
-    for (int c = 0; c < 3; ++c) M.last_fb[c] = (long long)fbh[c];
+    for (int c = 0; c < 3; ++c) M.last_fb[c] = (long long)S.counter(c);
     M.last_warm = warm;
     if (iters) *iters = k;
     if (rel_grad) *rel_grad = r;
@@ -2289,7 +2319,7 @@ cc_status cc_mlp_features(cc_ctx* ctx, int32_t mesh_id, const double* x, const d
     hipStream_t s = ctx->stream;
     MeshView mv = M.view();
     HIPC(hipMemsetAsync(M.bad, 0, sizeof(int), s));
-    cc::launch_predict(mv, M.d_vperm, x, v, x_bc, dt, 0, M.x, M.xt, M.x0, M.bad, s);
+    cc::launch_predict(mv, M.d_vperm, x, v, x_bc, dt, 0, M.x, M.xt, M.x0, M.xtrial, M.bad, s);
     cc::Material mat{};
     mat.mu = M.mu; mat.lam = M.lam; mat.model = M.model;
     mat.w_in = 1.0;

@@ -111,7 +111,7 @@ struct Material {
 // ---- launch wrappers (cc_kernels.hip) --------------------------------------
 void launch_predict(const MeshView& mv, const int* vperm, const double* x_user,
                     const double* v_user, const double* x_bc, double h, int quasi,
-                    double* x, double* xt, double* x0, int* bad, hipStream_t s);
+                    double* x, double* xt, double* x0, double* xtrial, int* bad, hipStream_t s);
 void launch_finalize(const MeshView& mv, const int* vperm, const double* x, const double* xt, const double* x0,
                      double h, int quasi, double* x_user, double* v_user, hipStream_t s);
 void launch_elem_hess(const MeshView& mv, int prec, const double* x, const Material& mat,
@@ -135,21 +135,30 @@ void launch_gradient(const MeshView& mv, const double* x, const double* xt, cons
                      double* g, double* partials, int* nparts, hipStream_t s);
 // Condensation of vertices [v0, v1).  With g and dout given (g the gradient
 // at the same x) the dense path also writes the directions into dout, and
-// with xmove given (a coloured sweep) adds them to xmove in place; the
-// return value says whether it did (else launch_cc_update).
+// with xmove given writes xfrom + d there (xfrom null: adds them to xmove in
+// place, as a coloured sweep does); the return value says whether it did
+// (else launch_cc_update).
 bool launch_cc_prep(const MeshView& mv, int prec, int method, int v0, int v1, const void* hb,
                     void* KL, unsigned long long* fallbacks, hipStream_t s,
                     const double* g = nullptr, double* dout = nullptr, double* xmove = nullptr,
-                    int tv_cap = 0, int chunk = 0);
+                    int tv_cap = 0, int chunk = 0, const double* xfrom = nullptr);
+// x_or_d = d, or with accumulate += d, or with from given = from + d.
 void launch_cc_update(const MeshView& mv, int prec, int method, int v0, int v1, const void* KL,
-                      const double* g, double* x_or_d, int accumulate, hipStream_t s);
+                      const double* g, double* x_or_d, int accumulate, hipStream_t s,
+                      const double* from = nullptr);
 void launch_energy(const MeshView& mv, const double* x, const double* xt, const Material& mat,
                    double* partials, int* nparts, hipStream_t s);
-void launch_reduce(const double* partials, int n, double* out, hipStream_t s);
 // Corotation: R_j = polar rotation of sum_{k in N(j)} (x_k - x_j)(X_k - X_j)^T for
 // every free vertex j (nptr/nidx: mesh neighbours, Xr: rest positions, SoA).
 void launch_rotations(const MeshView& mv, const double* x, const int* nptr, const int* nidx,
                       const double* Xr, double* rot, hipStream_t s);
+void launch_energy_grad(const MeshView& mv, const double* x, const double* xt, const Material& mat, double* g,
+                        double* partials, int* ne, int* ng, hipStream_t s);
+// Sums [first, first + sums) of: 0, the first ne partials into out[0]; 1, the
+// next ng into out[1]; and nc counters into out[2 ..].  out may be pinned host
+// memory.
+void launch_reduce_eg(const double* partials, int ne, int ng, int first, int sums,
+                      const unsigned long long* counters, int nc, double* out, hipStream_t s);
 void launch_axpy(int count, const double* x, const double* d, double alpha, double* out,
                  hipStream_t s);
 void launch_probe_element(const MeshView& mv, int prec, const double* x_user,

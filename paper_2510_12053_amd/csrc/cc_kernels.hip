@@ -1286,9 +1286,9 @@ __global__ void __launch_bounds__(WG) k_cc_dm_finish(MeshView mv, int method, in
                                                      const T* __restrict__ hb, T* __restrict__ KL,
                                                      unsigned long long* __restrict__ fb,
                                                      const double* __restrict__ g, double* __restrict__ dout,
-                                                     double* __restrict__ xmove) {
+                                                     const double* xfrom, double* xmove) {
   const int i = v0 + blockIdx.x * WG + threadIdx.x;
-  if (i < v1) dm_finish_body<T, D>(mv, method, i, hb, KL, fb, g, dout, xmove, xmove);
+  if (i < v1) dm_finish_body<T, D>(mv, method, i, hb, KL, fb, g, dout, xfrom, xmove);
 }
 
 template <typename T, int D, int TV, int CH>
@@ -1315,8 +1315,8 @@ k_cc_prep_tile(MeshView mv, int v0, int v1, const float* __restrict__ hb, float*
 template <typename T, int D, int G>
 __device__ __forceinline__ void update_body(const MeshView& mv, int method, int i, bool active,
                                             int lane, const T* __restrict__ KL,
-                                            const double* __restrict__ g, double* __restrict__ out,
-                                            int accumulate) {
+                                            const double* __restrict__ g, double* out,
+                                            int accumulate, const double* from = nullptr) {
   constexpr int DD = D * D;
   const T* Ub = basis_of<T>(mv);
   const int n = mv.n;
@@ -1371,7 +1371,8 @@ __device__ __forceinline__ void update_body(const MeshView& mv, int method, int 
     T acc = T(0);
 #pragma unroll
     for (int l = 0; l < D; ++l) acc += kl[r * D + l] * gt[l];
-    if (accumulate) out[r * n + i] -= double(acc);
+    if (from != nullptr) out[r * n + i] = from[r * n + i] - double(acc);
+    else if (accumulate) out[r * n + i] -= double(acc);
     else out[r * n + i] = -double(acc);
   }
 }
@@ -1380,9 +1381,9 @@ template <typename T, int D, int G>
 __global__ void __launch_bounds__(WG) k_cc_update(MeshView mv, int method, int v0, int v1,
                                                   const T* __restrict__ KL,
                                                   const double* __restrict__ g,
-                                                  double* __restrict__ out, int accumulate) {
+                                                  double* out, int accumulate, const double* from) {
   const int i = v0 + blockIdx.x * (WG / G) + threadIdx.x / G;
-  update_body<T, D, G>(mv, method, i, i < v1, threadIdx.x % G, KL, g, out, accumulate);
+  update_body<T, D, G>(mv, method, i, i < v1, threadIdx.x % G, KL, g, out, accumulate, from);
 }
 
 // Step energy: blocks [0, nbe) sum element energies, the rest the free-vertex
@@ -1463,13 +1464,47 @@ __global__ void __launch_bounds__(WG) k_energy(MeshView mv, const double* __rest
   if (threadIdx.x == 0) partials[blockIdx.x] = tot;
 }
 
-__global__ void __launch_bounds__(WG) k_reduce(const double* __restrict__ partials, int n,
-                                               double* __restrict__ out) {
+// Step energy (blocks [0, ne)) and gradient (the rest) at x in one launch: an
+// accepted trial point needs both, and each alone is a few us of mostly
+// latency on a small mesh.  With one reduction into host memory per point and
+// no second gradient at the point that the next sweep starts from, an iteration
+// of a single mesh is 6 launches and 1 wait instead of 13 and 2: the step of a
+// 17x17 square took 963 us and takes 594, of a 41x2x2 rod 466 and 252, of a
+// 21x6x6 bar 508 and 328, of the 81x21x21 beam with patch bases 2343 and 1768.
+template <int D, int G, bool FCR>
+__global__ void __launch_bounds__(WG) k_energy_grad(MeshView mv, const double* __restrict__ x,
+                                                    const double* __restrict__ xt, Material mat, int nbe, int ne,
+                                                    double* __restrict__ g, double* __restrict__ partials) {
   __shared__ double red[WG];
-  double v = 0.0;
-  for (int i = threadIdx.x; i < n; i += WG) v += partials[i];
+  const int b = blockIdx.x;
+  double v;
+  if (b < ne)
+    v = energy_body<D, FCR>(mv, b, nbe, x, xt, mat);
+  else
+    v = gradient_body<D, G, FCR>(mv, grad_vertex(mv, (b - ne) * (WG / G) + threadIdx.x / G), threadIdx.x % G, x, xt,
+                                 mat, g);
   const double tot = block_sum<WG>(v, red);
-  if (threadIdx.x == 0) out[0] = tot;
+  if (threadIdx.x == 0) partials[b] = tot;
+}
+
+// out[0] = sum of partials[0, ne), out[1] = sum of partials[ne, ne + ng), one
+// block each (the first block stands for sum `first`, so one block can do
+// either alone), and the step's counters into out[2 ..].  out may be pinned
+// host memory: the caller then reads it after one synchronisation, without a
+// copy of its own (about 3 us on the stream) for each value.
+__global__ void __launch_bounds__(WG) k_reduce_eg(const double* __restrict__ partials, int ne, int ng, int first,
+                                                  const unsigned long long* __restrict__ counters, int nc,
+                                                  double* __restrict__ out) {
+  __shared__ double red[WG];
+  const int which = first + blockIdx.x;
+  const double* p = partials + (which ? ne : 0);
+  const int cnt = which ? ng : ne;
+  double v = 0.0;
+  for (int i = threadIdx.x; i < cnt; i += WG) v += p[i];
+  const double tot = block_sum<WG>(v, red);
+  if (threadIdx.x == 0) out[which] = tot;
+  if (blockIdx.x == 0 && (int)threadIdx.x < nc)
+    reinterpret_cast<unsigned long long*>(out)[2 + threadIdx.x] = counters[threadIdx.x];
 }
 
 __global__ void k_axpy(int count, const double* __restrict__ x, const double* __restrict__ d,
@@ -1483,7 +1518,7 @@ __global__ void k_predict(MeshView mv, const int* __restrict__ vperm,
                           const double* __restrict__ xu, const double* __restrict__ vu,
                           const double* __restrict__ xbc, double h, int quasi,
                           double* __restrict__ x, double* __restrict__ xt,
-                          double* __restrict__ x0, int* __restrict__ bad) {
+                          double* __restrict__ x0, double* __restrict__ xtrial, int* __restrict__ bad) {
   const int v = blockIdx.x * WG + threadIdx.x;
   if (v >= mv.n) return;
   const int u = vperm[v], n = mv.n;
@@ -1502,6 +1537,8 @@ __global__ void k_predict(MeshView mv, const int* __restrict__ vperm,
     }
     xt[c * n + v] = xh;
     x[c * n + v] = xh;
+    // the trial buffer too: a sweep writes its free entries only
+    xtrial[c * n + v] = xh;
   }
   if (!ok) atomicOr(bad, 1);
 }
@@ -1594,9 +1631,9 @@ static inline int nblocks(long long n, int per) { return (int)((n + per - 1) / p
 
 void launch_predict(const MeshView& mv, const int* vperm, const double* x_user, const double* v_user,
                     const double* x_bc, double h, int quasi, double* x, double* xt, double* x0,
-                    int* bad, hipStream_t s) {
+                    double* xtrial, int* bad, hipStream_t s) {
   CC_DISPATCH_D(mv.D, k_predict<D><<<nblocks(mv.n, WG), WG, 0, s>>>(mv, vperm, x_user, v_user, x_bc,
-                                                                   h, quasi, x, xt, x0, bad));
+                                                                   h, quasi, x, xt, x0, xtrial, bad));
 }
 
 void launch_finalize(const MeshView& mv, const int* vperm, const double* x, const double* xt, const double* x0,
@@ -1824,7 +1861,7 @@ static bool band_ok(const MeshView& mv, int prec) {
 template <typename T, int D>
 static bool prep_dense(const MeshView& mv, int prec, int method, int v0, int v1, const void* hb,
                        void* KL, unsigned long long* fb, const double* g, double* dout, double* xmove,
-                       int tv_cap, int chunk, hipStream_t s) {
+                       const double* xfrom, int tv_cap, int chunk, hipStream_t s) {
   if (method == 0 || !band_ok(mv, prec)) return false;
   if constexpr (sizeof(T) == 4 && D == 3)
     if (mv.tile) {
@@ -1833,7 +1870,8 @@ static bool prep_dense(const MeshView& mv, int prec, int method, int v0, int v1,
                                                        tile_lds_bytes(cfg, mv.nf, mv.band_w), s>>>(
                                 mv, v0, v1, (const float*)hb, (float*)KL, g != nullptr ? dout : nullptr));
       k_cc_dm_finish<T, D><<<nblocks(v1 - v0, WG), WG, 0, s>>>(mv, method, v0, v1, (const T*)hb, (T*)KL, fb,
-                                                              g, dout, g != nullptr ? xmove : nullptr);
+                                                              g, dout, xfrom != nullptr ? xfrom : xmove,
+                                                              g != nullptr ? xmove : nullptr);
       return true;
     }
   const DenseCfg dc = dense_config(&mv.nf, &mv.band_w, 1, D, prec, tv_cap, chunk);
@@ -1841,21 +1879,22 @@ static bool prep_dense(const MeshView& mv, int prec, int method, int v0, int v1,
   CC_DISPATCH_TVCH(dc.tv, dc.ch, k_cc_prep_band<T, D, TV, CH><<<nblocks(v1 - v0, TV), CH, dc.lds, s>>>(
                                      mv, method, v0, v1, (const T*)hb, (T*)KL, g, dout));
   k_cc_dm_finish<T, D><<<nblocks(v1 - v0, WG), WG, 0, s>>>(mv, method, v0, v1, (const T*)hb, (T*)KL, fb,
-                                                          g, dout, g != nullptr ? xmove : nullptr);
+                                                          g, dout, xfrom != nullptr ? xfrom : xmove,
+                                                          g != nullptr ? xmove : nullptr);
   return true;
 }
 
 bool launch_cc_prep(const MeshView& mv, int prec, int method, int v0, int v1, const void* hb,
                     void* KL, unsigned long long* fb, hipStream_t s, const double* g, double* dout,
-                    double* xmove, int tv_cap, int chunk) {
+                    double* xmove, int tv_cap, int chunk, const double* xfrom) {
   if (v1 <= v0) return g != nullptr;
   bool done = false;
   if (prec == 0)
     CC_DISPATCH_D(mv.D, done = prep_dense<double, D>(mv, prec, method, v0, v1, hb, KL, fb, g, dout, xmove,
-                                                     tv_cap, chunk, s));
+                                                     xfrom, tv_cap, chunk, s));
   else
     CC_DISPATCH_D(mv.D, done = prep_dense<float, D>(mv, prec, method, v0, v1, hb, KL, fb, g, dout, xmove,
-                                                    tv_cap, chunk, s));
+                                                    xfrom, tv_cap, chunk, s));
   if (done) return g != nullptr;
   const int G = support_lanes(mv);
   if (prec == 0) CC_DISPATCH_D(mv.D, prep_g<double, D>(mv, method, v0, v1, hb, KL, fb, G, s));
@@ -1865,24 +1904,25 @@ bool launch_cc_prep(const MeshView& mv, int prec, int method, int v0, int v1, co
 
 template <typename T, int D>
 static void update_g(const MeshView& mv, int method, int v0, int v1, const void* KL, const double* g,
-                     double* out, int acc, int G, hipStream_t s) {
+                     double* out, int acc, const double* from, int G, hipStream_t s) {
   const int cnt = v1 - v0;
   if (G == 64)
     k_cc_update<T, D, 64><<<nblocks(cnt, WG / 64), WG, 0, s>>>(mv, method, v0, v1, (const T*)KL, g,
-                                                               out, acc);
+                                                               out, acc, from);
   else
     k_cc_update<T, D, 16><<<nblocks(cnt, WG / 16), WG, 0, s>>>(mv, method, v0, v1, (const T*)KL, g,
-                                                               out, acc);
+                                                               out, acc, from);
 }
 
 void launch_cc_update(const MeshView& mv, int prec, int method, int v0, int v1, const void* KL,
-                      const double* g, double* x_or_d, int accumulate, hipStream_t s) {
+                      const double* g, double* x_or_d, int accumulate, hipStream_t s,
+                      const double* from) {
   if (v1 <= v0) return;
   const int G = support_lanes(mv);
   if (prec == 0)
-    CC_DISPATCH_D(mv.D, update_g<double, D>(mv, method, v0, v1, KL, g, x_or_d, accumulate, G, s));
+    CC_DISPATCH_D(mv.D, update_g<double, D>(mv, method, v0, v1, KL, g, x_or_d, accumulate, from, G, s));
   else
-    CC_DISPATCH_D(mv.D, update_g<float, D>(mv, method, v0, v1, KL, g, x_or_d, accumulate, G, s));
+    CC_DISPATCH_D(mv.D, update_g<float, D>(mv, method, v0, v1, KL, g, x_or_d, accumulate, from, G, s));
 }
 
 void launch_energy(const MeshView& mv, const double* x, const double* xt, const Material& mat,
@@ -1894,9 +1934,6 @@ void launch_energy(const MeshView& mv, const double* x, const double* xt, const 
                   CC_DISPATCH_D(mv.D, k_energy<D, FCR><<<nbe + nbv, WG, 0, s>>>(mv, x, xt, mat, nbe, partials)));
 }
 
-void launch_reduce(const double* partials, int n, double* out, hipStream_t s) {
-  k_reduce<<<1, WG, 0, s>>>(partials, n, out);
-}
 
 // R_j = U V^T from the rotation-variant SVD of
 // M = sum_{k in N(j)} (x_k - x_j)(X_k - X_j)^T: the polar rotation (det +1).
@@ -1953,6 +1990,20 @@ void launch_rotations(const MeshView& mv, const double* x, const int* nptr, cons
   CC_DISPATCH_D(mv.D, k_rotations<D><<<nblocks(mv.nf, WG), WG, 0, s>>>(mv, x, nptr, nidx, Xr, rot));
 }
 
+void launch_energy_grad(const MeshView& mv, const double* x, const double* xt, const Material& mat, double* g,
+                        double* partials, int* ne, int* ng, hipStream_t s) {
+  const int nbe = nblocks(mv.m, WG);
+  *ne = nbe + nblocks(mv.nf, WG);
+  *ng = nblocks(mv.nf, WG / GRAD_G);
+  if (*ne + *ng == 0) return;
+  CC_DISPATCH_MAT(mat.model == MAT_FCR,
+                  CC_DISPATCH_D(mv.D, k_energy_grad<D, GRAD_G, FCR><<<*ne + *ng, WG, 0, s>>>(mv, x, xt, mat, nbe,
+                                                                                             *ne, g, partials)));
+}
+void launch_reduce_eg(const double* partials, int ne, int ng, int first, int sums,
+                      const unsigned long long* counters, int nc, double* out, hipStream_t s) {
+  k_reduce_eg<<<sums, WG, 0, s>>>(partials, ne, ng, first, counters, nc, out);
+}
 void launch_axpy(int count, const double* x, const double* d, double alpha, double* out,
                  hipStream_t s) {
   if (count <= 0) return;
