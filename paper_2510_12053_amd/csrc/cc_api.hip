@@ -65,7 +65,7 @@ struct Mesh {
          *g = nullptr, *partials = nullptr;
   double* rot = nullptr;  // corotation: rotation of every free vertex (D*D each)
   double* corr = nullptr; // last step's correction x - x~ (MeshView::corr)
-  void *estore = nullptr, *hb = nullptr, *KL = nullptr;
+  void *estore = nullptr, *hb = nullptr, *KL = nullptr, *segsum = nullptr;
   unsigned long long* fb = nullptr;   // STEP_COUNTERS words
   int* bad = nullptr;                 // = fb + 4
   // last-step info
@@ -87,6 +87,7 @@ struct Mesh {
     v.mass = mass; v.vperm = d_vperm; v.star_ptr = star_ptr; v.star = star; v.rowptr = d_rowptr;
     v.colidx = d_colidx; v.blkrow = blkrow; v.cptr = cptr; v.centry = centry; v.nnzb = nnzb;
     v.bvert = d_bvert; v.bpos = d_bpos; v.bq_cnt = d_bqcnt; v.hq_slot = d_hqslot;
+    v.segsum = segsum;
     v.hq = dense ? hq : nullptr;   // the assembly writes the band copy only for dense bases
     v.qmax = qmax; v.band_w = band_w;
     v.tb = dense ? tb : nullptr;
@@ -166,7 +167,7 @@ void free_mesh(Mesh& M) {
   dfree(M.d_cel_ptr); dfree(M.d_cel); dfree(M.d_csl_ptr); dfree(M.d_csl); dfree(M.dinv_d); dfree(M.vol_d); dfree(M.mass); dfree(M.dinv_f); dfree(M.vol_f);
   free_basis(M);
   dfree(M.x); dfree(M.xt); dfree(M.x0); dfree(M.xtrial); dfree(M.dvec); dfree(M.g);
-  dfree(M.partials); dfree(M.estore); dfree(M.hb); dfree(M.KL); dfree(M.fb);
+  dfree(M.partials); dfree(M.estore); dfree(M.hb); dfree(M.KL); dfree(M.segsum); dfree(M.fb);
   dfree(M.rot); dfree(M.corr);
   dfree(M.nptr); dfree(M.nidx); dfree(M.frank); dfree(M.Xr); dfree(M.feat); dfree(M.delta);
 }
@@ -803,6 +804,7 @@ void build_mesh(cc_ctx* ctx, Mesh& M) {
   M.estore = dalloc<double>((size_t)NB * m * D * D);
   M.hb = dalloc<double>((size_t)M.nnzb * D * D);
   M.KL = dalloc<double>((size_t)nf * 2 * D * D);
+  M.segsum = dalloc<double>((size_t)nf * (cc::SEG_MAX - 1) * (D * D + D));
   M.rot = dalloc<double>((size_t)std::max(nf, 1) * D * D);
   M.corr = dalloc<double>((size_t)D * n);
   HIPC(hipMemsetAsync(M.corr, 0, (size_t)D * n * sizeof(double), s));

@@ -40,6 +40,10 @@ struct MeshView {
   const int* hq_slot;
   void* hq;
   int qmax, band_w;
+  // Sums of the second and later segments of the dense condensation's rows:
+  // per segment and free vertex D*D values of Ht and D of b, in the precision
+  // of the sweep (room for SEG_MAX - 1 segments in float64).
+  void* segsum;
   // Tile records (float32 3D dense bases whose rows hold at most TILE_Q upper
   // blocks; null otherwise): the same blocks as hq in the operand layout of
   // the matrix-core condensation, tb[(p * TILE_Q + q) * 12 + s * 4 + r] =
@@ -227,6 +231,9 @@ DenseCfg dense_config(const int* nf, const int* band_w, int count, int D, int pr
                       int chunk = 0);
 
 // ---- matrix-core condensation of float32 3D dense bases (prep_tile_body) ----
+// Segments that the dense condensation splits a row's band into where a launch
+// is short of workgroups.
+constexpr int SEG_MAX = 2;
 constexpr int TILE_Q = 8;                    // upper blocks per band row it handles
 // Configurations (index + 1; 0: none): 1, ten vertices per workgroup of eight
 // waves, chunks of 64 band positions, for band widths up to TILE_RING - 64;

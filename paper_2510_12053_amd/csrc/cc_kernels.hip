@@ -691,6 +691,13 @@ struct SlotRegs {
 // The end of a dense condensation's workgroup: per vertex, A_i from its basis
 // row in global memory (one wave per vertex), and A_i, Ht_i = Y + Y^T and b_i
 // from the workgroup's sums tot ([vertex][Y, then b]).
+// Segment seg's (1 .. nseg - 1) sums of vertex i: its part of Ht and of b.
+// Segment 0 leaves its own in the K, L slots and the direction.
+template <typename T, int D>
+__device__ __forceinline__ T* seg_sums(const MeshView& mv, int seg, int i) {
+  return reinterpret_cast<T*>(mv.segsum) + ((size_t)(seg - 1) * mv.nf + i) * (D * D + D);
+}
+
 template <typename T, int D>
 __device__ __forceinline__ void band_tail(const MeshView& mv, int i0, int nv, int w, int nw,
                                           const T* __restrict__ hb, T* __restrict__ KL, const T* tot,
@@ -747,12 +754,13 @@ __device__ __forceinline__ void band_tail(const MeshView& mv, int i0, int nv, in
 template <typename T, int D, int TV, int CH>
 __device__ __forceinline__ void prep_band_body(const MeshView& mv, int method, int i0, int nv,
                                                const T* __restrict__ hb, T* __restrict__ KL, T* smem,
-                                               const double* __restrict__ g, double* __restrict__ bout) {
+                                               const double* __restrict__ g, double* __restrict__ bout, int seg,
+                                               int nseg) {
   constexpr int DD = D * D, NW = CH / 64, NR = DD + D, SLW = ring_slot_words(TV, D, sizeof(T));
   const int nf = mv.nf, n = mv.n, bw = mv.band_w;
   const int R = min(nf, CH + bw);                   // ring length (band_ring)
   // position pos >= p0 (the current chunk's start) lives in slot
-  // (pos - p0 + p0 % R) mod R; pos - p0 < CH + bw, so one conditional
+  // (pos - p0 + p0's slot) mod R; pos - p0 < CH + bw, so one conditional
   // subtraction of R reduces it
   auto wrap = [&](int t) { return (int)min((unsigned)t, (unsigned)(t - R)); };
   uint32_t* ring = reinterpret_cast<uint32_t*>(smem);              // [R][SLW] words
@@ -792,14 +800,16 @@ __device__ __forceinline__ void prep_band_body(const MeshView& mv, int method, i
         }
       }
   };
-  int lo = R;                                       // first fill: positions [0, R) in slots [0, R)
-  for (int pos = tid; pos < lo; pos += CH) {
+  // band rows [pa, pb): whole chunks, the segment's share of them
+  const int nch = (nf + CH - 1) / CH, pa = nch * seg / nseg * CH, pb = min(nf, nch * (seg + 1) / nseg * CH);
+  int lo = min(nf, pa + R);                         // first fill: positions [pa, lo) in slots [0, lo - pa)
+  for (int pos = pa + tid; pos < lo; pos += CH) {
     T blk[TV][DD];
     fetch(pos, blk);
-    put(pos, blk);
+    put(pos - pa, blk);
   }
-  int lo_slot = 0;                                  // lo % R
-  int p0_slot = 0;                                  // p0 % R
+  int lo_slot = 0;                                  // slot of position lo
+  int p0_slot = 0;                                  // slot of position p0
   __syncthreads();
   T Y[TV][DD], Bv[TV][D];
 #pragma unroll
@@ -809,9 +819,9 @@ __device__ __forceinline__ void prep_band_body(const MeshView& mv, int method, i
 #pragma unroll
     for (int r = 0; r < D; ++r) Bv[v][r] = T(0);
   }
-  for (int p0 = 0; p0 < nf; p0 += CH) {
+  for (int p0 = pa; p0 < pb; p0 += CH) {
     // chunk p0 + CH needs positions up to p0 + 2 CH + bw: prefetch them
-    const int nhi = min(nf, p0 + 2 * CH + bw);
+    const int nhi = min(nf, min(p0 + 2 * CH, pb) + bw);
     const int ppos = lo + tid;
     const bool pf = ppos < nhi;
     T pre[TV][DD];
@@ -950,7 +960,13 @@ __device__ __forceinline__ void prep_band_body(const MeshView& mv, int method, i
     tot[tid] = acc;
   }
   __syncthreads();
-  band_tail<T, D>(mv, i0, nv, w, NW, hb, KL, tot, bout);
+  if (seg == 0) {
+    band_tail<T, D>(mv, i0, nv, w, NW, hb, KL, tot, bout);
+  } else if (tid < nv * NR) {
+    const int v = tid / NR, k = tid % NR;
+    const T* Yt = tot + v * NR;
+    seg_sums<T, D>(mv, seg, i0 + v)[k] = k < DD ? Yt[k] + Yt[k % D * D + k / D] : Yt[k];
+  }
 }
 
 // A_i = sum_k H_ik R_k U_i[k] of a tile workgroup's vertices, into their K slots
@@ -1033,7 +1049,8 @@ __device__ __forceinline__ void tile_rows(const MeshView& mv, int i0, int nv, in
 // workgroups: one workgroup per CU fits, and eight waves took 117 ms).
 template <int NG, int NS, int CH>
 __device__ __forceinline__ void prep_tile_body(const MeshView& mv, int i0, int nv, const float* __restrict__ hb,
-                                               float* __restrict__ KL, float* smem, double* __restrict__ bout) {
+                                               float* __restrict__ KL, float* smem, double* __restrict__ bout,
+                                               int seg, int nseg) {
   typedef float f4 __attribute__((ext_vector_type(4)));
   typedef __attribute__((address_space(3))) float lds_float;
   constexpr int V = 5 * NG, NT = 64 * NS, SEG = CH / (4 * NS), NR = 12, PHASES = SEG * NG;
@@ -1043,6 +1060,9 @@ __device__ __forceinline__ void prep_tile_body(const MeshView& mv, int i0, int n
                     PHASES % 2 == 0 && TILE_Q == 8, "configuration");
   const int nf = mv.nf, nf9 = nf * 9;
   const int R = CFG == 0 ? TILE_RING : tile_ring(CFG + 1, nf, mv.band_w), VS = tile_stride(R);
+  // band rows [pa, pb): the segment's share of the row in whole rings, so that
+  // position p keeps its slot p mod R
+  const int rings = (nf + R - 1) / R, pa = rings * seg / nseg * R, pb = min(nf, rings * (seg + 1) / nseg * R);
   const int tid = threadIdx.x, l = tid % 64, w = __builtin_amdgcn_readfirstlane(tid / 64);
   // A vertex's row is copied into its ring in pieces of 64 words, one word per
   // lane.  What a piece reads past the row's end (the next row, or the padding
@@ -1058,18 +1078,18 @@ __device__ __forceinline__ void prep_tile_body(const MeshView& mv, int i0, int n
   };
   auto row4 = [&](int v) { return (uint32_t)((v < nv ? v : 0) * nf9) * 4u; };
   auto ring4 = [&](int v) { return (uint32_t)(v * VS) * 4u; };
-  const int UF = R * 9 / 64, fill = V * UF;          // first fill: positions [0, R)
+  const int UF = R * 9 / 64, fill = V * UF;          // first fill: positions [pa, pa + R)
   constexpr int FB = 17;                             // pieces in flight per wave
   uint32_t first[FB];
   auto fill_load = [&](int x0) {
 #pragma unroll
     for (int e = 0; e < FB; ++e) {
       const int k = min(x0 + e * NS, fill - 1);
-      first[e] = load_piece(row4(k / UF) + (uint32_t)(k % UF) * 256u);
+      first[e] = load_piece(row4(k / UF) + (uint32_t)(k % UF) * 256u + (uint32_t)pa * 36u);
     }
   };
   fill_load(w);
-  tile_rows<V>(mv, i0, nv, w, hb, KL);               // A_i, while the fill is on its way
+  if (seg == 0) tile_rows<V>(mv, i0, nv, w, hb, KL); // A_i, while the fill is on its way
   for (int x0 = w; x0 < fill; x0 += FB * NS) {
 #pragma unroll
     for (int e = 0; e < FB; ++e) {
@@ -1153,15 +1173,15 @@ __device__ __forceinline__ void prep_tile_body(const MeshView& mv, int i0, int n
   };
 #pragma unroll
   for (int t = 0; t < SEG; ++t) {
-    fetch_off(t, 0);
-    fetch_rec(t, 0);
+    fetch_off(t, pa);
+    fetch_rec(t, pa);
   }
   uint32_t slot4 = 0;                                // bytes of the chunk's first ring slot
   __syncthreads();
-  for (int p0 = 0; p0 < nf; p0 += CH) {
+  for (int p0 = pa; p0 < pb; p0 += CH) {
     // chunk p0 + CH needs positions up to p0 + R + CH: read them ahead; they
     // replace positions [p0, p0 + CH), which no later row reads
-    const bool refill = p0 + R < nf;
+    const bool refill = p0 + R < nf && p0 + CH < pb;
     uint32_t pre[NP];
     addresses(0);
     read_u(0, 0);
@@ -1234,7 +1254,8 @@ __device__ __forceinline__ void prep_tile_body(const MeshView& mv, int i0, int n
         for (int r = 0; r < 4; ++r) acc += rw[4 * 64 + r * 16 + c3 + k - 9];
       }
     }
-    if (k < 9) gptr_w(KL)[(size_t)(i0 + v) * 18 + 9 + k] = acc + acc_t;
+    if (seg > 0) gptr_w(seg_sums<float, 3>(mv, seg, i0 + v))[k] = k < 9 ? acc + acc_t : acc;
+    else if (k < 9) gptr_w(KL)[(size_t)(i0 + v) * 18 + 9 + k] = acc + acc_t;
     else if (bout != nullptr) gptr_w(bout)[(size_t)(k - 9) * mv.n + i0 + v] = double(acc);
   }
 }
@@ -1246,14 +1267,23 @@ __device__ __forceinline__ void dm_finish_body(const MeshView& mv, int method, i
                                                const T* __restrict__ hb, T* __restrict__ KL,
                                                unsigned long long* __restrict__ fb,
                                                const double* __restrict__ g, double* __restrict__ dout,
-                                               const double* x = nullptr, double* xtrial = nullptr) {
+                                               const double* x, double* xtrial, int nseg) {
   constexpr int DD = D * D;
-  T A[DD], Ht[DD];
+  T A[DD], Ht[DD], bs[D];
   const T* in = KL + (size_t)i * 2 * DD;
 #pragma unroll
   for (int r = 0; r < DD; ++r) {
     A[r] = in[r];
     Ht[r] = in[DD + r];
+  }
+#pragma unroll
+  for (int c = 0; c < D; ++c) bs[c] = T(0);
+  for (int sg = 1; sg < nseg; ++sg) {                // the other segments' sums, in order
+    const T* ss = seg_sums<T, D>(mv, sg, i);
+#pragma unroll
+    for (int r = 0; r < DD; ++r) Ht[r] += ss[r];
+#pragma unroll
+    for (int c = 0; c < D; ++c) bs[c] += ss[DD + c];
   }
   cc_finish<T, D>(mv, method, i, mv.nf <= 1, A, Ht, hb, KL, fb);
   if (dout == nullptr) return;
@@ -1261,7 +1291,7 @@ __device__ __forceinline__ void dm_finish_body(const MeshView& mv, int method, i
   const T* kl = KL + (size_t)i * 2 * DD;
   T b[D], gt[D];
 #pragma unroll
-  for (int c = 0; c < D; ++c) b[c] = T(dout[(size_t)c * n + i]);
+  for (int c = 0; c < D; ++c) b[c] = T(dout[(size_t)c * n + i]) + bs[c];
 #pragma unroll
   for (int r = 0; r < D; ++r) {
     T lb = T(0);
@@ -1286,28 +1316,30 @@ __global__ void __launch_bounds__(WG) k_cc_dm_finish(MeshView mv, int method, in
                                                      const T* __restrict__ hb, T* __restrict__ KL,
                                                      unsigned long long* __restrict__ fb,
                                                      const double* __restrict__ g, double* __restrict__ dout,
-                                                     const double* xfrom, double* xmove) {
+                                                     const double* xfrom, double* xmove, int nseg) {
   const int i = v0 + blockIdx.x * WG + threadIdx.x;
-  if (i < v1) dm_finish_body<T, D>(mv, method, i, hb, KL, fb, g, dout, xfrom, xmove);
+  if (i < v1) dm_finish_body<T, D>(mv, method, i, hb, KL, fb, g, dout, xfrom, xmove, nseg);
 }
 
 template <typename T, int D, int TV, int CH>
 __global__ void __launch_bounds__(CH) k_cc_prep_band(MeshView mv, int method, int v0, int v1,
                                                       const T* __restrict__ hb, T* __restrict__ KL,
-                                                      const double* __restrict__ g, double* __restrict__ bout) {
+                                                      const double* __restrict__ g, double* __restrict__ bout,
+                                                      int nseg) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int i0 = v0 + blockIdx.x * TV;
+  const int nb = gridDim.x / nseg, i0 = v0 + blockIdx.x % nb * TV;
   prep_band_body<T, D, TV, CH>(mv, method, i0, min(TV, v1 - i0), hb, KL, reinterpret_cast<T*>(smem_raw), g,
-                               bout);
+                               bout, blockIdx.x / nb, nseg);
 }
 
 template <int NG, int NS, int CH>
 __global__ void __launch_bounds__(64 * NS, 4)
 k_cc_prep_tile(MeshView mv, int v0, int v1, const float* __restrict__ hb, float* __restrict__ KL,
-               double* __restrict__ bout) {
+               double* __restrict__ bout, int nseg) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int i0 = v0 + blockIdx.x * 5 * NG;
-  prep_tile_body<NG, NS, CH>(mv, i0, min(5 * NG, v1 - i0), hb, KL, reinterpret_cast<float*>(smem_raw), bout);
+  const int nb = gridDim.x / nseg, i0 = v0 + blockIdx.x % nb * 5 * NG;
+  prep_tile_body<NG, NS, CH>(mv, i0, min(5 * NG, v1 - i0), hb, KL, reinterpret_cast<float*>(smem_raw), bout,
+                             blockIdx.x / nb, nseg);
 }
 
 // dx_i = -K_i (g_i - L_i U_i^T g_C); written to d (Jacobi) or added to x
@@ -1795,6 +1827,28 @@ DenseCfg dense_config(const int* nf, const int* band_w, int count, int D, int pr
   return best;
 }
 
+// Workgroups of the dense condensation that are resident at once.
+static int dense_resident(const DenseCfg& dc, int prec) {
+  const int by_lds = (int)(g_lds_limit / dc.lds), by_reg = 4 * dense_reg_waves(prec, dc.tv) / (dc.ch / 64);
+  return 256 * std::max(1, std::min(by_lds, by_reg));
+}
+static int tile_resident(int cfg) { return cfg == 2 ? 256 : 512; }
+
+// Segments that a launch of the dense condensation splits its rows' bands
+// into: two where the launch has at most one and a half workgroups per
+// resident place and a row is longer than a segment's unit (ring or chunk).
+// The time of such a launch is that of one workgroup's serial walk along the
+// band, or two where the second round is mostly empty; half the walk costs a
+// second ring fill.  Measured with one / two / three segments: 29x9x7 bar
+// (353 workgroups on 512 places) 72 / 65 us, the colours of sixteen uneven bars
+// (about 600 on 512) 52 / 43 / 43 us and the step 15.8 / 14.7 / 14.6 ms,
+// float64 21x6x6 bar (360 on 1,024) step 477 / 433 / 452 us, four of them
+// (1,440) 624 / 602 / 639 us; sixteen uneven bars whole (2,400 on 512), four
+// steps 11.99 / 12.25 / 12.68 ms.
+static int prep_segments(int max_nf, int blocks, int unit, int resident) {
+  return 2 * blocks <= 3 * resident && max_nf > unit ? SEG_MAX : 1;
+}
+
 size_t tile_lds_bytes(int cfg, int nf, int band_w) {
   const int v = 5 * TILE_G[cfg - 1];
   const size_t ring = (size_t)v * tile_stride(tile_ring(cfg, nf, band_w)) * 4;
@@ -1866,21 +1920,24 @@ static bool prep_dense(const MeshView& mv, int prec, int method, int v0, int v1,
   if constexpr (sizeof(T) == 4 && D == 3)
     if (mv.tile) {
       const int rows = v1 - v0, cfg = tile_config(&mv.nf, &mv.band_w, &rows, 1);
-      CC_DISPATCH_TILE(cfg, k_cc_prep_tile<NG, NS, CH><<<nblocks(rows, 5 * NG), 64 * NS,
+      const int blocks = nblocks(rows, 5 * TILE_G[cfg - 1]);
+      const int nseg = prep_segments(mv.nf, blocks, tile_ring(cfg, mv.nf, mv.band_w), tile_resident(cfg));
+      CC_DISPATCH_TILE(cfg, k_cc_prep_tile<NG, NS, CH><<<blocks * nseg, 64 * NS,
                                                        tile_lds_bytes(cfg, mv.nf, mv.band_w), s>>>(
-                                mv, v0, v1, (const float*)hb, (float*)KL, g != nullptr ? dout : nullptr));
+                                mv, v0, v1, (const float*)hb, (float*)KL, g != nullptr ? dout : nullptr, nseg));
       k_cc_dm_finish<T, D><<<nblocks(v1 - v0, WG), WG, 0, s>>>(mv, method, v0, v1, (const T*)hb, (T*)KL, fb,
                                                               g, dout, xfrom != nullptr ? xfrom : xmove,
-                                                              g != nullptr ? xmove : nullptr);
+                                                              g != nullptr ? xmove : nullptr, nseg);
       return true;
     }
   const DenseCfg dc = dense_config(&mv.nf, &mv.band_w, 1, D, prec, tv_cap, chunk);
   if (dc.tv == 0) return false;
-  CC_DISPATCH_TVCH(dc.tv, dc.ch, k_cc_prep_band<T, D, TV, CH><<<nblocks(v1 - v0, TV), CH, dc.lds, s>>>(
-                                     mv, method, v0, v1, (const T*)hb, (T*)KL, g, dout));
+  const int blocks = nblocks(v1 - v0, dc.tv), nseg = prep_segments(mv.nf, blocks, dc.ch, dense_resident(dc, prec));
+  CC_DISPATCH_TVCH(dc.tv, dc.ch, k_cc_prep_band<T, D, TV, CH><<<blocks * nseg, CH, dc.lds, s>>>(
+                                     mv, method, v0, v1, (const T*)hb, (T*)KL, g, dout, nseg));
   k_cc_dm_finish<T, D><<<nblocks(v1 - v0, WG), WG, 0, s>>>(mv, method, v0, v1, (const T*)hb, (T*)KL, fb,
                                                           g, dout, xfrom != nullptr ? xfrom : xmove,
-                                                          g != nullptr ? xmove : nullptr);
+                                                          g != nullptr ? xmove : nullptr, nseg);
   return true;
 }
 
@@ -2246,38 +2303,39 @@ __global__ void __launch_bounds__(CH) kb_prep_band(const BatchItem* __restrict__
                                                     const BatchCtl* __restrict__ ctl,
                                                     const int* __restrict__ boff,
                                                     const int* __restrict__ order, int nmesh,
-                                                    int method, int colour, int fuse) {
+                                                    int method, int colour, int fuse, int nseg) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int slot = block_mesh(boff, nmesh, blockIdx.x), mi = order[slot];
   if (!ctl[mi].active) return;
   const BatchItem& it = items[mi];
   int v0, v1;
   vertex_range(it, colour, v0, v1);
-  const int i0 = v0 + (blockIdx.x - boff[slot]) * TV;
+  const int lb = blockIdx.x - boff[slot], nb = (boff[slot + 1] - boff[slot]) / nseg, i0 = v0 + lb % nb * TV;
   prep_band_body<T, D, TV, CH>(it.mv, method, i0, min(TV, v1 - i0), (const T*)it.hb, (T*)it.KL,
-                           reinterpret_cast<T*>(smem_raw), fuse ? it.g : nullptr, fuse ? it.d : nullptr);
+                           reinterpret_cast<T*>(smem_raw), fuse ? it.g : nullptr, fuse ? it.d : nullptr, lb / nb,
+                           nseg);
 }
 
 template <int NG, int NS, int CH>
 __global__ void __launch_bounds__(64 * NS, 4)
 kb_prep_tile(const BatchItem* __restrict__ items, const BatchCtl* __restrict__ ctl, const int* __restrict__ boff,
-             const int* __restrict__ order, int nmesh, int colour, int fuse) {
+             const int* __restrict__ order, int nmesh, int colour, int fuse, int nseg) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int slot = block_mesh(boff, nmesh, blockIdx.x), mi = order[slot];
   if (!ctl[mi].active) return;
   const BatchItem& it = items[mi];
   int v0, v1;
   vertex_range(it, colour, v0, v1);
-  const int i0 = v0 + (blockIdx.x - boff[slot]) * 5 * NG;
+  const int lb = blockIdx.x - boff[slot], nb = (boff[slot + 1] - boff[slot]) / nseg, i0 = v0 + lb % nb * 5 * NG;
   prep_tile_body<NG, NS, CH>(it.mv, i0, min(5 * NG, v1 - i0), (const float*)it.hb, (float*)it.KL,
-                             reinterpret_cast<float*>(smem_raw), fuse ? it.d : nullptr);
+                             reinterpret_cast<float*>(smem_raw), fuse ? it.d : nullptr, lb / nb, nseg);
 }
 
 template <typename T, int D>
 __global__ void __launch_bounds__(WG) kb_dm_finish(const BatchItem* __restrict__ items,
                                                    const BatchCtl* __restrict__ ctl,
                                                    const int* __restrict__ boff, int nmesh,
-                                                   int method, int colour, int fuse) {
+                                                   int method, int colour, int fuse, int nseg) {
   const int mi = block_mesh(boff, nmesh, blockIdx.x);
   if (!ctl[mi].active) return;
   const BatchItem& it = items[mi];
@@ -2288,7 +2346,7 @@ __global__ void __launch_bounds__(WG) kb_dm_finish(const BatchItem* __restrict__
   // vertices move in place in the sweep's running state xtrial
   if (i < v1)
     dm_finish_body<T, D>(it.mv, method, i, (const T*)it.hb, (T*)it.KL, it.fb, fuse ? it.g : nullptr,
-                         fuse ? it.d : nullptr, fuse == 2 ? it.xtrial : it.x, fuse ? it.xtrial : nullptr);
+                         fuse ? it.d : nullptr, fuse == 2 ? it.xtrial : it.x, fuse ? it.xtrial : nullptr, nseg);
 }
 
 template <typename T, int D, int G>
@@ -2614,6 +2672,7 @@ struct BatchPlan {
   Offsets eg;       // energy then gradient blocks of each mesh (kb_energy_grad)
   std::vector<Offsets> elemc, asmbc;   // element / slot blocks of colour c's dirty lists
   std::vector<Offsets> prep, prepd, fin, upd;   // index 0: all free vertices, c+1: colour c
+  std::vector<int> nseg;      // segments of the dense condensation's rows (prep_segments), indexed as prepd
   std::vector<int> dorder_h;  // meshes by falling nf: the order of prepd's blocks
   int* dorder = nullptr;
   int max_colours = 0;
@@ -2668,6 +2727,7 @@ static void plan_vertex_offsets(BatchPlan* p, hipStream_t s) {
   p->prepd.assign(p->max_colours + 1, Offsets{});
   p->fin.assign(p->max_colours + 1, Offsets{});
   p->upd.assign(p->max_colours + 1, Offsets{});
+  p->nseg.clear();
   for (int c = -1; c < p->max_colours; ++c) {
     std::vector<int> cp(p->nmesh), cd(p->nmesh), cf(p->nmesh), cu(p->nmesh);
     for (int m = 0; m < p->nmesh; ++m) {
@@ -2688,7 +2748,23 @@ static void plan_vertex_offsets(BatchPlan* p, hipStream_t s) {
     }
     offsets_build(p->prep[c + 1], cp, s);
     std::vector<int> cdo(p->nmesh);
-    for (int m = 0; m < p->nmesh; ++m) cdo[m] = cd[p->dorder_h[m]];
+    int blocks = 0, max_nf = 0, unit = p->ch;         // the longest of these rows, and its segments' unit
+    for (int m = 0; m < p->nmesh; ++m) {
+      const MeshView& mv = p->items_h[p->dorder_h[m]].mv;
+      cdo[m] = cd[p->dorder_h[m]];
+      blocks += cdo[m];
+      if (cdo[m] > 0 && mv.nf > max_nf) {
+        max_nf = mv.nf;
+        if (p->tile > 0) unit = tile_ring(p->tile, mv.nf, mv.band_w);
+      }
+    }
+    int ns = 1;
+    if (blocks > 0)
+      ns = prep_segments(max_nf, blocks, unit,
+                         p->tile > 0 ? tile_resident(p->tile)
+                                     : dense_resident(DenseCfg{p->tv, p->ch, p->lds}, p->cfg.prec));
+    p->nseg.push_back(ns);
+    for (int& k : cdo) k *= ns;
     offsets_build(p->prepd[c + 1], cdo, s);
     offsets_build(p->fin[c + 1], cf, s);
     offsets_build(p->upd[c + 1], cu, s);
@@ -2869,15 +2945,17 @@ static void b_prep(BatchPlan* p, int colour, hipStream_t s, int fuse = 0) {
                                                   colour, p->scap);
   if (gridn(od) > 0) {
     const Offsets& of = p->fin[colour + 1];
+    const int nseg = p->nseg[colour + 1];
     if (p->tile > 0) {
       CC_DISPATCH_TILE(p->tile, kb_prep_tile<NG, NS, CH><<<gridn(od), 64 * NS, p->lds, s>>>(
-                                    p->items_d, p->ctl_d, od.d, p->dorder, p->nmesh, colour, fuse));
+                                    p->items_d, p->ctl_d, od.d, p->dorder, p->nmesh, colour, fuse, nseg));
     } else {
       CC_DISPATCH_TVCH(p->tv, p->ch, kb_prep_band<T, D, TV, CH><<<gridn(od), CH, p->lds, s>>>(
-                                p->items_d, p->ctl_d, od.d, p->dorder, p->nmesh, p->cfg.method, colour, fuse));
+                                p->items_d, p->ctl_d, od.d, p->dorder, p->nmesh, p->cfg.method, colour, fuse,
+                                nseg));
     }
     kb_dm_finish<T, D><<<gridn(of), WG, 0, s>>>(p->items_d, p->ctl_d, of.d, p->nmesh, p->cfg.method,
-                                               colour, fuse);
+                                               colour, fuse, nseg);
   }
   p->mark(3, 0);
 }
