@@ -1182,21 +1182,31 @@ struct Stepper {
     g_ok = x == M.x;
   }
   // Element Hessians and block rows at x: of every element (colour < 0), or
-  // only of those that the moves of colour `colour`'s vertices changed.
-  void hessian(const double* x, int colour = -1) {
+  // only of those that the moves of colour `colour`'s vertices changed; before
+  // the assembly, which may store them with its records, the vertex rotations
+  // (corotation) and, unless M.g holds it already, the gradient at x.  at: x, or
+  // the buffer with the same free entries that M.g may belong to.  One launch
+  // for all of that unless its kernels are being timed one by one.
+  void hessian(const double* x, int colour, const double* at) {
     mv.rot = p.corotate ? M.rot : nullptr;   // corotation: rotations at the Hessian's positions
-    if (p.corotate) {
-      if (!M.rot || !M.nptr || !M.nidx || !M.Xr)
-        throw ApiError{CC_E_STATE, "corotation buffers missing"};
-      cc::launch_rotations(mv, x, M.nptr, M.nidx, M.Xr, M.rot, s);
-    }
+    if (p.corotate && (!M.rot || !M.nptr || !M.nidx || !M.Xr))
+      throw ApiError{CC_E_STATE, "corotation buffers missing"};
+    const bool grad = !(g_ok && at == M.x);
     const int* el = colour < 0 ? nullptr : mv.cel + M.cel_ptr_h[colour];
     const int ne = colour < 0 ? M.m : M.cel_ptr_h[colour + 1] - M.cel_ptr_h[colour];
+    if ((p.corotate || grad) && !(ctx->prof_mask & (1 << CC_K_ELEM_HESS | 1 << CC_K_GRADIENT))) {
+      cc::launch_point(mv, p.precision, x, M.xt, mat, M.estore, el, ne, M.nptr, M.nidx, M.Xr,
+                       p.corotate ? M.rot : nullptr, grad ? M.g : nullptr, s);
+      g_ok = at == M.x;
+    } else {
+      gradient_only(at);
+      if (p.corotate) cc::launch_rotations(mv, x, M.nptr, M.nidx, M.Xr, M.rot, s);
+      ctx->timed(CC_K_ELEM_HESS, [&] {
+        cc::launch_elem_hess_list(mv, p.precision, x, mat, mat.s_el, M.estore, s, el, ne);
+      });
+    }
     const int* sl = colour < 0 ? nullptr : mv.csl + M.csl_ptr_h[colour];
     const int ns = colour < 0 ? M.nnzb : M.csl_ptr_h[colour + 1] - M.csl_ptr_h[colour];
-    ctx->timed(CC_K_ELEM_HESS, [&] {
-      cc::launch_elem_hess_list(mv, p.precision, x, mat, mat.s_el, M.estore, s, el, ne);
-    });
     ctx->timed(CC_K_ASSEMBLE, [&] {
       cc::launch_assemble_list(mv, p.precision, M.estore, mat, M.hb, mv.tile ? M.g : nullptr, s, sl, ns);
       // a partial assembly leaves band records of unchanged blocks whose
@@ -1220,8 +1230,7 @@ struct Stepper {
   void sweep(const double* x, double* out, int method, int sweep_kind = -1) {
     const int nd = M.D * M.n;
     if ((sweep_kind < 0 ? p.sweep : sweep_kind) == CC_SWEEP_JACOBI) {
-      gradient_only(x);              // before the assembly, which may store it with its records
-      hessian(x);
+      hessian(x, -1, x);
       // the finish or update kernel writes the free entries x + d itself; the
       // Dirichlet ones are the same in both buffers
       bool done = false;
@@ -1240,10 +1249,8 @@ struct Stepper {
       if (v1 <= v0) continue;
       if (p.hess_refresh == CC_HESS_PER_COLOR) {
         // every Hessian at the sweep's start, then only what the previous
-        // colour's moves changed; the gradient first, which the assembly may
-        // store with its records
-        gradient_only(at);
-        hessian(out, moved);
+        // colour's moves changed
+        hessian(out, moved, at);
         moved = c;
         at = out;
         // a dense basis forms b_i from this gradient and moves the colour's
@@ -1257,7 +1264,7 @@ struct Stepper {
         continue;
       }
       if (c == 0) {
-        hessian(out);
+        hessian(out, -1, at);
         prep(method, 0, M.nf);
       }
       gradient_only(at);
@@ -1788,17 +1795,17 @@ cc_status cc_probe_sweep(cc_ctx* ctx, int32_t mesh_id, const double* x, const do
     S.mv.tile = cc::tile_usable(S.mv, p.precision, 0, 0);
     cc::launch_gather_user(S.mv, M.d_vinv, x, M.x, s);
     cc::launch_gather_user(S.mv, M.d_vinv, x_tilde, M.xt, s);
-    if (energy) *energy = S.energy(M.x);
-    S.gradient_only(M.x);
+    S.eval(M.x, energy != nullptr, true);
     if (g) cc::launch_scatter_user(S.mv, M.d_vperm, M.g, g, 1, s);
     if (dx) {
-      S.hessian(M.x);
+      S.hessian(M.x, -1, M.x);
       HIPC(hipMemsetAsync(M.fb, 0, 4 * sizeof(unsigned long long), s));
       if (!cc::launch_cc_prep(S.mv, p.precision, p.method, 0, M.nf, M.hb, M.KL, M.fb, s, M.g, M.dvec))
         cc::launch_cc_update(S.mv, p.precision, p.method, 0, M.nf, M.KL, M.g, M.dvec, 0, s);
       cc::launch_scatter_user(S.mv, M.d_vperm, M.dvec, dx, 1, s);
     }
-    HIPC(hipStreamSynchronize(s));
+    S.wait();
+    if (energy) *energy = S.out()[0];
     return CC_OK;
   });
 }

@@ -156,6 +156,12 @@ void launch_energy(const MeshView& mv, const double* x, const double* xt, const 
 // every free vertex j (nptr/nidx: mesh neighbours, Xr: rest positions, SoA).
 void launch_rotations(const MeshView& mv, const double* x, const int* nptr, const int* nidx,
                       const double* Xr, double* rot, hipStream_t s);
+// Rotations (rot given; nptr, nidx, Xr as in launch_rotations), element Hessians
+// scaled by mat.s_el (elist, ecount as in launch_elem_hess_list) and gradient (g
+// given) at x in one launch.
+void launch_point(const MeshView& mv, int prec, const double* x, const double* xt, const Material& mat, void* estore,
+                  const int* elist, int ecount, const int* nptr, const int* nidx, const double* Xr, double* rot,
+                  double* g, hipStream_t s);
 void launch_energy_grad(const MeshView& mv, const double* x, const double* xt, const Material& mat, double* g,
                         double* partials, int* ne, int* ng, hipStream_t s);
 // Sums [first, first + sums) of: 0, the first ne partials into out[0]; 1, the

@@ -2047,6 +2047,74 @@ void launch_rotations(const MeshView& mv, const double* x, const int* nptr, cons
   CC_DISPATCH_D(mv.D, k_rotations<D><<<nblocks(mv.nf, WG), WG, 0, s>>>(mv, x, nptr, nidx, Xr, rot));
 }
 
+// What a sweep needs at a point before its assembly, in one launch: vertex
+// rotations (rot given), element Hessians (of the list or all) and the gradient
+// (g given).  None reads another's result, and on a mesh or batch that does not
+// fill the chip each is one long chain of dependent loads and float64
+// arithmetic per thread (11 to 15 us), so side by side they take little more
+// than the longest.  Block b: rotations first, which take longest, with as few
+// threads per workgroup as the elements, then elements, then gradient.
+// Measured: directions of the corotated 29x9x7 bar 188 us one by one, 164 in one
+// launch; coloured step of sixteen uneven bars 13.69 and 11.48 ms.
+template <typename T, int D, bool FCR>
+__device__ __forceinline__ void point_body(const MeshView& mv, int b, const double* __restrict__ x,
+                                           const double* __restrict__ xt, const Material& mat, T* __restrict__ est,
+                                           const int* elist, int ecount, const int* __restrict__ nptr,
+                                           const int* __restrict__ nidx, const double* __restrict__ Xr,
+                                           double* __restrict__ rot, double* __restrict__ g) {
+  constexpr int TH = elem_threads<T>();
+  const int tid = threadIdx.x;
+  const int nr = rot != nullptr ? (mv.nf + TH - 1) / TH : 0, ne = (ecount + EWG - 1) / EWG;
+  if (b < nr) {
+    rotation_body<D>(mv, b * TH + tid, x, nptr, nidx, Xr, rot);
+  } else if (b < nr + ne) {
+    elem_hess_split<T, D>(mv, (b - nr) * EWG, x, T(mat.mu), T(mat.lam), FCR ? mat.model : MAT_SNH, T(mat.s_el), est,
+                          elist, ecount);
+  } else if (g != nullptr) {
+    (void)gradient_body<D, GRAD_G, FCR>(mv, grad_vertex(mv, (b - nr - ne) * (TH / GRAD_G) + tid / GRAD_G),
+                                        tid % GRAD_G, x, xt, mat, g);
+  }
+}
+
+// Workgroups of point_body for a mesh.
+template <typename T>
+static int point_blocks(const MeshView& mv, int ecount, bool rot, bool grad) {
+  constexpr int TH = elem_threads<T>();
+  return (rot ? nblocks(mv.nf, TH) : 0) + nblocks(ecount, EWG) + (grad ? nblocks(mv.nf, TH / GRAD_G) : 0);
+}
+
+template <typename T, int D, bool FCR>
+__global__ void __launch_bounds__(elem_threads<T>()) k_point(MeshView mv, const double* __restrict__ x,
+                                                             const double* __restrict__ xt, Material mat,
+                                                             T* __restrict__ est, const int* elist, int ecount,
+                                                             const int* __restrict__ nptr,
+                                                             const int* __restrict__ nidx,
+                                                             const double* __restrict__ Xr,
+                                                             double* __restrict__ rot, double* __restrict__ g) {
+  point_body<T, D, FCR>(mv, blockIdx.x, x, xt, mat, est, elist, ecount, nptr, nidx, Xr, rot, g);
+}
+
+template <typename T, int D, bool FCR>
+static void point(const MeshView& mv, const double* x, const double* xt, const Material& mat, void* est,
+                  const int* elist, int ecount, const int* nptr, const int* nidx, const double* Xr, double* rot,
+                  double* g, hipStream_t s) {
+  const int nb = point_blocks<T>(mv, ecount, rot != nullptr, g != nullptr);
+  if (nb > 0)
+    k_point<T, D, FCR><<<nb, elem_threads<T>(), 0, s>>>(mv, x, xt, mat, (T*)est, elist, ecount, nptr, nidx, Xr, rot,
+                                                       g);
+}
+
+void launch_point(const MeshView& mv, int prec, const double* x, const double* xt, const Material& mat, void* estore,
+                  const int* elist, int ecount, const int* nptr, const int* nidx, const double* Xr, double* rot,
+                  double* g, hipStream_t s) {
+  if (prec == 0)
+    CC_DISPATCH_MAT(mat.model == MAT_FCR, CC_DISPATCH_D(mv.D, point<double, D, FCR>(mv, x, xt, mat, estore, elist,
+                                                                                   ecount, nptr, nidx, Xr, rot, g, s)));
+  else
+    CC_DISPATCH_MAT(mat.model == MAT_FCR, CC_DISPATCH_D(mv.D, point<float, D, FCR>(mv, x, xt, mat, estore, elist,
+                                                                                  ecount, nptr, nidx, Xr, rot, g, s)));
+}
+
 void launch_energy_grad(const MeshView& mv, const double* x, const double* xt, const Material& mat, double* g,
                         double* partials, int* ne, int* ng, hipStream_t s) {
   const int nbe = nblocks(mv.m, WG);
@@ -2199,6 +2267,27 @@ __global__ void __launch_bounds__(elem_threads<T>()) kb_elem_hess(const BatchIte
   const int cnt = lst ? mv.cel_ptr[colour + 1] - mv.cel_ptr[colour] : mv.m;
   elem_hess_split<T, D>(mv, (bx - boff[mi]) * EWG, pick(it, which), T(it.mat.mu), T(it.mat.lam),
                         FCR ? it.mat.model : MAT_SNH, T(it.mat.s_el), (T*)it.estore, el, cnt);
+}
+
+// point_body of every mesh at positions `which` (grad: with the gradient).
+template <typename T, int D, bool FCR>
+__global__ void __launch_bounds__(elem_threads<T>()) kb_point(const BatchItem* __restrict__ items,
+                                                              const BatchCtl* __restrict__ ctl,
+                                                              const int* __restrict__ boff, int nmesh, int which,
+                                                              int colour, int grad) {
+  // blocks of one XCD take a contiguous range of the launch (one mesh, or
+  // neighbouring ones), so each mesh's data stays in one L2
+  const int bx = xcd_block(blockIdx.x, gridDim.x);
+  const int mi = block_mesh(boff, nmesh, bx);
+  if (!ctl[mi].active) return;
+  const BatchItem& it = items[mi];
+  const MeshView mv = it.mv;
+  // colour >= 0: only the elements that colour's moves changed
+  const bool lst = colour >= 0 && colour < it.ncol;
+  const int* el = lst ? mv.cel + mv.cel_ptr[colour] : nullptr;
+  const int cnt = lst ? mv.cel_ptr[colour + 1] - mv.cel_ptr[colour] : mv.m;
+  point_body<T, D, FCR>(mv, bx - boff[mi], pick(it, which), it.xt, it.mat, (T*)it.estore, el, cnt, it.nptr, it.nidx,
+                        it.Xr, const_cast<double*>(mv.rot), grad ? it.g : nullptr);
 }
 
 // Corotation: vertex rotations of every mesh at positions `which`.
@@ -2670,6 +2759,8 @@ struct BatchPlan {
   BatchCtl* ctl_d = nullptr;
   Offsets pred, elem, asmb, grad, energy, axpy, axpyj, feat, rotn;   // axpyj: Jacobi trial points
   Offsets eg;       // energy then gradient blocks of each mesh (kb_energy_grad)
+  Offsets point;    // rotations and elements of each mesh (kb_point)
+  std::vector<Offsets> pointg;   // with the gradient; index 0: all elements, c + 1: colour c's dirty ones
   std::vector<Offsets> elemc, asmbc;   // element / slot blocks of colour c's dirty lists
   std::vector<Offsets> prep, prepd, fin, upd;   // index 0: all free vertices, c+1: colour c
   std::vector<int> nseg;      // segments of the dense condensation's rows (prep_segments), indexed as prepd
@@ -2873,6 +2964,19 @@ BatchPlan* batch_plan_create(const BatchItem* items_host, int nmesh, const Batch
   offsets_build(p->axpyj, caxj, s);
   offsets_build(p->feat, cfeat, s);
   offsets_build(p->rotn, crot, s);
+  // c = -2: without the gradient, -1: with it, all elements
+  for (int c = -2; c < (cfg.sweep == 1 ? p->max_colours : -1); ++c) {
+    std::vector<int> cp(nmesh);
+    for (int m = 0; m < nmesh; ++m) {
+      const BatchItem& it = p->items_h[m];
+      if (c >= it.ncol && c >= 0) continue;           // the mesh has no such colour
+      const int cnt = c >= 0 ? it.cel_n[c] : it.mv.m;
+      cp[m] = cfg.prec == 0 ? point_blocks<double>(it.mv, cnt, crot[m] > 0, c > -2)
+                            : point_blocks<float>(it.mv, cnt, crot[m] > 0, c > -2);
+    }
+    if (c > -2) p->pointg.emplace_back();
+    offsets_build(c == -2 ? p->point : p->pointg.back(), cp, s);
+  }
   p->dorder_h.resize(nmesh);
   for (int m = 0; m < nmesh; ++m) p->dorder_h[m] = m;
   std::stable_sort(p->dorder_h.begin(), p->dorder_h.end(),
@@ -2891,8 +2995,9 @@ void batch_plan_destroy(BatchPlan* p) {
   if (!p) return;
   drop_graph(p);
   for (Offsets* o : {&p->pred, &p->elem, &p->asmb, &p->grad, &p->energy, &p->eg, &p->axpy, &p->axpyj, &p->feat,
-                     &p->rotn})
+                     &p->rotn, &p->point})
     offsets_free(*o);
+  for (auto& o : p->pointg) offsets_free(o);
   for (auto& o : p->prep) offsets_free(o);
   for (auto& o : p->prepd) offsets_free(o);
   for (auto& o : p->fin) offsets_free(o);
@@ -2934,6 +3039,16 @@ static void b_energy(BatchPlan* p, int which, int dst, hipStream_t s, int post =
                                     p->cfg.max_iters, 0);
 }
 
+// The gradient at positions `which`, without its norm.
+template <int D>
+static void b_gradient_only(BatchPlan* p, int which, hipStream_t s) {
+  if (gridn(p->grad) == 0) return;
+  p->mark(2, 1);
+  CC_DISPATCH_MAT(p->cfg.any_fcr, kb_gradient<D, GRAD_G, FCR><<<gridn(p->grad), WG, 0, s>>>(
+                                      p->items_d, p->ctl_d, p->grad.d, p->nmesh, which, 0));
+  p->mark(2, 0);
+}
+
 template <typename T, int D, int G>
 static void b_prep(BatchPlan* p, int colour, hipStream_t s, int fuse = 0) {
   const Offsets& o = p->prep[colour + 1];
@@ -2970,19 +3085,30 @@ static void b_update(BatchPlan* p, int colour, int into_trial, hipStream_t s) {
   p->mark(4, 0);
 }
 
-// Element Hessians and block rows at positions `which`: of every element
-// (colour < 0), or only those that colour's moves changed.
+// Element Hessians and block rows at positions `which`, with the rotations of
+// corotated meshes and (grad) the gradient at the same positions: of every
+// element (colour < 0), or only those that colour's moves changed.  The
+// kernels are launched one by one where they are timed one by one, and where
+// only element Hessians are wanted.
 template <typename T, int D>
-static void b_hessian(BatchPlan* p, int which, hipStream_t s, int colour = -1) {
-  if (gridn(p->rotn) > 0)   // corotation: rotations at the positions of the Hessian
-    kb_rotations<D><<<gridn(p->rotn), WG, 0, s>>>(p->items_d, p->ctl_d, p->rotn.d, p->nmesh, which);
+static void b_hessian(BatchPlan* p, int which, hipStream_t s, int colour = -1, bool grad = false) {
+  const bool rot = gridn(p->rotn) > 0;
   const Offsets& oe = colour < 0 ? p->elem : p->elemc[colour];
   const Offsets& oa = colour < 0 ? p->asmb : p->asmbc[colour];
-  if (gridn(oe) > 0) {
-    p->mark(0, 1);
-    CC_DISPATCH_MAT(p->cfg.any_fcr, kb_elem_hess<T, D, FCR><<<gridn(oe), elem_threads<T>(), 0, s>>>(
-                                        p->items_d, p->ctl_d, oe.d, p->nmesh, which, colour));
-    p->mark(0, 0);
+  if (p->hook == nullptr && (rot || grad)) {
+    const Offsets& o = grad ? p->pointg[colour + 1] : p->point;
+    if (gridn(o) > 0)
+      CC_DISPATCH_MAT(p->cfg.any_fcr, kb_point<T, D, FCR><<<gridn(o), elem_threads<T>(), 0, s>>>(
+                                          p->items_d, p->ctl_d, o.d, p->nmesh, which, colour, grad));
+  } else {
+    if (grad) b_gradient_only<D>(p, which, s);
+    if (rot) kb_rotations<D><<<gridn(p->rotn), WG, 0, s>>>(p->items_d, p->ctl_d, p->rotn.d, p->nmesh, which);
+    if (gridn(oe) > 0) {
+      p->mark(0, 1);
+      CC_DISPATCH_MAT(p->cfg.any_fcr, kb_elem_hess<T, D, FCR><<<gridn(oe), elem_threads<T>(), 0, s>>>(
+                                          p->items_d, p->ctl_d, oe.d, p->nmesh, which, colour));
+      p->mark(0, 0);
+    }
   }
   if (gridn(oa) > 0) {
     p->mark(1, 1);
@@ -3017,18 +3143,14 @@ static void b_iteration(BatchPlan* p, hipStream_t s) {
         b_hessian<T, D>(p, 1, s);
         b_prep<T, D, G>(p, -1, s);
       }
-      if (gridn(p->grad) > 0) {
-        p->mark(2, 1);
-        CC_DISPATCH_MAT(c.any_fcr, kb_gradient<D, GRAD_G, FCR><<<gridn(p->grad), WG, 0, s>>>(
-                                       p->items_d, p->ctl_d, p->grad.d, nm, 1, 0));
-        p->mark(2, 0);
-      }
       // dense meshes form b_i from the fresh gradient (which the assembly
       // stores with tile records) and move the colour's vertices in the finish
       // kernel; sparse ones take the update kernel
       if (c.hess_refresh == 0) {
-        b_hessian<T, D>(p, 1, s, col == 0 ? -1 : col - 1);
+        b_hessian<T, D>(p, 1, s, col == 0 ? -1 : col - 1, true);
         b_prep<T, D, G>(p, col, s, 2);
+      } else {
+        b_gradient_only<D>(p, 1, s);
       }
       b_update<T, D, G>(p, col, 1, s);
     }
