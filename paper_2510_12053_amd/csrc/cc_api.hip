@@ -1205,13 +1205,13 @@ struct Stepper {
         cc::launch_elem_hess_list(mv, p.precision, x, mat, mat.s_el, M.estore, s, el, ne);
       });
     }
-    const int* sl = colour < 0 ? nullptr : mv.csl + M.csl_ptr_h[colour];
-    const int ns = colour < 0 ? M.nnzb : M.csl_ptr_h[colour + 1] - M.csl_ptr_h[colour];
+    // band records carry both vertices' rotations, which change everywhere: with
+    // them a colour's assembly takes every block too
+    const bool part = colour >= 0 && !(mv.rot != nullptr && mv.hq != nullptr);
+    const int* sl = part ? mv.csl + M.csl_ptr_h[colour] : nullptr;
+    const int ns = part ? M.csl_ptr_h[colour + 1] - M.csl_ptr_h[colour] : M.nnzb;
     ctx->timed(CC_K_ASSEMBLE, [&] {
       cc::launch_assemble_list(mv, p.precision, M.estore, mat, M.hb, mv.tile ? M.g : nullptr, s, sl, ns);
-      // a partial assembly leaves band records of unchanged blocks whose
-      // rotations did change
-      if (colour >= 0 && mv.rot != nullptr) cc::launch_band_copy(mv, p.precision, M.hb, mv.tile ? M.g : nullptr, s);
     });
   }
   void prep(int method, int v0, int v1) {

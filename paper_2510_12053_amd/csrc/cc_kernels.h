@@ -32,7 +32,7 @@ struct MeshView {
   // (when k comes later).  Row p's blocks (j, k) with bpos[k] >= bpos[j]
   // ("upper" blocks, the diagonal first) number bq_cnt[p] <= qmax.  When hq
   // is set (dense bases), hq[q * nf + p] is the BandRec (precision of hb) of
-  // the q-th of them, written by the assembly and band-copy kernels:
+  // the q-th of them, written by the assembly kernels:
   // hq_slot[t] = q * nf + p for an upper slot t of hb, -1 otherwise.
   const int* bvert;
   const int* bpos;
@@ -131,10 +131,6 @@ void launch_elem_hess_list(const MeshView& mv, int prec, const double* x, const 
                            double scale, void* estore, hipStream_t s, const int* elist, int count);
 void launch_assemble_list(const MeshView& mv, int prec, const void* estore, const Material& mat, void* hb,
                           const double* g, hipStream_t s, const int* slist, int count);
-// Rewrites every BandRec of a dense-basis mesh (hq set) from the block rows
-// hb and the current rotations: after a partial assembly whose rotations
-// changed everywhere (a coloured sweep of a corotated mesh).
-void launch_band_copy(const MeshView& mv, int prec, const void* hb, const double* g, hipStream_t s);
 void launch_gradient(const MeshView& mv, const double* x, const double* xt, const Material& mat,
                      double* g, double* partials, int* nparts, hipStream_t s);
 // Condensation of vertices [v0, v1).  With g and dout given (g the gradient

@@ -278,12 +278,6 @@ __device__ __forceinline__ void assemble_body(const MeshView& mv, int tt, const 
 }
 
 template <typename T, int D>
-__global__ void __launch_bounds__(EWG) k_band_copy(MeshView mv, const T* __restrict__ hb, const double* g) {
-  const int t = blockIdx.x * EWG + threadIdx.x;
-  if (t < mv.nnzb) band_rec_write<T, D>(mv, t, mv.blkrow[t], hb + (size_t)t * D * D, g);
-}
-
-template <typename T, int D>
 __global__ void __launch_bounds__(EWG) k_assemble(MeshView mv, const T* __restrict__ est, T w_in,
                                                   T* __restrict__ hb, const double* g, const int* slist,
                                                   int scount) {
@@ -1700,13 +1694,6 @@ void launch_assemble(const MeshView& mv, int prec, const void* estore, const Mat
   launch_assemble_list(mv, prec, estore, mat, hb, g, s, nullptr, mv.nnzb);
 }
 
-void launch_band_copy(const MeshView& mv, int prec, const void* hb, const double* g, hipStream_t s) {
-  if (mv.hq == nullptr || mv.nnzb <= 0) return;
-  const int nb = nblocks(mv.nnzb, EWG);
-  if (prec == 0) CC_DISPATCH_D(mv.D, k_band_copy<double, D><<<nb, EWG, 0, s>>>(mv, (const double*)hb, g));
-  else CC_DISPATCH_D(mv.D, k_band_copy<float, D><<<nb, EWG, 0, s>>>(mv, (const float*)hb, g));
-}
-
 void launch_assemble_list(const MeshView& mv, int prec, const void* estore, const Material& mat, void* hb,
                           const double* g, hipStream_t s, const int* slist, int count) {
   if (count <= 0) return;
@@ -2322,24 +2309,6 @@ __global__ void __launch_bounds__(EWG) kb_assemble(const BatchItem* __restrict__
   const int cnt = lst ? mv.csl_ptr[colour + 1] - mv.csl_ptr[colour] : mv.nnzb;
   assemble_body<T, D>(mv, (bx - boff[mi]) * EWG + threadIdx.x, (const T*)it.estore,
                       T(it.mat.w_in), (T*)it.hb, mv.tile ? it.g : nullptr, sl, cnt);
-}
-
-// Every BandRec of the dense-basis meshes from their block rows and current
-// rotations (after a partial assembly of corotated meshes).
-template <typename T, int D>
-__global__ void __launch_bounds__(EWG) kb_band_copy(const BatchItem* __restrict__ items,
-                                                   const BatchCtl* __restrict__ ctl,
-                                                   const int* __restrict__ boff, int nmesh) {
-  // blocks of one XCD take a contiguous range of the launch (one mesh, or
-  // neighbouring ones), so each mesh's data stays in one L2
-  const int bx = xcd_block(blockIdx.x, gridDim.x);
-  const int mi = block_mesh(boff, nmesh, bx);
-  if (!ctl[mi].active) return;
-  const BatchItem& it = items[mi];
-  const MeshView& mv = it.mv;
-  if (mv.hq == nullptr) return;
-  const int t = (bx - boff[mi]) * EWG + threadIdx.x;
-  if (t < mv.nnzb) band_rec_write<T, D>(mv, t, mv.blkrow[t], (const T*)it.hb + (size_t)t * D * D, mv.tile ? it.g : nullptr);
 }
 
 template <int D, int G, bool FCR>
@@ -3093,8 +3062,12 @@ static void b_update(BatchPlan* p, int colour, int into_trial, hipStream_t s) {
 template <typename T, int D>
 static void b_hessian(BatchPlan* p, int which, hipStream_t s, int colour = -1, bool grad = false) {
   const bool rot = gridn(p->rotn) > 0;
+  // band records carry both vertices' rotations, which change everywhere:
+  // with them a colour's assembly takes every block too (sixteen uneven bars:
+  // 21 us, against 18 for the changed blocks and 7 for the other records)
+  const int ac = rot && (p->tv > 0 || p->tile > 0) ? -1 : colour;
   const Offsets& oe = colour < 0 ? p->elem : p->elemc[colour];
-  const Offsets& oa = colour < 0 ? p->asmb : p->asmbc[colour];
+  const Offsets& oa = ac < 0 ? p->asmb : p->asmbc[ac];
   if (p->hook == nullptr && (rot || grad)) {
     const Offsets& o = grad ? p->pointg[colour + 1] : p->point;
     if (gridn(o) > 0)
@@ -3112,11 +3085,7 @@ static void b_hessian(BatchPlan* p, int which, hipStream_t s, int colour = -1, b
   }
   if (gridn(oa) > 0) {
     p->mark(1, 1);
-    kb_assemble<T, D><<<gridn(oa), EWG, 0, s>>>(p->items_d, p->ctl_d, oa.d, p->nmesh, colour);
-    // the band records of blocks the partial assembly left alone still
-    // carry the previous rotations
-    if (colour >= 0 && gridn(p->rotn) > 0 && (p->tv > 0 || p->tile > 0))
-      kb_band_copy<T, D><<<gridn(p->asmb), EWG, 0, s>>>(p->items_d, p->ctl_d, p->asmb.d, p->nmesh);
+    kb_assemble<T, D><<<gridn(oa), EWG, 0, s>>>(p->items_d, p->ctl_d, oa.d, p->nmesh, ac);
     p->mark(1, 0);
   }
 }
