@@ -51,6 +51,7 @@ FP32_PEAK_TFLOPS = 157.3          # published vector peak: counts packed FP32 (t
 # issues at most one FMA per lane per clock: 256 CUs x 64 lanes x 2 flops x
 # 2.4 GHz, the same figure as the FP64 vector peak
 FP32_SCALAR_PEAK_TFLOPS = 78.6
+FP32_MATRIX_PEAK_TFLOPS = 157.3   # published float32 matrix peak: the condensation's, unless a row count is forced
 TOL = 1e-6
 MAX_ITERS = 10000          # per step; the headline Jacobi solves never come near it
 GS_MAX_ITERS = 200
@@ -285,8 +286,11 @@ def summary(rec, elapsed, steps, nmesh, per_mesh_time):
     return out
 
 
-def roofline(wl, rec, kern, S, peak_f):
-    """Dominant kernel class of the profiled launches against HBM and VALU."""
+def roofline(wl, rec, kern, S, peak_f, dense_rows):
+    """Dominant kernel class of the profiled launches against HBM and the
+    arithmetic peak of the unit that does its products.  dense_rows: the
+    tuning's rows per workgroup of the condensation (0: matrix cores in
+    float32)."""
     models = [kernel_model(s, S) for s in wl.scenes]
     its_mesh = [0] * len(wl.scenes)
     for k, r in enumerate(rec):
@@ -297,6 +301,9 @@ def roofline(wl, rec, kern, S, peak_f):
     alg = sum(i * m[0][dom] for i, m in zip(its_mesh, models))
     fl = sum(i * m[1][dom] for i, m in zip(its_mesh, models))
     gbs, tfl = alg / secs / 1e9, fl / secs / 1e12
+    tile = S == 4 and dense_rows == 0
+    if tile and dom == "cc_prep":
+        peak_f = FP32_MATRIX_PEAK_TFLOPS
     hbm = {"achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(gbs / HBM_PEAK_GBS, 4)}
     alu = {"achieved": round(tfl, 3), "peak": peak_f, "unit": "TFLOP/s", "frac": round(tfl / peak_f, 4)}
     if peak_f == FP32_SCALAR_PEAK_TFLOPS and S == 4:
@@ -305,7 +312,8 @@ def roofline(wl, rec, kern, S, peak_f):
     bound = "alu" if alu["frac"] >= hbm["frac"] else "hbm"
     roof = dict(alu if bound == "alu" else hbm)
     roof = {"bound": bound, **roof}
-    roof.update({"kernel": "kb_prep_band+kb_dm_finish" if dom == "cc_prep" else "kb_" + dom,
+    prep = "kb_prep_tile" if tile else "kb_prep_band"
+    roof.update({"kernel": prep + "+kb_dm_finish" if dom == "cc_prep" else "kb_" + dom,
                  "avg_launch_us": round(ms_tot / max(launches, 1) * 1e3, 2), "launches": launches,
                  "algorithmic_bytes_per_launch": round(alg / max(launches, 1)),
                  "flops_per_launch": round(fl / max(launches, 1)),
@@ -422,8 +430,8 @@ def main():
     plain = summary(rec_p, el_p, args.steps, nb, True)
     batched = summary(rec_b, el_b, args.steps, nb, False)
     learned = summary(rec_l, el_l, args.steps, nb, False)
-    roof, kernel_roofline, dom = roofline(wl, rec_k, kern_k, S, peak_f)
-    tr = measured_traffic(f"traffic_kb_prep_band_batch64_{args.precision}.md") if dom == "cc_prep" else None
+    roof, kernel_roofline, dom = roofline(wl, rec_k, kern_k, S, peak_f, tuning["dense_rows"])
+    tr = measured_traffic(f"traffic_kb_prep_tile_batch64_{args.precision}.md") if dom == "cc_prep" else None
     # counter bytes per bar-iteration times the bar-iterations of a mean launch
     if tr is not None:
         per_it = (tr["fetch_bytes_per_launch"] + tr["write_bytes_per_launch"]) / tr["mesh_iters_per_launch"]
@@ -486,7 +494,7 @@ def main():
             res[name] = summary(rec, el, nsteps, 1, False)
             res[name]["iters_per_step"] = [r[1] for r in rec]
         rec, _, kern = timed(cg, ctx, bw, bw.run_batch, 0, min(nsteps, 2), profile=True)
-        broof, bcls, _ = roofline(bw, rec, kern, 4, FP32_SCALAR_PEAK_TFLOPS)
+        broof, bcls, _ = roofline(bw, rec, kern, 4, FP32_SCALAR_PEAK_TFLOPS, tuning["dense_rows"])
         res["roofline"] = broof
         res["kernel_roofline"] = bcls
         out["beam81x21x21_twist"] = res

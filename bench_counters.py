@@ -7,11 +7,11 @@ per step, so that every launch of the iteration covers the whole workload,
 then copies a buffer of known size (the calibration kernel):
   batch64  the 64 seed-drawn bars of the benchmark with their exact bases,
            corotated, float32 local arithmetic (kernel of record:
-           kb_prep_band);
+           kb_prep_tile, or kb_prep_band with --dense-rows);
   beam     the 81x21x21 twisted beam with its exact, corotated basis,
            float32 local arithmetic.
 --dense-rows sets the rows per workgroup of the condensation (the
-autotuner's choice in bench.py; 0: the most that fit).
+autotuner's choice in bench.py; 0: the matrix-core condensation).
 
 Summarize mode: reads the counter CSVs of a FETCH_SIZE run and a WRITE_SIZE
 run, scales each counter by the ratio of known to counted bytes of the copy
@@ -27,8 +27,8 @@ kernel (that factor comes from 128-byte requests, which FETCH_SIZE counts as
     cd /tmp && export TMPDIR=/tmp          # R: repository root, OUT: an output folder
     timeout -s KILL 240 rocprofv3 --pmc FETCH_SIZE --output-format csv -d $OUT/ctr_fetch -o run -- python -u $R/bench_counters.py
     timeout -s KILL 240 rocprofv3 --pmc WRITE_SIZE --output-format csv -d $OUT/ctr_write -o run -- python -u $R/bench_counters.py
-    python $R/bench_counters.py --summarize $OUT/ctr_fetch $OUT/ctr_write > $R/profiles/traffic_kb_prep_band_batch64_fp32.md
-    # the same three commands with `--workload beam` -> traffic_kb_prep_band_beam81x21x21_fp32.md
+    python $R/bench_counters.py --summarize $OUT/ctr_fetch $OUT/ctr_write > $R/profiles/traffic_kb_prep_tile_batch64_fp32.md
+    # the same three commands with `--workload beam` -> traffic_kb_prep_tile_beam81x21x21_fp32.md
 
 Trace-summary mode: Markdown table of a `rocprofv3 --kernel-trace --stats`
 run of bench.py, with the condensation kernels' average over the dispatches
@@ -49,8 +49,9 @@ sys.path.insert(0, ROOT)
 COPY_BYTES = 512 * 1024 * 1024      # calibration copy: read and written once each
 COPY_REPS = 4
 # counter kernel name fragment -> bench.kernel_model class
-KERNELS = {"kb_prep_band<": "cc_prep", "kb_dm_finish<": "cc_prep", "kb_elem_hess<": "elem_hess",
-           "kb_assemble<": "assemble", "kb_gradient<": "gradient", "kb_energy_grad<": "energy_grad"}
+KERNELS = {"kb_prep_tile<": "cc_prep", "kb_prep_band<": "cc_prep", "kb_dm_finish<": "cc_prep", "kb_elem_hess<": "elem_hess",
+           "kb_point<": "elem_hess", "kb_assemble<": "assemble", "kb_gradient<": "gradient", "kb_energy_grad<": "energy_grad"}
+PREPS = ("kb_prep_tile<", "kb_prep_band<")      # the condensation, by the kernel a run took
 SOURCE = os.path.join(ROOT, "paper_2510_12053_amd", "csrc", "cc_kernels.hip")
 
 
@@ -229,16 +230,18 @@ def summarize(fetch_dir, write_dir, workload, req_dir=None):
     if rq is not None and "copy" in rq:
         line += f" {rq['copy'][0] / 1e6:.1f} ({rq['copy'][1]:.3f}) | |"
     print(line)
-    pf, pw = rows["kb_prep_band<"]
+    prep = next(k for k in PREPS if k in rows)
+    pname = prep.rstrip("<")
+    pf, pw = rows[prep]
     ff, fw = rows.get("kb_dm_finish<", (0.0, 0.0))
     fetch, write = pf + ff, pw + fw
-    print(f"\nCondensation (kb_prep_band + kb_dm_finish): fetch {fetch / 1e6:.1f} MB, write {write / 1e6:.2f} MB "
+    print(f"\nCondensation ({pname} + kb_dm_finish): fetch {fetch / 1e6:.1f} MB, write {write / 1e6:.2f} MB "
           f"per launch, against {alg['cc_prep'] / 1e6:.1f} MB algorithmic ({(fetch + write) / alg['cc_prep']:.3f}x).\n")
-    rec = {"kernel": "kb_prep_band+kb_dm_finish", "workload": tag, "precision": "fp32",
+    rec = {"kernel": f"{pname}+kb_dm_finish", "workload": tag, "precision": "fp32",
            "mesh_iters_per_launch": len(scenes_of(workload)), "fetch_bytes_per_launch": round(fetch),
            "write_bytes_per_launch": round(write), "algorithmic_bytes_per_launch": round(alg["cc_prep"]),
            "fetch_scale": round(sf, 4), "write_scale": round(sw, 4),
-           "dispatches": len(fe["kb_prep_band<"]), "source_sha256_16": source_hash()}
+           "dispatches": len(fe[prep]), "source_sha256_16": source_hash()}
     print("traffic_json: " + json.dumps(rec))
 
 
@@ -274,10 +277,12 @@ def trace_summary(folder, bench_log):
     def window(key):
         return [(int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3
                 for r in disp if key in r["Kernel_Name"] and t0 < int(r["Start_Timestamp"]) < t1]
-    lp, lf = window("kb_prep_band<float"), window("kb_dm_finish<float")
+    tile = window("kb_prep_tile<")
+    lp, lf = tile or window("kb_prep_band<float"), window("kb_dm_finish<float")
+    pname = "kb_prep_tile" if tile else "kb_prep_band"
     mp = sum(lp) / max(len(lp), 1)
     mf = sum(lf) / max(len(lf), 1)
-    print(f"\nDominant kernels of the timed path: `kb_prep_band` + `kb_dm_finish` (exact-basis "
+    print(f"\nDominant kernels of the timed path: `{pname}` + `kb_dm_finish` (exact-basis "
           f"condensation).  The {len(lp)} dispatches of the uncaptured learned+batched region average "
           f"{mp:.1f} + {mf:.1f} = {mp + mf:.1f} us per pair; bench.py's HIP-event average of the "
           f"same launches in this run: {ro['avg_launch_us']} us.\n")
@@ -319,7 +324,7 @@ def counters_summary(dirs, workload):
         if not files:
             continue
         for row in csv.DictReader(open(files[0])):
-            if "kb_prep_band<" not in row["Kernel_Name"]:
+            if not any(k in row["Kernel_Name"] for k in PREPS):
                 continue
             c = row["Counter_Name"]
             tot[c] = tot.get(c, 0.0) + float(row["Counter_Value"])
@@ -328,7 +333,7 @@ def counters_summary(dirs, workload):
     name = {"batch64": "the 64 seed-drawn bars of the benchmark, exact corotated bases",
             "beam": "the 81x21x21 twisted beam, exact corotated basis"}[workload]
     flag = "" if workload == "batch64" else " --workload beam"
-    print(f"# Shader and cache counters of kb_prep_band: {name}, float32 local arithmetic\n")
+    print(f"# Shader and cache counters of the exact-basis condensation: {name}, float32 local arithmetic\n")
     print("Commands (repo root `$R`, output folder `$OUT`, one MI355X; one pass per counter group):\n")
     print("```")
     print("cd /tmp && export TMPDIR=/tmp")
