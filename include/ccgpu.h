@@ -244,9 +244,10 @@ cc_status cc_step_batch(cc_ctx* ctx, int32_t n, const int32_t* mesh_ids, double*
    (ms_out: 3 values for 16, 32, 64; may be NULL). */
 cc_status cc_batch_tuning(cc_ctx* ctx, int32_t lanes, int32_t iters_per_graph);
 /* Rows per workgroup of the exact-basis condensation (every basis row it
-   stages serves that many vertices per H block it loads): 0 = the most whose
-   LDS ring fits (4 in float32, 2 in float64 on MI355X), or a cap of 1 to
-   4; and its chunk of band positions per pass, which is also its workgroup
+   stages serves that many vertices per H block it loads): 0 = automatic (the
+   matrix-core kernel for float32 3D meshes when the chunk is 0 too, else the
+   most rows whose LDS ring fits, 4 in float32 and 2 in float64 on MI355X), or
+   a cap of 1 to 4; and its chunk of band positions per pass, which is also its workgroup
    size: 0 = the one that leaves more waves resident per CU, or 128 / 256 /
    512.
    A forced chunk whose ring does not fit sends the mesh to the sparse-row
@@ -364,7 +365,8 @@ cc_status cc_mlp_train_step(cc_ctx* ctx, const float* X, const float* T, const i
 /* Record the duration of every launch of the kernels whose bit is set in
    `mask` (bit k = kernel id k) with HIP events on the context's stream;
    mask = 0 stops recording.  Enabling clears the accumulators.  Timing adds
-   two event records per timed launch.  Enabling, and stopping a recording,
+   two event records per timed launch, and the element Hessians, rotations and
+   gradient of a sweep, which otherwise share launches, run one by one.  Enabling, and stopping a recording,
    also launch an empty kernel `k_profile_mark` on the context's stream, the
    region's boundary in a kernel trace. */
 cc_status cc_profile_enable(cc_ctx* ctx, int32_t mask);
