@@ -122,8 +122,6 @@ struct ApiError {
 // Exact bases keep a float64 copy (for CC_FP64 steps) while it takes at most
 // this many bytes; larger ones are stored in float32 only.
 constexpr size_t DENSE_F64_MAX_BYTES = size_t(4) << 30;
-// Floats past a float32 dense basis: the look-ahead of the last row's copy ends there.
-constexpr size_t DENSE_F32_PAD = 4096;
 // Unknowns per level of the block-tridiagonal exact-basis build.
 constexpr int LEVEL_DOFS = 768;
 
@@ -908,7 +906,7 @@ void upload_basis(cc_ctx* ctx, Mesh& M, const int64_t* ptr, const int32_t* idx, 
         std::memcpy(&band[((size_t)i * nf + M.bpos_h[sidx[q]]) * DD], &Ud[(size_t)q * DD], DD * sizeof(double));
     if (blocks * DD * sizeof(double) <= DENSE_F64_MAX_BYTES) M.U_d = dupload(band, s);
     std::vector<float> Uf(band.begin(), band.end());
-    Uf.resize(Uf.size() + DENSE_F32_PAD, 0.f);
+    Uf.resize(Uf.size() + cc::DENSE_F32_PAD, 0.f);
     M.U_f = dupload(Uf, s);
     M.dense = 1;
   } else {
@@ -993,8 +991,8 @@ void build_basis(cc_ctx* ctx, Mesh& M, int radius, double dt, int quasi, const d
     double* Ud = nullptr;
     float* Uf = nullptr;
     try {
-      Uf = dalloc<float>(blocks * DD + DENSE_F32_PAD);
-      HIPC(hipMemsetAsync(Uf + blocks * DD, 0, DENSE_F32_PAD * sizeof(float), s));
+      Uf = dalloc<float>(blocks * DD + cc::DENSE_F32_PAD);
+      HIPC(hipMemsetAsync(Uf + blocks * DD, 0, cc::DENSE_F32_PAD * sizeof(float), s));
       if (blocks * DD * sizeof(double) <= DENSE_F64_MAX_BYTES) Ud = dalloc<double>(blocks * DD);
     } catch (...) {
       dfree(Ud); dfree(Uf);

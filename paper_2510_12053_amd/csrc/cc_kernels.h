@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "cc_tile.h"
+
 namespace cc {
 
 // Device view of one mesh in the internal (colour-sorted) order.
@@ -233,30 +235,6 @@ DenseCfg dense_config(const int* nf, const int* band_w, int count, int D, int pr
                       int chunk = 0);
 
 // ---- matrix-core condensation of float32 3D dense bases (prep_tile_body) ----
-// Segments that the dense condensation splits a row's band into where a launch
-// is short of workgroups.
-constexpr int SEG_MAX = 2;
-constexpr int TILE_Q = 8;                    // upper blocks per band row it handles
-// Configurations (index + 1; 0: none): 1, ten vertices per workgroup of eight
-// waves, chunks of 64 band positions, for band widths up to TILE_RING - 64;
-// 2, five vertices per workgroup of sixteen waves, chunks of 256; 3, five
-// vertices per workgroup of eight waves, chunks of 128.
-constexpr int TILE_N = 3;
-constexpr int TILE_G[TILE_N] = {2, 1, 1};            // groups of five vertices
-constexpr int TILE_CH[TILE_N] = {64, 256, 128};      // chunks of band positions
-constexpr int TILE_WAVES[TILE_N] = {8, 16, 8};
-constexpr int TILE_RING = 192;               // ring of the first configuration
-constexpr int TILE_PAD = 1024;               // zero band rows after the last one (look-ahead reads)
-// LDS ring length (positions, a multiple of the chunk, so that no refill
-// wraps), nine words each; the vertices' rings are tile_stride words apart:
-// 3 mod 16, so that the 15 columns a row of 16 lanes reads fall into 15
-// consecutive banks (mod 16).
-__host__ __device__ inline int tile_ring(int cfg, int nf, int band_w) {
-  if (cfg == 1) return TILE_RING;
-  const int ch = TILE_CH[cfg - 1], need = nf < ch + band_w ? nf : ch + band_w;
-  return (need + ch - 1) / ch * ch;
-}
-__host__ __device__ inline constexpr int tile_stride(int ring) { return ring * 9 + 3; }
 int tile_config(const int* nf, const int* band_w, const int* rows, int count);
 size_t tile_lds_bytes(int cfg, int nf, int band_w);
 // Whether a mesh's dense condensation in precision prec takes it (the caller

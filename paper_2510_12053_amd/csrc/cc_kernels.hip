@@ -1056,13 +1056,15 @@ __device__ __forceinline__ void prep_tile_body(const MeshView& mv, int i0, int n
   const int R = CFG == 0 ? TILE_RING : tile_ring(CFG + 1, nf, mv.band_w), VS = tile_stride(R);
   // band rows [pa, pb): the segment's share of the row in whole rings, so that
   // position p keeps its slot p mod R
-  const int rings = (nf + R - 1) / R, pa = rings * seg / nseg * R, pb = min(nf, rings * (seg + 1) / nseg * R);
+  const int pa = tile_segment(nf, R, seg, nseg), pb = min(nf, tile_segment(nf, R, seg + 1, nseg));
   const int tid = threadIdx.x, l = tid % 64, w = __builtin_amdgcn_readfirstlane(tid / 64);
   // A vertex's row is copied into its ring in pieces of 64 words, one word per
-  // lane.  What a piece reads past the row's end (the next row, or the padding
-  // past the last) is never used.
+  // lane.  What a piece reads past the row's end (the next row, or the
+  // DENSE_F32_PAD words past the last) is never used.  The descriptor does not
+  // check it: a piece's place is a scalar offset, which is not part of the check.
+  static_assert(TILE_PIECE == 64, "one word per lane");
   constexpr int UC = CH * 9 / 64, NP = (V * UC + NS - 1) / NS;   // pieces of a chunk per vertex, per wave
-  const __amdgpu_buffer_rsrc_t urs = buf_rsrc(mv.U_f + (size_t)i0 * nf9, (uint32_t)(nv * nf9 + 4096) * 4u);
+  const __amdgpu_buffer_rsrc_t urs = buf_rsrc(mv.U_f + (size_t)i0 * nf9, (uint32_t)(nv * nf9 + DENSE_F32_PAD) * 4u);
   const uint32_t gl4 = (uint32_t)l * 4u;
   uint32_t wl4 = (uint32_t)(uintptr_t)(lds_float*)smem + gl4;
   asm volatile("" : "+v"(wl4));
@@ -1072,14 +1074,14 @@ __device__ __forceinline__ void prep_tile_body(const MeshView& mv, int i0, int n
   };
   auto row4 = [&](int v) { return (uint32_t)((v < nv ? v : 0) * nf9) * 4u; };
   auto ring4 = [&](int v) { return (uint32_t)(v * VS) * 4u; };
-  const int UF = R * 9 / 64, fill = V * UF;          // first fill: positions [pa, pa + R)
+  const int UF = R * 9 / 64, fill = V * UF;          // first fill: positions [pa, min(pa + R, nf))
   constexpr int FB = 17;                             // pieces in flight per wave
   uint32_t first[FB];
   auto fill_load = [&](int x0) {
 #pragma unroll
     for (int e = 0; e < FB; ++e) {
       const int k = min(x0 + e * NS, fill - 1);
-      first[e] = load_piece(row4(k / UF) + (uint32_t)(k % UF) * 256u + (uint32_t)pa * 36u);
+      first[e] = load_piece(row4(k / UF) + tile_fill_piece(pa, k % UF, nf) * 4u);
     }
   };
   fill_load(w);
@@ -1097,7 +1099,7 @@ __device__ __forceinline__ void prep_tile_body(const MeshView& mv, int i0, int n
 #pragma unroll
   for (int e = 0; e < NP; ++e) {
     const int x = min(w + e * NS, V * UC - 1);
-    gat[e] = row4(x / UC) + (uint32_t)(x % UC) * 256u;
+    gat[e] = row4(x / UC) + tile_piece(0, x % UC) * 4u;
     lat[e] = ring4(x / UC) + (uint32_t)(x % UC) * 256u;
     asm volatile("" : "+s"(gat[e]), "+s"(lat[e]));
   }
@@ -1181,7 +1183,7 @@ __device__ __forceinline__ void prep_tile_body(const MeshView& mv, int i0, int n
     read_u(0, 0);
     fetch_off(0, p0 + CH);
     if (refill) {
-      const uint32_t f4b = (uint32_t)(p0 + R) * 36u;
+      const uint32_t f4b = tile_piece(p0 + R, 0) * 4u;
 #pragma unroll
       for (int e = 0; e < NP; ++e) pre[e] = load_piece(gat[e] + f4b);
     }
