@@ -1613,7 +1613,7 @@ cc_status cc_step(cc_ctx* ctx, int32_t mesh_id, double* x, double* v, const doub
     for (int c = 0; c < 3; ++c) mat.grav[c] = p.gravity[c];
     const double h = p.quasistatic ? 1.0 : dt;
     Stepper S{ctx, M, M.view(), mat, p, s};
-    S.mv.tile = cc::tile_usable(S.mv, p.precision, ctx->dense_rows, ctx->dense_chunk);
+    S.mv.tile = cc::tile_chosen(S.mv, p.precision, ctx->dense_rows, ctx->dense_chunk, p.sweep != CC_SWEEP_JACOBI);
     HIPC(hipMemsetAsync(M.fb, 0, STEP_COUNTERS * sizeof(unsigned long long), s));
     cc::launch_predict(S.mv, M.d_vperm, x, v, x_bc, h, p.quasistatic, M.x, M.xt, M.x0, M.xtrial, M.bad, s);
     // one launch, one reduction and one wait per point evaluated: the energy
@@ -1790,7 +1790,7 @@ cc_status cc_probe_sweep(cc_ctx* ctx, int32_t mesh_id, const double* x, const do
     mat.s_el = p.quasistatic ? 1.0 : dt * dt;
     for (int c = 0; c < 3; ++c) mat.grav[c] = p.gravity[c];
     Stepper S{ctx, M, M.view(), mat, p, s};
-    S.mv.tile = cc::tile_usable(S.mv, p.precision, 0, 0);
+    S.mv.tile = cc::tile_chosen(S.mv, p.precision, 0, 0, false);
     cc::launch_gather_user(S.mv, M.d_vinv, x, M.x, s);
     cc::launch_gather_user(S.mv, M.d_vinv, x_tilde, M.xt, s);
     S.eval(M.x, energy != nullptr, true);
@@ -1925,7 +1925,7 @@ static void batch_host_fallback(cc_ctx* ctx, Mesh& M, cc::BatchItem& it, cc::Bat
   M.x = it.x;
   M.xtrial = it.xtrial;
   Stepper S{ctx, M, M.view(), it.mat, p, s};
-  S.mv.tile = cc::tile_usable(S.mv, p.precision, ctx->dense_rows, ctx->dense_chunk);
+  S.mv.tile = cc::tile_chosen(S.mv, p.precision, ctx->dense_rows, ctx->dense_chunk, p.sweep != CC_SWEEP_JACOBI);
   const int nd = M.D * M.n;
   const double tau = 1e-12 * std::max(std::fabs(c.E_cur), 1.0);
   // a Jacobi sweep of the same method (coloured sweeps of CC or JGS2), then
@@ -2000,7 +2000,7 @@ cc_status cc_step_batch(cc_ctx* ctx, int32_t n, const int32_t* mesh_ids, double*
       items[i] = make_item(M, mat);
       items[i].prep_dense = (p.method != CC_METHOD_CD && use_dense_band(ctx, M, p.precision)) ? 1 : 0;
       items[i].mv.rot = p.corotate ? M.rot : nullptr;
-      items[i].mv.tile = items[i].prep_dense && cc::batch_tile(plan) > 0;
+      items[i].mv.tile = items[i].prep_dense && cc::batch_tile(plan, i);
       items[i].feat_off = 0;
       for (int q = 0; q < i; ++q) items[i].feat_off += ms[q]->nf;
       items[i].xu = x[i];

@@ -240,6 +240,8 @@ size_t tile_lds_bytes(int cfg, int nf, int band_w);
 // Whether a mesh's dense condensation in precision prec takes it (the caller
 // sets MeshView::tile): no forced rows or chunk, tile records, a ring that fits.
 bool tile_usable(const MeshView& mv, int prec, int tv_cap, int chunk);
+// The same, and whether it is also the better kernel for the sweeps of that mesh alone.
+bool tile_chosen(const MeshView& mv, int prec, int tv_cap, int chunk, bool coloured);
 
 // Exact basis U_i[j] = (H^{-1})_ji ((H^{-1})_ii)^{-1} from float64 block rows
 // hb (cc_basis.hip), through the block-tridiagonal structure of H in band
@@ -326,7 +328,7 @@ struct BatchConfig {
 BatchPlan* batch_plan_create(const BatchItem* items_host, int nmesh, const BatchConfig& cfg,
                              hipStream_t s);
 void batch_plan_destroy(BatchPlan* p);
-int batch_tile(BatchPlan* p);   // > 0: the plan's dense meshes use tile records (MeshView::tile)
+int batch_tile(BatchPlan* p, int m);   // whether the plan's mesh m uses tile records (MeshView::tile)
 BatchItem* batch_items_dev(BatchPlan* p);
 BatchCtl* batch_ctl_dev(BatchPlan* p);
 // Start of a step: predictor, initial gradient norm and energy, control reset.

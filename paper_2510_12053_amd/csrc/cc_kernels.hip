@@ -1822,6 +1822,8 @@ static int dense_resident(const DenseCfg& dc, int prec) {
   return 256 * std::max(1, std::min(by_lds, by_reg));
 }
 static int tile_resident(int cfg) { return cfg == 2 ? 256 : 512; }
+// Workgroups from which on a launch fills the chip: three rounds of resident places.
+static bool tile_fills(int cfg, int blocks) { return blocks >= 3 * tile_resident(cfg); }
 
 // Segments that a launch of the dense condensation splits its rows' bands
 // into: two where the launch has at most one and a half workgroups per
@@ -1864,10 +1866,33 @@ int tile_config(const int* nf, const int* band_w, const int* rows, int count) {
   return lds[2] <= g_lds_limit ? 2 : lds[3] <= g_lds_limit ? 3 : 0;
 }
 
+// Whether the band kernel is the better one for a mesh's share of a launch that
+// fills the chip and would run in configuration cfg: where rounding up to whole
+// chunks leaves a quarter or more of the tile's ring unused, rows are short
+// enough for the longer first fill to show (it is not overlapped), and the band
+// kernel still has four rows and every wave that its registers allow.  Full
+// launches of equal bars, tile against band kernel, us: section 17x17, nf 4,913
+// 2315 / 2020, 6,647 2565 / 2516, 8,381 3085 / 3012, 10,115 2915 / 3046; 17x18,
+// 5,508 2319 / 2113; 18x18 (band kernel short of waves), 5,832 2525 / 3661;
+// 12x12 (ring 384), 1,728 725 / 706, 3,456 1293 / 1285, 5,760 2236 / 2317; 13x13,
+// 2,028 792 / 806, 6,760 2533 / 2660.
+static bool band_better(const MeshView& mv, int cfg) {
+  const int R = tile_ring(cfg, mv.nf, mv.band_w);
+  if (cfg == 1 || 4 * (TILE_CH[cfg - 1] + mv.band_w) > 3 * R || mv.nf >= 10 * R) return false;
+  const DenseCfg dc = dense_config(&mv.nf, &mv.band_w, 1, 3, 1);
+  return dc.tv == 4 && dense_resident(dc, 1) / 256 * (dc.ch / 64) == 4 * dense_reg_waves(1, 4);
+}
+
 bool tile_usable(const MeshView& mv, int prec, int tv_cap, int chunk) {
   if (prec != 1 || mv.D != 3 || tv_cap != 0 || chunk != 0 || mv.tb == nullptr || !mv.dense_supp || mv.nf < 2)
     return false;
   return tile_config(&mv.nf, &mv.band_w, &mv.nf, 1) > 0;
+}
+
+bool tile_chosen(const MeshView& mv, int prec, int tv_cap, int chunk, bool coloured) {
+  if (!tile_usable(mv, prec, tv_cap, chunk)) return false;
+  const int cfg = tile_config(&mv.nf, &mv.band_w, &mv.nf, 1);
+  return coloured || !tile_fills(cfg, nblocks(mv.nf, 5 * TILE_G[cfg - 1])) || !band_better(mv, cfg);
 }
 
 #define CC_DISPATCH_TILE(cfg, ...)                                                    \
@@ -2395,7 +2420,8 @@ template <typename T, int D>
 __global__ void __launch_bounds__(WG) kb_dm_finish(const BatchItem* __restrict__ items,
                                                    const BatchCtl* __restrict__ ctl,
                                                    const int* __restrict__ boff, int nmesh,
-                                                   int method, int colour, int fuse, int nseg) {
+                                                   int method, int colour, int fuse, int nseg,
+                                                   const int* __restrict__ segs) {
   const int mi = block_mesh(boff, nmesh, blockIdx.x);
   if (!ctl[mi].active) return;
   const BatchItem& it = items[mi];
@@ -2406,7 +2432,8 @@ __global__ void __launch_bounds__(WG) kb_dm_finish(const BatchItem* __restrict__
   // vertices move in place in the sweep's running state xtrial
   if (i < v1)
     dm_finish_body<T, D>(it.mv, method, i, (const T*)it.hb, (T*)it.KL, it.fb, fuse ? it.g : nullptr,
-                         fuse ? it.d : nullptr, fuse == 2 ? it.xtrial : it.x, fuse ? it.xtrial : nullptr, nseg);
+                         fuse ? it.d : nullptr, fuse == 2 ? it.xtrial : it.x, fuse ? it.xtrial : nullptr,
+                         segs != nullptr ? segs[mi] : nseg);
 }
 
 template <typename T, int D, int G>
@@ -2722,6 +2749,15 @@ struct Offsets {
   int total() const { return h.empty() ? 0 : h.back(); }
 };
 
+// The dense meshes of a batch that share a condensation launch.
+struct DenseGroup {
+  int tile = 0;     // configuration of the matrix-core condensation (tile_config; 0: the plan's rows of tv)
+  size_t lds = 0;   // dynamic LDS of the launch
+  std::vector<char> in;       // by mesh
+  std::vector<Offsets> prep;  // blocks of the plan's meshes in its order; index 0: all free vertices, c+1: colour c
+  std::vector<int> nseg;      // segments of their rows (prep_segments), indexed as prep
+};
+
 struct BatchPlan {
   int nmesh = 0;
   BatchConfig cfg{};
@@ -2733,15 +2769,14 @@ struct BatchPlan {
   Offsets point;    // rotations and elements of each mesh (kb_point)
   std::vector<Offsets> pointg;   // with the gradient; index 0: all elements, c + 1: colour c's dirty ones
   std::vector<Offsets> elemc, asmbc;   // element / slot blocks of colour c's dirty lists
-  std::vector<Offsets> prep, prepd, fin, upd;   // index 0: all free vertices, c+1: colour c
-  std::vector<int> nseg;      // segments of the dense condensation's rows (prep_segments), indexed as prepd
-  std::vector<int> dorder_h;  // meshes by falling nf: the order of prepd's blocks
+  std::vector<Offsets> prep, fin, upd;   // index 0: all free vertices, c+1: colour c
+  Offsets fseg;     // with several groups: the segments of every mesh's rows, nmesh for each entry of fin
+  std::vector<DenseGroup> dense;         // none: no dense mesh
+  std::vector<int> dorder_h;  // meshes by falling nf: the order of the groups' blocks
   int* dorder = nullptr;
   int max_colours = 0;
-  int tv = 0;       // vertices per workgroup of the dense condensation (0: no dense mesh)
+  int tv = 0;       // vertices per workgroup of the band kernel (0: no dense mesh)
   int ch = 0;       // its chunk of band positions (= workgroup size)
-  size_t lds = 0;   // its dynamic LDS
-  int tile = 0;     // configuration of the matrix-core condensation (tile_config; 0: rows of tv)
   int scap = 0;     // staged support blocks per vertex of the sparse condensation (0: none)
   size_t slds = 0;  // its dynamic LDS
   double* wpart = nullptr;   // energy partials of LS_WIDTH backtracking steps
@@ -2770,12 +2805,16 @@ void batch_set_hook(BatchPlan* p, BatchHook hook, void* user) {
 int batch_capturing(BatchPlan* p) { return p->capturing; }
 int batch_has_graph(BatchPlan* p) { return p->exec != nullptr; }
 
-static void offsets_build(Offsets& o, const std::vector<int>& counts, hipStream_t s) {
-  o.h.assign(counts.size() + 1, 0);
-  for (size_t i = 0; i < counts.size(); ++i) o.h[i + 1] = o.h[i] + counts[i];
+static void offsets_upload(Offsets& o, hipStream_t s) {
   if (o.d) (void)hipFree(o.d);
   (void)hipMalloc(&o.d, o.h.size() * sizeof(int));
   (void)hipMemcpyAsync(o.d, o.h.data(), o.h.size() * sizeof(int), hipMemcpyHostToDevice, s);
+}
+
+static void offsets_build(Offsets& o, const std::vector<int>& counts, hipStream_t s) {
+  o.h.assign(counts.size() + 1, 0);
+  for (size_t i = 0; i < counts.size(); ++i) o.h[i + 1] = o.h[i] + counts[i];
+  offsets_upload(o, s);
 }
 
 static void offsets_free(Offsets& o) {
@@ -2783,24 +2822,61 @@ static void offsets_free(Offsets& o) {
   o.d = nullptr;
 }
 
+static void vertex_offsets_free(BatchPlan* p) {
+  for (auto* v : {&p->prep, &p->fin, &p->upd, &p->elemc, &p->asmbc})
+    for (auto& o : *v) offsets_free(o);
+  offsets_free(p->fseg);
+  for (auto& g : p->dense)
+    for (auto& o : g.prep) offsets_free(o);
+}
+
+// Blocks of a group's meshes for colour c (cnt: every mesh's vertices of that
+// colour), and the segments of their rows, which nseg receives for each mesh.
+static void group_offsets(const BatchPlan* p, DenseGroup& g, const std::vector<int>& cnt, std::vector<int>& nseg,
+                          hipStream_t s) {
+  std::vector<int> blocks(p->nmesh);
+  int total = 0, max_nf = 0, unit = p->ch;            // the longest of these rows, and its segments' unit
+  for (int k = 0; k < p->nmesh; ++k) {
+    const int m = p->dorder_h[k];
+    if (!g.in[m]) continue;
+    const MeshView& mv = p->items_h[m].mv;
+    blocks[k] = nblocks(cnt[m], g.tile > 0 ? 5 * TILE_G[g.tile - 1] : p->tv);
+    total += blocks[k];
+    if (blocks[k] > 0 && mv.nf > max_nf) {
+      max_nf = mv.nf;
+      if (g.tile > 0) unit = tile_ring(g.tile, mv.nf, mv.band_w);
+    }
+  }
+  const int resident = g.tile > 0 ? tile_resident(g.tile) : dense_resident(DenseCfg{p->tv, p->ch, g.lds}, p->cfg.prec);
+  const int ns = total > 0 ? prep_segments(max_nf, total, unit, resident) : 1;
+  for (int& b : blocks) b *= ns;
+  for (int m = 0; m < p->nmesh; ++m)
+    if (g.in[m]) nseg[m] = ns;
+  g.nseg.push_back(ns);
+  g.prep.emplace_back();
+  offsets_build(g.prep.back(), blocks, s);
+}
+
 static void plan_vertex_offsets(BatchPlan* p, hipStream_t s) {
   const int G = p->cfg.G;
   p->prep.assign(p->max_colours + 1, Offsets{});
-  p->prepd.assign(p->max_colours + 1, Offsets{});
   p->fin.assign(p->max_colours + 1, Offsets{});
+  p->fseg.h.clear();
   p->upd.assign(p->max_colours + 1, Offsets{});
-  p->nseg.clear();
+  for (auto& g : p->dense) {
+    g.prep.clear();
+    g.nseg.clear();
+  }
   for (int c = -1; c < p->max_colours; ++c) {
-    std::vector<int> cp(p->nmesh), cd(p->nmesh), cf(p->nmesh), cu(p->nmesh);
+    std::vector<int> cnts(p->nmesh), cp(p->nmesh), cf(p->nmesh), cu(p->nmesh), nseg(p->nmesh, 1);
     for (int m = 0; m < p->nmesh; ++m) {
       const BatchItem& it = p->items_h[m];
       int v0, v1;
       if (c < 0) { v0 = 0; v1 = it.mv.nf; }
       else if (c < it.ncol) { v0 = it.coff[c]; v1 = it.coff[c + 1]; }
       else { v0 = v1 = 0; }
-      const int cnt = v1 - v0;
+      const int cnt = cnts[m] = v1 - v0;
       cp[m] = it.prep_dense ? 0 : nblocks(cnt, WG / G);
-      cd[m] = it.prep_dense ? nblocks(cnt, p->tile > 0 ? 5 * TILE_G[p->tile - 1] : p->tv) : 0;
       cf[m] = it.prep_dense ? nblocks(cnt, WG) : 0;
       // dense meshes get their direction from the fused condensation: in a
       // Jacobi sweep, and per colour in a coloured sweep with per-colour Hessians
@@ -2809,28 +2885,12 @@ static void plan_vertex_offsets(BatchPlan* p, hipStream_t s) {
       cu[m] = fused ? 0 : nblocks(cnt, WG / G);
     }
     offsets_build(p->prep[c + 1], cp, s);
-    std::vector<int> cdo(p->nmesh);
-    int blocks = 0, max_nf = 0, unit = p->ch;         // the longest of these rows, and its segments' unit
-    for (int m = 0; m < p->nmesh; ++m) {
-      const MeshView& mv = p->items_h[p->dorder_h[m]].mv;
-      cdo[m] = cd[p->dorder_h[m]];
-      blocks += cdo[m];
-      if (cdo[m] > 0 && mv.nf > max_nf) {
-        max_nf = mv.nf;
-        if (p->tile > 0) unit = tile_ring(p->tile, mv.nf, mv.band_w);
-      }
-    }
-    int ns = 1;
-    if (blocks > 0)
-      ns = prep_segments(max_nf, blocks, unit,
-                         p->tile > 0 ? tile_resident(p->tile)
-                                     : dense_resident(DenseCfg{p->tv, p->ch, p->lds}, p->cfg.prec));
-    p->nseg.push_back(ns);
-    for (int& k : cdo) k *= ns;
-    offsets_build(p->prepd[c + 1], cdo, s);
+    for (auto& g : p->dense) group_offsets(p, g, cnts, nseg, s);
+    p->fseg.h.insert(p->fseg.h.end(), nseg.begin(), nseg.end());
     offsets_build(p->fin[c + 1], cf, s);
     offsets_build(p->upd[c + 1], cu, s);
   }
+  if (p->dense.size() > 1) offsets_upload(p->fseg, s);
   p->elemc.assign(p->max_colours, Offsets{});
   p->asmbc.assign(p->max_colours, Offsets{});
   for (int c = 0; c < p->max_colours; ++c) {
@@ -2843,6 +2903,81 @@ static void plan_vertex_offsets(BatchPlan* p, hipStream_t s) {
     offsets_build(p->elemc[c], ce, s);
     offsets_build(p->asmbc[c], cs, s);
   }
+}
+
+// Float32 3D meshes with tile records, unless a row count or a chunk is forced:
+// the matrix-core condensation takes the plan's dense group over, or parts of it.
+// A launch has one configuration and one LDS size, so meshes whose band leaves
+// one workgroup per CU (wide) bring every other mesh of theirs down to that.
+// Where the others fill the chip by themselves, each kind has a launch of its
+// own; below that a second launch's end costs more than it gives.  Then the
+// batch takes the kernel that the wide meshes prefer; a coloured sweep, whose
+// launches are short, the tiles.  Steps of five iterations, us, one launch in
+// one configuration / this rule / the band kernel for all: a 17x17x17 cube with
+// four uneven bars 2445 / 2192 / 2343, with sixteen 6754 / 5220 / 5580, with 64
+// (four iterations) 17200 / 12754 / 13528; three cubes and sixteen bars 8188 /
+// 6606 / 6802; a 19x19x19 cube and twelve bars 5280 / 4794 / 6771.  One launch
+// against two: the 17x17x17 cube and two bars 2271 / 2406, coloured with sixteen
+// bars (two iterations) 6437 / 6719, the band kernel 7589.
+static void tile_groups(BatchPlan* p) {
+  if (p->dense.empty()) return;
+  const DenseGroup all = p->dense[0];
+  const bool coloured = p->cfg.sweep == 1;
+  for (int m = 0; m < p->nmesh; ++m)
+    if (all.in[m] && !tile_usable(p->items_h[m].mv, p->cfg.prec, p->cfg.tv_cap, p->cfg.chunk)) return;
+  auto wide = [&](int m) {
+    const MeshView& mv = p->items_h[m].mv;
+    return 2 * tile_lds_bytes(3, mv.nf, mv.band_w) > g_lds_limit;
+  };
+  struct Part {
+    DenseGroup g;
+    int blocks = 0, band = 0;                         // workgroups of a launch, and of meshes that band_better names
+    bool fills() const { return g.tile > 0 && tile_fills(g.tile, blocks); }
+    bool prefers_band() const { return fills() && 2 * band > blocks; }
+  };
+  auto part = [&](auto take) {
+    Part r;
+    r.g.in.assign(p->nmesh, 0);
+    std::vector<int> id, nf, bw, rows;
+    for (int m = 0; m < p->nmesh; ++m) {
+      if (!all.in[m] || !take(m)) continue;
+      const BatchItem& it = p->items_h[m];
+      r.g.in[m] = 1;
+      id.push_back(m);
+      nf.push_back(it.mv.nf);
+      bw.push_back(it.mv.band_w);
+      rows.push_back(coloured && it.ncol > 0 ? it.mv.nf / it.ncol : it.mv.nf);
+    }
+    if (id.empty()) return r;
+    r.g.tile = tile_config(nf.data(), bw.data(), rows.data(), (int)id.size());   // > 0: fits each of them
+    if (r.g.tile == 0) return r;
+    for (size_t k = 0; k < id.size(); ++k) {
+      const int b = nblocks(rows[k], 5 * TILE_G[r.g.tile - 1]);
+      r.g.lds = std::max(r.g.lds, tile_lds_bytes(r.g.tile, nf[k], bw[k]));
+      r.blocks += b;
+      if (band_better(p->items_h[id[k]].mv, r.g.tile)) r.band += b;
+    }
+    return r;
+  };
+  const Part w = part(wide), n = part([&](int m) { return !wide(m); });
+  std::vector<Part> parts{w, n};                      // long workgroups first
+  if (w.g.tile > 0 && n.g.tile > 0 && !n.fills()) {
+    if (!coloured && w.prefers_band()) return;
+    parts = {part([](int) { return true; })};
+    parts[0].band = 0;
+  }
+  p->dense.clear();
+  for (const Part& r : parts) {
+    if (r.blocks == 0) continue;
+    p->dense.push_back(r.g);
+    if (!coloured && r.prefers_band()) {
+      p->dense.back().tile = 0;
+      p->dense.back().lds = all.lds;
+    }
+  }
+  for (const DenseGroup& g : p->dense)
+    for (int m = 0; m < p->nmesh; ++m)
+      if (g.in[m]) p->items_h[m].mv.tile = g.tile > 0;
 }
 
 BatchPlan* batch_plan_create(const BatchItem* items_host, int nmesh, const BatchConfig& cfg,
@@ -2873,28 +3008,14 @@ BatchPlan* batch_plan_create(const BatchItem* items_host, int nmesh, const Batch
                           cfg.chunk);
       p->tv = dc.tv;
       p->ch = dc.ch;
-      p->lds = dc.lds;
       if (dc.tv == 0)
         for (int m = 0; m < nmesh; ++m) p->items_h[m].prep_dense = 0;
-      // float32 3D meshes with tile records, unless a row count or a chunk is
-      // forced: the matrix-core condensation
-      bool tiles = dc.tv > 0;
-      std::vector<int> rows;
-      for (int m = 0; m < nmesh; ++m)
-        if (p->items_h[m].prep_dense) {
-          const BatchItem& it = p->items_h[m];
-          tiles = tiles && tile_usable(it.mv, cfg.prec, cfg.tv_cap, cfg.chunk);
-          rows.push_back(cfg.sweep == 1 && it.ncol > 0 ? it.mv.nf / it.ncol : it.mv.nf);
-        }
-      if (tiles) {
-        p->tile = tile_config(dense_nf.data(), dense_bw.data(), rows.data(), (int)rows.size());
-        if (p->tile > 0) {
-          p->lds = 0;
-          for (size_t m = 0; m < rows.size(); ++m)
-            p->lds = std::max(p->lds, tile_lds_bytes(p->tile, dense_nf[m], dense_bw[m]));
-          for (BatchItem& it : p->items_h) it.mv.tile = it.prep_dense;
-        }
-      }
+      DenseGroup all;
+      all.lds = dc.lds;
+      all.in.assign(nmesh, 0);
+      for (int m = 0; m < nmesh; ++m) all.in[m] = p->items_h[m].prep_dense;
+      if (dc.tv > 0) p->dense.push_back(all);
+      tile_groups(p);
     }
   }
   int sparse_supp = 0;
@@ -2969,12 +3090,7 @@ void batch_plan_destroy(BatchPlan* p) {
                      &p->rotn, &p->point})
     offsets_free(*o);
   for (auto& o : p->pointg) offsets_free(o);
-  for (auto& o : p->prep) offsets_free(o);
-  for (auto& o : p->prepd) offsets_free(o);
-  for (auto& o : p->fin) offsets_free(o);
-  for (auto& o : p->upd) offsets_free(o);
-  for (auto& o : p->elemc) offsets_free(o);
-  for (auto& o : p->asmbc) offsets_free(o);
+  vertex_offsets_free(p);
   if (p->dorder) (void)hipFree(p->dorder);
   if (p->wpart) (void)hipFree(p->wpart);
   if (p->items_d) (void)hipFree(p->items_d);
@@ -2982,7 +3098,7 @@ void batch_plan_destroy(BatchPlan* p) {
   delete p;
 }
 
-int batch_tile(BatchPlan* p) { return p->tile; }
+int batch_tile(BatchPlan* p, int m) { return p->items_h[m].mv.tile; }
 BatchItem* batch_items_dev(BatchPlan* p) { return p->items_d; }
 BatchCtl* batch_ctl_dev(BatchPlan* p) { return p->ctl_d; }
 
@@ -3023,26 +3139,29 @@ static void b_gradient_only(BatchPlan* p, int which, hipStream_t s) {
 template <typename T, int D, int G>
 static void b_prep(BatchPlan* p, int colour, hipStream_t s, int fuse = 0) {
   const Offsets& o = p->prep[colour + 1];
-  const Offsets& od = p->prepd[colour + 1];
-  if (gridn(o) == 0 && gridn(od) == 0) return;
+  const Offsets& of = p->fin[colour + 1];
+  if (gridn(o) == 0 && gridn(of) == 0) return;
   p->mark(3, 1);
   if (gridn(o) > 0)
     kb_prep<T, D, G><<<gridn(o), WG, p->slds, s>>>(p->items_d, p->ctl_d, o.d, p->nmesh, p->cfg.method,
                                                   colour, p->scap);
-  if (gridn(od) > 0) {
-    const Offsets& of = p->fin[colour + 1];
-    const int nseg = p->nseg[colour + 1];
-    if (p->tile > 0) {
-      CC_DISPATCH_TILE(p->tile, kb_prep_tile<NG, NS, CH><<<gridn(od), 64 * NS, p->lds, s>>>(
-                                    p->items_d, p->ctl_d, od.d, p->dorder, p->nmesh, colour, fuse, nseg));
+  for (const DenseGroup& g : p->dense) {
+    const Offsets& od = g.prep[colour + 1];
+    const int nseg = g.nseg[colour + 1];
+    if (gridn(od) == 0) continue;
+    if (g.tile > 0) {
+      CC_DISPATCH_TILE(g.tile, kb_prep_tile<NG, NS, CH><<<gridn(od), 64 * NS, g.lds, s>>>(
+                                   p->items_d, p->ctl_d, od.d, p->dorder, p->nmesh, colour, fuse, nseg));
     } else {
-      CC_DISPATCH_TVCH(p->tv, p->ch, kb_prep_band<T, D, TV, CH><<<gridn(od), CH, p->lds, s>>>(
+      CC_DISPATCH_TVCH(p->tv, p->ch, kb_prep_band<T, D, TV, CH><<<gridn(od), CH, g.lds, s>>>(
                                 p->items_d, p->ctl_d, od.d, p->dorder, p->nmesh, p->cfg.method, colour, fuse,
                                 nseg));
     }
-    kb_dm_finish<T, D><<<gridn(of), WG, 0, s>>>(p->items_d, p->ctl_d, of.d, p->nmesh, p->cfg.method,
-                                               colour, fuse, nseg);
   }
+  if (gridn(of) > 0)
+    kb_dm_finish<T, D><<<gridn(of), WG, 0, s>>>(p->items_d, p->ctl_d, of.d, p->nmesh, p->cfg.method,
+                                               colour, fuse, p->dense[0].nseg[colour + 1],
+                                               p->dense.size() > 1 ? p->fseg.d + (colour + 1) * p->nmesh : nullptr);
   p->mark(3, 0);
 }
 
@@ -3067,7 +3186,7 @@ static void b_hessian(BatchPlan* p, int which, hipStream_t s, int colour = -1, b
   // band records carry both vertices' rotations, which change everywhere:
   // with them a colour's assembly takes every block too (sixteen uneven bars:
   // 21 us, against 18 for the changed blocks and 7 for the other records)
-  const int ac = rot && (p->tv > 0 || p->tile > 0) ? -1 : colour;
+  const int ac = rot && p->tv > 0 ? -1 : colour;
   const Offsets& oe = colour < 0 ? p->elem : p->elemc[colour];
   const Offsets& oa = ac < 0 ? p->asmb : p->asmbc[ac];
   if (p->hook == nullptr && (rot || grad)) {
@@ -3278,12 +3397,7 @@ void batch_set_lanes(BatchPlan* p, int G) {
   if (G == p->cfg.G) return;
   p->cfg.G = G;
   drop_graph(p);
-  for (auto& o : p->prep) offsets_free(o);
-  for (auto& o : p->prepd) offsets_free(o);
-  for (auto& o : p->fin) offsets_free(o);
-  for (auto& o : p->upd) offsets_free(o);
-  for (auto& o : p->elemc) offsets_free(o);
-  for (auto& o : p->asmbc) offsets_free(o);
+  vertex_offsets_free(p);
   plan_vertex_offsets(p, nullptr);
   (void)hipDeviceSynchronize();
 }
