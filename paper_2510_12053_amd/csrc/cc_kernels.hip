@@ -1826,18 +1826,23 @@ static int tile_resident(int cfg) { return cfg == 2 ? 256 : 512; }
 static bool tile_fills(int cfg, int blocks) { return blocks >= 3 * tile_resident(cfg); }
 
 // Segments that a launch of the dense condensation splits its rows' bands
-// into: two where the launch has at most one and a half workgroups per
-// resident place and a row is longer than a segment's unit (ring or chunk).
-// The time of such a launch is that of one workgroup's serial walk along the
-// band, or two where the second round is mostly empty; half the walk costs a
-// second ring fill.  Measured with one / two / three segments: 29x9x7 bar
-// (353 workgroups on 512 places) 72 / 65 us, the colours of sixteen uneven bars
-// (about 600 on 512) 52 / 43 / 43 us and the step 15.8 / 14.7 / 14.6 ms,
-// float64 21x6x6 bar (360 on 1,024) step 477 / 433 / 452 us, four of them
-// (1,440) 624 / 602 / 639 us; sixteen uneven bars whole (2,400 on 512), four
-// steps 11.99 / 12.25 / 12.68 ms.
-static int prep_segments(int max_nf, int blocks, int unit, int resident) {
-  return 2 * blocks <= 3 * resident && max_nf > unit ? SEG_MAX : 1;
+// into (rows: the band rows of all its workgroups): two up to one and a half times
+// what the resident places do in the longest row's time, where a row is longer
+// than a segment's unit (ring or chunk).  The time of such a launch is that of one
+// workgroup's serial walk along the band, or two where the second round is mostly
+// empty; half the walk costs a second ring fill.  In float32 the band kernel, whose
+// places share a CU's issue, gains nothing where one round is more than half full.
+// Unsplit / split, us: band kernel, four vertices a workgroup on 1,024 places,
+// 29x9x7 bars, one (441) 50.6 / 36.5, two (882) 58.4 / 61.4, three (1,323) 104 / 93;
+// 21x6x6, one (180) 26 / 20, four (720) 32.2 / 35.0, six (1,080) 49 / 43; coloured
+// step of ten uneven bars (0.43 of a round by rows, 0.78 by workgroups) 2248 / 2035;
+// float64 21x6x6 bar's step 477 / 433 (three segments 452), coloured 17x17x17 cube
+// (0.56 of a round) 2608 / 2514.  Tiles, steps of uneven bars, four (0.98 of a round
+// by rows) 1386 / 1219, six (1.13) 1443 / 1343.
+static int prep_segments(bool band32, int max_nf, long long rows, int unit, int resident) {
+  const long long full = (long long)resident * max_nf;   // every place busy for the longest row's time
+  const bool one_round = 2 * rows > full && rows <= full;
+  return 2 * rows <= 3 * full && !(band32 && one_round) && max_nf > unit ? SEG_MAX : 1;
 }
 
 size_t tile_lds_bytes(int cfg, int nf, int band_w) {
@@ -1935,7 +1940,8 @@ static bool prep_dense(const MeshView& mv, int prec, int method, int v0, int v1,
     if (mv.tile) {
       const int rows = v1 - v0, cfg = tile_config(&mv.nf, &mv.band_w, &rows, 1);
       const int blocks = nblocks(rows, 5 * TILE_G[cfg - 1]);
-      const int nseg = prep_segments(mv.nf, blocks, tile_ring(cfg, mv.nf, mv.band_w), tile_resident(cfg));
+      const int nseg = prep_segments(false, mv.nf, (long long)blocks * mv.nf, tile_ring(cfg, mv.nf, mv.band_w),
+                                     tile_resident(cfg));
       CC_DISPATCH_TILE(cfg, k_cc_prep_tile<NG, NS, CH><<<blocks * nseg, 64 * NS,
                                                        tile_lds_bytes(cfg, mv.nf, mv.band_w), s>>>(
                                 mv, v0, v1, (const float*)hb, (float*)KL, g != nullptr ? dout : nullptr, nseg));
@@ -1946,7 +1952,8 @@ static bool prep_dense(const MeshView& mv, int prec, int method, int v0, int v1,
     }
   const DenseCfg dc = dense_config(&mv.nf, &mv.band_w, 1, D, prec, tv_cap, chunk);
   if (dc.tv == 0) return false;
-  const int blocks = nblocks(v1 - v0, dc.tv), nseg = prep_segments(mv.nf, blocks, dc.ch, dense_resident(dc, prec));
+  const int blocks = nblocks(v1 - v0, dc.tv);
+  const int nseg = prep_segments(prec == 1, mv.nf, (long long)blocks * mv.nf, dc.ch, dense_resident(dc, prec));
   CC_DISPATCH_TVCH(dc.tv, dc.ch, k_cc_prep_band<T, D, TV, CH><<<blocks * nseg, CH, dc.lds, s>>>(
                                      mv, method, v0, v1, (const T*)hb, (T*)KL, g, dout, nseg));
   k_cc_dm_finish<T, D><<<nblocks(v1 - v0, WG), WG, 0, s>>>(mv, method, v0, v1, (const T*)hb, (T*)KL, fb,
@@ -2835,20 +2842,21 @@ static void vertex_offsets_free(BatchPlan* p) {
 static void group_offsets(const BatchPlan* p, DenseGroup& g, const std::vector<int>& cnt, std::vector<int>& nseg,
                           hipStream_t s) {
   std::vector<int> blocks(p->nmesh);
-  int total = 0, max_nf = 0, unit = p->ch;            // the longest of these rows, and its segments' unit
+  int max_nf = 0, unit = p->ch;                       // the longest of these rows, and its segments' unit
+  long long rows = 0;
   for (int k = 0; k < p->nmesh; ++k) {
     const int m = p->dorder_h[k];
     if (!g.in[m]) continue;
     const MeshView& mv = p->items_h[m].mv;
     blocks[k] = nblocks(cnt[m], g.tile > 0 ? 5 * TILE_G[g.tile - 1] : p->tv);
-    total += blocks[k];
+    rows += (long long)blocks[k] * mv.nf;
     if (blocks[k] > 0 && mv.nf > max_nf) {
       max_nf = mv.nf;
       if (g.tile > 0) unit = tile_ring(g.tile, mv.nf, mv.band_w);
     }
   }
   const int resident = g.tile > 0 ? tile_resident(g.tile) : dense_resident(DenseCfg{p->tv, p->ch, g.lds}, p->cfg.prec);
-  const int ns = total > 0 ? prep_segments(max_nf, total, unit, resident) : 1;
+  const int ns = prep_segments(g.tile == 0 && p->cfg.prec == 1, max_nf, rows, unit, resident);
   for (int& b : blocks) b *= ns;
   for (int m = 0; m < p->nmesh; ++m)
     if (g.in[m]) nseg[m] = ns;
