@@ -1822,8 +1822,6 @@ static int dense_resident(const DenseCfg& dc, int prec) {
   return 256 * std::max(1, std::min(by_lds, by_reg));
 }
 static int tile_resident(int cfg) { return cfg == 2 ? 256 : 512; }
-// Workgroups from which on a launch fills the chip: three rounds of resident places.
-static bool tile_fills(int cfg, int blocks) { return blocks >= 3 * tile_resident(cfg); }
 
 // Segments that a launch of the dense condensation splits its rows' bands
 // into (rows: the band rows of all its workgroups): two up to one and a half times
@@ -1871,21 +1869,36 @@ int tile_config(const int* nf, const int* band_w, const int* rows, int count) {
   return lds[2] <= g_lds_limit ? 2 : lds[3] <= g_lds_limit ? 3 : 0;
 }
 
-// Whether the band kernel is the better one for a mesh's share of a launch that
-// fills the chip and would run in configuration cfg: where rounding up to whole
-// chunks leaves a quarter or more of the tile's ring unused, rows are short
-// enough for the longer first fill to show (it is not overlapped), and the band
-// kernel still has four rows and every wave that its registers allow.  Full
-// launches of equal bars, tile against band kernel, us: section 17x17, nf 4,913
-// 2315 / 2020, 6,647 2565 / 2516, 8,381 3085 / 3012, 10,115 2915 / 3046; 17x18,
-// 5,508 2319 / 2113; 18x18 (band kernel short of waves), 5,832 2525 / 3661;
-// 12x12 (ring 384), 1,728 725 / 706, 3,456 1293 / 1285, 5,760 2236 / 2317; 13x13,
-// 2,028 792 / 806, 6,760 2533 / 2660.
+// Whether a launch of `blocks` workgroups (with that many band rows and ring
+// positions between them) is long enough for the tiles: below that, the band
+// kernel's smaller rings fill sooner, and its rows split better.
+// Launches, tiles / band kernel, us: 21x6x6 bars, one 26 / 20, four 47 / 32; 29x9x7,
+// one 47 / 36, two 76 / 58, three (530 of ten vertices) 98 / 93, four (706) 118 / 121;
+// 41x11x11, one (484, rows of 25 rings) 189 / 227; 25x15x15 (1,080 of five, 14 rings)
+// 287 / 273, 41x13x13 (1,352, 18 rings) 647 / 729.  Steps of uneven corotated
+// batches, three bars (425 of ten) 1141 / 1110, four (582) 1226 / 1289, six (720)
+// 1351 / 1414, sixteen 3196 / 3492, 64 13121 / 13613; coloured, sixteen bars (294)
+// 4849 / 4789, thirty (600) 8029 / 8467.
+static bool tile_fills(int cfg, int blocks, long long rows, long long rings) {
+  if (cfg == 1) return 10 * blocks >= 11 * tile_resident(1) || rows >= 12 * rings;
+  return blocks >= 3 * tile_resident(cfg) || (cfg == 3 && blocks >= 700 && rows >= 16 * rings);
+}
+
+// Whether the band kernel is the better one for a mesh's share of such a launch in
+// configuration cfg: where the band kernel has every wave that its registers
+// allow, and rows are short enough for the tile's first ring fill to show.  That
+// fill is not overlapped where one workgroup is on a CU (configuration 2), and
+// costs most where rounding up to whole chunks leaves a quarter of the ring unused
+// (3).  Full launches of equal bars, tile / band kernel, us: section 17x17, nf 4,913
+// 2315 / 2020, 6,647 2565 / 2516, 10,115 2915 / 3046; 18x18 (band kernel short of
+// waves), 5,832 2525 / 3661; 21x21, nf 3,528 411 / 331, steps of three with 8,820
+// 14.4 / 15.4 ms; 12x12 (ring 384), 1,728 725 / 706, 5,760 2236 / 2317; 13x13, 2,028
+// 792 / 806.
 static bool band_better(const MeshView& mv, int cfg) {
   const int R = tile_ring(cfg, mv.nf, mv.band_w);
-  if (cfg == 1 || 4 * (TILE_CH[cfg - 1] + mv.band_w) > 3 * R || mv.nf >= 10 * R) return false;
+  if (cfg == 1 || mv.nf >= 10 * R || (cfg == 3 && 4 * (TILE_CH[2] + mv.band_w) > 3 * R)) return false;
   const DenseCfg dc = dense_config(&mv.nf, &mv.band_w, 1, 3, 1);
-  return dc.tv == 4 && dense_resident(dc, 1) / 256 * (dc.ch / 64) == 4 * dense_reg_waves(1, 4);
+  return dc.tv > 0 && dense_resident(dc, 1) / 256 * (dc.ch / 64) == 4 * dense_reg_waves(1, dc.tv);
 }
 
 bool tile_usable(const MeshView& mv, int prec, int tv_cap, int chunk) {
@@ -1894,10 +1907,11 @@ bool tile_usable(const MeshView& mv, int prec, int tv_cap, int chunk) {
   return tile_config(&mv.nf, &mv.band_w, &mv.nf, 1) > 0;
 }
 
-bool tile_chosen(const MeshView& mv, int prec, int tv_cap, int chunk, bool coloured) {
+bool tile_chosen(const MeshView& mv, int prec, int tv_cap, int chunk, int rows) {
   if (!tile_usable(mv, prec, tv_cap, chunk)) return false;
-  const int cfg = tile_config(&mv.nf, &mv.band_w, &mv.nf, 1);
-  return coloured || !tile_fills(cfg, nblocks(mv.nf, 5 * TILE_G[cfg - 1])) || !band_better(mv, cfg);
+  const int cfg = tile_config(&mv.nf, &mv.band_w, &rows, 1);
+  return tile_fills(cfg, nblocks(rows, 5 * TILE_G[cfg - 1]), mv.nf, tile_ring(cfg, mv.nf, mv.band_w)) &&
+         !band_better(mv, cfg);
 }
 
 #define CC_DISPATCH_TILE(cfg, ...)                                                    \
@@ -1950,7 +1964,11 @@ static bool prep_dense(const MeshView& mv, int prec, int method, int v0, int v1,
                                                               g != nullptr ? xmove : nullptr, nseg);
       return true;
     }
-  const DenseCfg dc = dense_config(&mv.nf, &mv.band_w, 1, D, prec, tv_cap, chunk);
+  // one colour's rows in float32: chunks of 256, as in a batch's coloured sweeps
+  // (41x11x11 bar, two iterations, 128 / 256: 2014 / 1618 us; float64 2518 / 2718)
+  DenseCfg dc{};
+  if (prec == 1 && chunk == 0 && v1 - v0 < mv.nf) dc = dense_config(&mv.nf, &mv.band_w, 1, D, prec, tv_cap, 256);
+  if (dc.tv == 0) dc = dense_config(&mv.nf, &mv.band_w, 1, D, prec, tv_cap, chunk);
   if (dc.tv == 0) return false;
   const int blocks = nblocks(v1 - v0, dc.tv);
   const int nseg = prep_segments(prec == 1, mv.nf, (long long)blocks * mv.nf, dc.ch, dense_resident(dc, prec));
@@ -2914,23 +2932,21 @@ static void plan_vertex_offsets(BatchPlan* p, hipStream_t s) {
 }
 
 // Float32 3D meshes with tile records, unless a row count or a chunk is forced:
-// the matrix-core condensation takes the plan's dense group over, or parts of it.
+// the matrix-core condensation takes the plan's dense group over, or parts of it,
+// where its launch pays (tile_fills, band_better).
 // A launch has one configuration and one LDS size, so meshes whose band leaves
 // one workgroup per CU (wide) bring every other mesh of theirs down to that.
-// Where the others fill the chip by themselves, each kind has a launch of its
-// own; below that a second launch's end costs more than it gives.  Then the
-// batch takes the kernel that the wide meshes prefer; a coloured sweep, whose
-// launches are short, the tiles.  Steps of five iterations, us, one launch in
-// one configuration / this rule / the band kernel for all: a 17x17x17 cube with
-// four uneven bars 2445 / 2192 / 2343, with sixteen 6754 / 5220 / 5580, with 64
-// (four iterations) 17200 / 12754 / 13528; three cubes and sixteen bars 8188 /
-// 6606 / 6802; a 19x19x19 cube and twelve bars 5280 / 4794 / 6771.  One launch
-// against two: the 17x17x17 cube and two bars 2271 / 2406, coloured with sixteen
-// bars (two iterations) 6437 / 6719, the band kernel 7589.
+// Where the others pay by themselves, each kind has a launch of its own; below
+// that a second launch's end costs more than it gives, and the batch takes the
+// kernel that the wide meshes prefer.  Steps of five iterations, us, one launch in
+// one configuration / this rule / the band kernel for all: a 17x17x17 cube with four
+// uneven bars 2445 / 2192 / 2343, with sixteen 6754 / 5220 / 5580, with 64 (four
+// iterations) 17200 / 12754 / 13528; three cubes and sixteen bars 8188 / 6606 /
+// 6802; a 19x19x19 cube and twelve bars 5280 / 4794 / 6771.
 static void tile_groups(BatchPlan* p) {
   if (p->dense.empty()) return;
   const DenseGroup all = p->dense[0];
-  const bool coloured = p->cfg.sweep == 1;
+  const bool by_colour = p->cfg.sweep == 1 && p->cfg.hess_refresh == 0;
   for (int m = 0; m < p->nmesh; ++m)
     if (all.in[m] && !tile_usable(p->items_h[m].mv, p->cfg.prec, p->cfg.tv_cap, p->cfg.chunk)) return;
   auto wide = [&](int m) {
@@ -2940,8 +2956,8 @@ static void tile_groups(BatchPlan* p) {
   struct Part {
     DenseGroup g;
     int blocks = 0, band = 0;                         // workgroups of a launch, and of meshes that band_better names
-    bool fills() const { return g.tile > 0 && tile_fills(g.tile, blocks); }
-    bool prefers_band() const { return fills() && 2 * band > blocks; }
+    long long rows = 0, rings = 0;                    // their band rows and ring positions
+    bool pays() const { return g.tile > 0 && tile_fills(g.tile, blocks, rows, rings) && 2 * band <= blocks; }
   };
   auto part = [&](auto take) {
     Part r;
@@ -2954,7 +2970,7 @@ static void tile_groups(BatchPlan* p) {
       id.push_back(m);
       nf.push_back(it.mv.nf);
       bw.push_back(it.mv.band_w);
-      rows.push_back(coloured && it.ncol > 0 ? it.mv.nf / it.ncol : it.mv.nf);
+      rows.push_back(by_colour && it.ncol > 0 ? it.mv.nf / it.ncol : it.mv.nf);
     }
     if (id.empty()) return r;
     r.g.tile = tile_config(nf.data(), bw.data(), rows.data(), (int)id.size());   // > 0: fits each of them
@@ -2963,22 +2979,23 @@ static void tile_groups(BatchPlan* p) {
       const int b = nblocks(rows[k], 5 * TILE_G[r.g.tile - 1]);
       r.g.lds = std::max(r.g.lds, tile_lds_bytes(r.g.tile, nf[k], bw[k]));
       r.blocks += b;
+      r.rows += (long long)b * nf[k];
+      r.rings += (long long)b * tile_ring(r.g.tile, nf[k], bw[k]);
       if (band_better(p->items_h[id[k]].mv, r.g.tile)) r.band += b;
     }
     return r;
   };
   const Part w = part(wide), n = part([&](int m) { return !wide(m); });
   std::vector<Part> parts{w, n};                      // long workgroups first
-  if (w.g.tile > 0 && n.g.tile > 0 && !n.fills()) {
-    if (!coloured && w.prefers_band()) return;
+  if (!n.pays()) {
+    if (!w.pays()) return;
     parts = {part([](int) { return true; })};
-    parts[0].band = 0;
   }
   p->dense.clear();
   for (const Part& r : parts) {
     if (r.blocks == 0) continue;
     p->dense.push_back(r.g);
-    if (!coloured && r.prefers_band()) {
+    if (parts.size() > 1 && !r.pays()) {
       p->dense.back().tile = 0;
       p->dense.back().lds = all.lds;
     }

@@ -1,17 +1,23 @@
 """Batches whose meshes do not share a condensation launch, or not the kernel that
 each would take alone.
 
-  few:    three small bars beside a short one with a wide section: one launch in
-          the wide one's configuration;
-  many:   four 41x11x11 bars, which fill the chip, beside it: two launches;
+  few:    three small bars beside a short one with a wide section: too few rows for
+          the tiles, the band kernel for all;
+  many:   four 41x11x11 bars, which fill the chip, beside it: two launches, tiles
+          for the bars;
   cube:   a 17x17x17 cube, for whose launch the band kernel is the better one,
           beside two small bars: the band kernel for all;
   both:   the cube and four 41x11x11 bars: the band kernel and the tiles;
+  wide:   a 19x19x19 cube, for which the tiles are the better ones, beside two small
+          bars: one launch in its configuration;
+  tiny:   two 41x11x11 bars and six of 4 to 180 free vertices: one launch of ten
+          vertices per workgroup;
+  mid:    two 25x15x15 bars and the six: one launch of five vertices per workgroup;
   long:   a mesh with a row of more than eight upper blocks (no tile records)
           beside two small bars: the band kernel for all.
 
-One Jacobi or coloured sweep at full steps (coloured: tiles in all but the last),
-corotated, float32 local arithmetic, from the predictor, against the same sweep of
+One Jacobi or coloured sweep (the band kernel, except for twelve 41x11x11 bars) at
+full steps, corotated, float32 local arithmetic, from the predictor, against the same sweep of
 each mesh by itself in float64.  Tolerance: 1e-4 of the largest displacement, that
 of float32 local arithmetic in the other sweep tests."""
 import numpy as np
@@ -59,11 +65,15 @@ def _star(*shape):
 
 
 WIDE = ((4, 17, 17), dict(length=(1.05, 1.0, 1.0)))
+TINY = lambda: [_bar(*d) for d in [(2, 2, 2), (3, 2, 2), (5, 4, 4), (9, 4, 4), (14, 5, 2), (6, 6, 6)]]
 SETS = {
     "few": lambda: [_bar(7, 4, 4), _bar(*WIDE[0], **WIDE[1]), _bar(12, 5, 3), _bar(9, 6, 6)],
     "many": lambda: [_bar(41, 11, 11)] * 2 + [_bar(*WIDE[0], **WIDE[1])] + [_bar(41, 11, 11)] * 2,
     "cube": lambda: [_bar(7, 4, 4), _bar(17, 17, 17), _bar(9, 6, 6)],
     "both": lambda: [_bar(41, 11, 11)] * 3 + [_bar(17, 17, 17), _bar(41, 11, 11)],
+    "wide": lambda: [_bar(7, 4, 4), _bar(19, 19, 19), _bar(9, 6, 6)],
+    "tiny": lambda: [_bar(41, 11, 11)] * 2 + TINY(),
+    "mid": lambda: [_bar(25, 15, 15)] * 2 + TINY(),
     "long": lambda: [_bar(7, 4, 4), _star(9, 5, 5), _bar(9, 6, 6)],
 }
 
@@ -75,10 +85,9 @@ def cg():
     return cg
 
 
-@pytest.mark.parametrize("sweep", [0, 1])
-@pytest.mark.parametrize("name", SETS)
+@pytest.mark.parametrize("name,sweep", [(n, w) for n in SETS for w in (0, 1)] + [("twelve", 1)])
 def test_batch_against_float64_of_each_mesh(cg, name, sweep):
-    meshes = SETS[name]()
+    meshes = SETS[name]() if name in SETS else [_bar(41, 11, 11)] * 12
     dt = 1.0 / 60
     ctx = cg.cc_create(0)
     mids = []
