@@ -44,7 +44,11 @@ struct Mesh {
   std::vector<int> cel_ptr_h, csl_ptr_h;   // per-colour dirty element / slot list offsets
   int *d_bvert = nullptr, *d_bpos = nullptr, *d_bqcnt = nullptr, *d_hqslot = nullptr;
   void* hq = nullptr;
-  float* tb = nullptr;             // tile records and their index arrays (MeshView::tb)
+  // what only dense bases need, in one allocation (dense_buffers): segment sums,
+  // tile records and their index arrays (MeshView::segsum, tb)
+  char* dense_buf = nullptr;
+  void* segsum = nullptr;
+  float* tb = nullptr;
   int *d_tbslot = nullptr, *d_tboff[cc::TILE_N] = {};
   int qmax = 0, band_w = 0;
 
@@ -65,7 +69,7 @@ struct Mesh {
          *g = nullptr, *partials = nullptr;
   double* rot = nullptr;  // corotation: rotation of every free vertex (D*D each)
   double* corr = nullptr; // last step's correction x - x~ (MeshView::corr)
-  void *estore = nullptr, *hb = nullptr, *KL = nullptr, *segsum = nullptr;
+  void *estore = nullptr, *hb = nullptr, *KL = nullptr;
   unsigned long long* fb = nullptr;   // STEP_COUNTERS words
   int* bad = nullptr;                 // = fb + 4
   // last-step info
@@ -91,7 +95,7 @@ struct Mesh {
     v.hq = dense ? hq : nullptr;   // the assembly writes the band copy only for dense bases
     v.qmax = qmax; v.band_w = band_w;
     v.tb = dense ? tb : nullptr;
-    v.tb_slot = d_tbslot; 
+    v.tb_slot = d_tbslot;
     for (int c = 0; c < cc::TILE_N; ++c) v.tb_off[c] = d_tboff[c];
     v.sptr = sptr; v.sidx = sidx; v.U_d = U_d; v.U_f = U_f; v.dense_supp = dense;
     v.smap = smap; v.smap_words = smap_words; v.smap_supp = smap_supp;
@@ -159,13 +163,12 @@ void free_mesh(Mesh& M) {
   dfree(M.ev); dfree(M.star_ptr); dfree(M.star); dfree(M.d_rowptr); dfree(M.d_colidx);
   dfree(M.blkrow); dfree(M.cptr); dfree(M.centry); dfree(M.d_vperm); dfree(M.d_vinv);
   dfree(M.d_bvert); dfree(M.d_bpos); dfree(M.d_bqcnt); dfree(M.d_hqslot); dfree(M.hq);
-  dfree(M.tb); dfree(M.d_tbslot); 
-  for (int*& o : M.d_tboff) dfree(o);
+  dfree(M.dense_buf);
   dfree(M.d_eperm); dfree(M.d_sorder); dfree(M.d_aorder);
   dfree(M.d_cel_ptr); dfree(M.d_cel); dfree(M.d_csl_ptr); dfree(M.d_csl); dfree(M.dinv_d); dfree(M.vol_d); dfree(M.mass); dfree(M.dinv_f); dfree(M.vol_f);
   free_basis(M);
   dfree(M.x); dfree(M.xt); dfree(M.x0); dfree(M.xtrial); dfree(M.dvec); dfree(M.g);
-  dfree(M.partials); dfree(M.estore); dfree(M.hb); dfree(M.KL); dfree(M.segsum); dfree(M.fb);
+  dfree(M.partials); dfree(M.estore); dfree(M.hb); dfree(M.KL); dfree(M.fb);
   dfree(M.rot); dfree(M.corr);
   dfree(M.nptr); dfree(M.nidx); dfree(M.frank); dfree(M.Xr); dfree(M.feat); dfree(M.delta);
 }
@@ -677,27 +680,6 @@ void build_mesh(cc_ctx* ctx, Mesh& M) {
     const size_t hqb = (size_t)std::max(M.qmax, 1) * std::max(nf, 1) * rec;
     M.hq = dalloc<double>(hqb / sizeof(double));
     HIPC(hipMemsetAsync(M.hq, 0, hqb, s));
-    if (D == 3 && nf >= 2 && M.qmax <= cc::TILE_Q) {
-      // tile records (zero where a row has fewer blocks and past the last
-      // row) and, for each chunk size, the ring offsets of their columns
-      constexpr int Q = cc::TILE_Q;
-      const size_t rows = (size_t)nf + cc::TILE_PAD;
-      std::vector<int> tslot(M.nnzb, -1), off(rows * Q);
-      for (int p = 0; p < nf; ++p)
-        for (int q = 0; q < cnt[p]; ++q) tslot[up[p][q].second] = p * Q + q;
-      M.d_tbslot = dupload(tslot, s);
-      for (int c = 0; c < cc::TILE_N; ++c) {
-        const int R = cc::tile_ring(c + 1, nf, M.band_w);
-        for (size_t p = 0; p < rows; ++p)
-          for (int q = 0; q < Q; ++q) {
-            const int row = std::min((int)p, nf - 1);
-            off[p * Q + q] = ((int)p < nf && q < cnt[p] ? up[p][q].first : row) % R * 36;
-          }
-        M.d_tboff[c] = dupload(off, s);
-      }
-      M.tb = dalloc<float>(rows * Q * 12);
-      HIPC(hipMemsetAsync(M.tb, 0, rows * Q * 48, s));
-    }
   }
   M.cptr = dupload(cptr, s);
   M.centry = dupload(centry, s);
@@ -802,7 +784,6 @@ void build_mesh(cc_ctx* ctx, Mesh& M) {
   M.estore = dalloc<double>((size_t)NB * m * D * D);
   M.hb = dalloc<double>((size_t)M.nnzb * D * D);
   M.KL = dalloc<double>((size_t)nf * 2 * D * D);
-  M.segsum = dalloc<double>((size_t)nf * (cc::SEG_MAX - 1) * (D * D + D));
   M.rot = dalloc<double>((size_t)std::max(nf, 1) * D * D);
   M.corr = dalloc<double>((size_t)D * n);
   HIPC(hipMemsetAsync(M.corr, 0, (size_t)D * n * sizeof(double), s));
@@ -813,6 +794,51 @@ void build_mesh(cc_ctx* ctx, Mesh& M) {
 }
 
 // ---- basis upload ------------------------------------------------------
+// Buffers that only a dense basis needs, allocated with the mesh's first one:
+// segment sums and, for 3D meshes whose rows hold at most TILE_Q upper blocks,
+// tile records (zero where a row has fewer blocks and past the last row) and, for
+// each chunk size, the ring offsets of their columns.
+void dense_buffers(cc_ctx* ctx, Mesh& M) {
+  if (M.dense_buf != nullptr) return;
+  constexpr int Q = cc::TILE_Q;
+  const int D = M.D, nf = M.nf;
+  const bool tile = D == 3 && nf >= 2 && M.qmax <= Q;
+  const size_t rows = tile ? (size_t)nf + cc::TILE_PAD : 0, slots = tile ? M.nnzb : 0;
+  const size_t seg = (size_t)nf * (cc::SEG_MAX - 1) * (D * D + D) * sizeof(double), rec = rows * Q * 48;
+  std::vector<int> ints(slots + cc::TILE_N * rows * Q, -1);
+  if (tile) {
+    std::vector<std::pair<int, int>> row;            // a band row's upper blocks: position, slot
+    for (size_t p = 0; p < rows; ++p) {
+      row.clear();
+      if ((int)p < nf) {
+        const int j = M.bvert_h[p];
+        for (int t = M.rowptr[j]; t < M.rowptr[j + 1]; ++t)
+          if (M.bpos_h[M.colidx[t]] >= (int)p) row.push_back({M.bpos_h[M.colidx[t]], t});
+        std::sort(row.begin(), row.end());
+      }
+      for (int q = 0; q < Q; ++q) {
+        const bool real = q < (int)row.size();
+        if (real) ints[row[q].second] = (int)p * Q + q;
+        const int pos = real ? row[q].first : std::min((int)p, nf - 1);
+        for (int c = 0; c < cc::TILE_N; ++c)
+          ints[slots + c * rows * Q + p * Q + q] = pos % cc::tile_ring(c + 1, nf, M.band_w) * 36;
+      }
+    }
+  }
+  hipStream_t s = ctx->stream;
+  char* buf = dalloc<char>(seg + rec + ints.size() * sizeof(int));
+  int* di = reinterpret_cast<int*>(buf + seg + rec);
+  HIPC(hipMemsetAsync(buf, 0, seg + rec, s));
+  if (!ints.empty()) HIPC(hipMemcpyAsync(di, ints.data(), ints.size() * sizeof(int), hipMemcpyHostToDevice, s));
+  HIPC(hipStreamSynchronize(s));
+  M.dense_buf = buf;
+  M.segsum = buf;
+  if (!tile) return;
+  M.tb = reinterpret_cast<float*>(buf + seg);
+  M.d_tbslot = di;
+  for (int c = 0; c < cc::TILE_N; ++c) M.d_tboff[c] = di + slots + c * rows * Q;
+}
+
 // Slot map of a sparse basis (MeshView::smap): one byte per support entry
 // (i, j) and block of row j, so the condensation kernel finds U_i[k] for each
 // block (j, k), k >= j, without searching supp(i).  Left null, and the kernel searches,
@@ -894,6 +920,7 @@ void upload_basis(cc_ctx* ctx, Mesh& M, const int64_t* ptr, const int32_t* idx, 
     }
     if ((int)row.size() != nf - 1) dense = false;
   }
+  if (dense && nf > 1) dense_buffers(ctx, M);
   free_basis(M);
   hipStream_t s = ctx->stream;
   if (dense && nf > 1) {
@@ -980,6 +1007,7 @@ void build_basis(cc_ctx* ctx, Mesh& M, int radius, double dt, int quasi, const d
   cc::launch_elem_hess(mv, 0, M.x, mat, mat.s_el, M.estore, s);
   cc::launch_assemble(mv, 0, M.estore, mat, M.hb, nullptr, s);
   if (radius == 0) {  // exact basis from the block-tridiagonal factorisation of H (band order)
+    dense_buffers(ctx, M);
     const size_t blocks = (size_t)nf * nf;
     // breadth-first levels merged until each holds at least LEVEL_DOFS unknowns
     // (fewer, larger products; merged levels still couple only neighbours)
