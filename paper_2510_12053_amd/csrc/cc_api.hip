@@ -932,9 +932,11 @@ void upload_basis(cc_ctx* ctx, Mesh& M, const int64_t* ptr, const int32_t* idx, 
       for (int64_t q = sptr[i]; q < sptr[i + 1]; ++q)
         std::memcpy(&band[((size_t)i * nf + M.bpos_h[sidx[q]]) * DD], &Ud[(size_t)q * DD], DD * sizeof(double));
     if (blocks * DD * sizeof(double) <= DENSE_F64_MAX_BYTES) M.U_d = dupload(band, s);
-    std::vector<float> Uf(band.begin(), band.end());
-    Uf.resize(Uf.size() + cc::DENSE_F32_PAD, 0.f);
-    M.U_f = dupload(Uf, s);
+    const std::vector<float> Uf(band.begin(), band.end());
+    M.U_f = dalloc<float>(Uf.size() + cc::DENSE_F32_PAD);
+    HIPC(hipMemcpyAsync(M.U_f, Uf.data(), Uf.size() * sizeof(float), hipMemcpyHostToDevice, s));
+    HIPC(hipMemsetAsync(M.U_f + Uf.size(), 0, cc::DENSE_F32_PAD * sizeof(float), s));
+    HIPC(hipStreamSynchronize(s));                   // Uf goes
     M.dense = 1;
   } else {
     M.sptr = dupload(sptr, s);
