@@ -13,11 +13,14 @@ fastest is kept.  Results are cached in a JSON file keyed by the device
 architecture, the precision, the sweep, whether any basis is exact, and the
 size bucket of the batch (log2 of its free vertices and of its mesh count),
 so a later process on the same kind of device and workload takes the cached
-choice without timing.
+choice without timing.  An entry holds the library build it was timed with: what
+a choice means and which is fastest change with the kernels, so an entry of
+another build is timed again and replaced.
 
 This module only orders library calls and times them; every kernel runs in
 libccgpu.
 """
+import hashlib
 import json
 import math
 import os
@@ -27,7 +30,7 @@ from . import ccgpu as cg
 
 LANES = (16, 32, 64)
 ITERS_PER_GRAPH = (1, 2, 4)
-DENSE_ROWS = (0, 3, 2, 1)       # 0: automatic (float32 3D: matrix cores)
+DENSE_ROWS = (0, 3, 2, 1)       # 0: automatic (matrix cores for float32 3D launches that fill the chip)
 
 
 def default_cache_path():
@@ -49,6 +52,12 @@ def _load(path):
             return json.load(f)
     except (OSError, ValueError):
         return {}
+
+
+def _build():
+    """Name of the library build: a hash of the library file."""
+    with open(cg.LIB_PATH, "rb") as f:
+        return hashlib.sha256(f.read()).hexdigest()[:16]
 
 
 def _save(path, table):
@@ -78,9 +87,11 @@ def tune(ctx, mesh_ids, xs, vs, bcs, dt, params, tol, gravity, n_free, any_dense
         device_arch = torch.cuda.get_device_properties(xs[0].device).gcnArchName
     key = cache_key(device_arch, params.precision, params.sweep, any_dense, n_free, len(mesh_ids))
     table = _load(cache_path) if use_cache else {}
-    if key in table:
-        apply(ctx, table[key])
-        return table[key], None
+    build = _build()
+    choice = table.get(key, {})
+    if choice.pop("build", None) == build:
+        apply(ctx, choice)
+        return choice, None
     lanes = LANES if any_sparse else (16,)
     rows = DENSE_ROWS if any_dense else (0,)
     timings = []
@@ -109,7 +120,7 @@ def tune(ctx, mesh_ids, xs, vs, bcs, dt, params, tol, gravity, n_free, any_dense
     apply(ctx, choice)
     if use_cache:
         table = _load(cache_path)
-        table[key] = choice
+        table[key] = dict(choice, build=build)
         _save(cache_path, table)
     return choice, timings
 
