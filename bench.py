@@ -115,10 +115,10 @@ def kernel_model(s, S):
     return byts, flops
 
 
-def measured_traffic(summary):
+def measured_traffic(summary, kernel=None):
     """HBM bytes of one condensation launch from the counter summary written
-    by bench_counters.py, or None when the summary is missing or was taken on
-    another version of the kernel source."""
+    by bench_counters.py, or None when the summary is missing, was taken on
+    another version of the kernel source, or (kernel given) of another kernel."""
     import hashlib
     path = os.path.join(ROOT, "profiles", summary)
     src = os.path.join(ROOT, "paper_2510_12053_amd", "csrc", "cc_kernels.hip")
@@ -130,7 +130,7 @@ def measured_traffic(summary):
             rec = json.loads(line[len("traffic_json: "):])
     with open(src, "rb") as f:
         h = hashlib.sha256(f.read()).hexdigest()[:16]
-    if rec is None or rec.get("source_sha256_16") != h:
+    if rec is None or rec.get("source_sha256_16") != h or kernel not in (None, rec.get("kernel")):
         return None
     return rec
 
@@ -431,7 +431,9 @@ def main():
     batched = summary(rec_b, el_b, args.steps, nb, False)
     learned = summary(rec_l, el_l, args.steps, nb, False)
     roof, kernel_roofline, dom = roofline(wl, rec_k, kern_k, S, peak_f, tuning["dense_rows"])
-    tr = measured_traffic(f"traffic_kb_prep_tile_batch64_{args.precision}.md") if dom == "cc_prep" else None
+    prep = roof["kernel"].split("+")[0]
+    tr = (measured_traffic(f"traffic_{prep}_batch64_{args.precision}.md", roof["kernel"])
+          if dom == "cc_prep" else None)
     # counter bytes per bar-iteration times the bar-iterations of a mean launch
     if tr is not None:
         per_it = (tr["fetch_bytes_per_launch"] + tr["write_bytes_per_launch"]) / tr["mesh_iters_per_launch"]
