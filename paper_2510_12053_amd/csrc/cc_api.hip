@@ -1649,7 +1649,7 @@ cc_status cc_step(cc_ctx* ctx, int32_t mesh_id, double* x, double* v, const doub
     for (int c = 0; c < 3; ++c) mat.grav[c] = p.gravity[c];
     const double h = p.quasistatic ? 1.0 : dt;
     Stepper S{ctx, M, M.view(), mat, p, s};
-    S.mv.tile = cc::tile_chosen(S.mv, p.precision, ctx->dense_rows, ctx->dense_chunk, launch_rows(M, p));
+    S.mv.tile = cc::tile_chosen(S.mv, p.precision, ctx->dense_rows, ctx->dense_chunk, p.corotate, launch_rows(M, p));
     HIPC(hipMemsetAsync(M.fb, 0, STEP_COUNTERS * sizeof(unsigned long long), s));
     cc::launch_predict(S.mv, M.d_vperm, x, v, x_bc, h, p.quasistatic, M.x, M.xt, M.x0, M.xtrial, M.bad, s);
     // one launch, one reduction and one wait per point evaluated: the energy
@@ -1840,7 +1840,7 @@ cc_status cc_probe_sweep(cc_ctx* ctx, int32_t mesh_id, const double* x, const do
     mat.s_el = p.quasistatic ? 1.0 : dt * dt;
     for (int c = 0; c < 3; ++c) mat.grav[c] = p.gravity[c];
     Stepper S{ctx, M, M.view(), mat, p, s};
-    S.mv.tile = cc::tile_chosen(S.mv, p.precision, 0, 0, M.nf);
+    S.mv.tile = cc::tile_chosen(S.mv, p.precision, 0, 0, p.corotate, M.nf);
     cc::launch_gather_user(S.mv, M.d_vinv, x, M.x, s);
     cc::launch_gather_user(S.mv, M.d_vinv, x_tilde, M.xt, s);
     S.eval(M.x, energy != nullptr, true);
@@ -1975,7 +1975,7 @@ static void batch_host_fallback(cc_ctx* ctx, Mesh& M, cc::BatchItem& it, cc::Bat
   M.x = it.x;
   M.xtrial = it.xtrial;
   Stepper S{ctx, M, M.view(), it.mat, p, s};
-  S.mv.tile = cc::tile_chosen(S.mv, p.precision, ctx->dense_rows, ctx->dense_chunk, launch_rows(M, p));
+  S.mv.tile = cc::tile_chosen(S.mv, p.precision, ctx->dense_rows, ctx->dense_chunk, p.corotate, launch_rows(M, p));
   const int nd = M.D * M.n;
   const double tau = 1e-12 * std::max(std::fabs(c.E_cur), 1.0);
   // a Jacobi sweep of the same method (coloured sweeps of CC or JGS2), then

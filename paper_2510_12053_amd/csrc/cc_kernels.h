@@ -241,7 +241,7 @@ size_t tile_lds_bytes(int cfg, int nf, int band_w);
 // sets MeshView::tile): no forced rows or chunk, tile records, a ring that fits.
 bool tile_usable(const MeshView& mv, int prec, int tv_cap, int chunk);
 // The same, and whether it is also the better kernel for launches of `rows` vertices of that mesh alone.
-bool tile_chosen(const MeshView& mv, int prec, int tv_cap, int chunk, int rows);
+bool tile_chosen(const MeshView& mv, int prec, int tv_cap, int chunk, bool corotate, int rows);
 
 // Exact basis U_i[j] = (H^{-1})_ji ((H^{-1})_ii)^{-1} from float64 block rows
 // hb (cc_basis.hip), through the block-tridiagonal structure of H in band

@@ -1830,13 +1830,13 @@ static int tile_resident(int cfg) { return cfg == 2 ? 256 : 512; }
 // workgroup's serial walk along the band, or two where the second round is mostly
 // empty; half the walk costs a second ring fill.  In float32 the band kernel, whose
 // places share a CU's issue, gains nothing where one round is more than half full.
-// Unsplit / split, us: band kernel, four vertices a workgroup on 1,024 places,
-// 29x9x7 bars, one (441) 50.6 / 36.5, two (882) 58.4 / 61.4, three (1,323) 104 / 93;
-// 21x6x6, one (180) 26 / 20, four (720) 32.2 / 35.0, six (1,080) 49 / 43; coloured
-// step of ten uneven bars (0.43 of a round by rows, 0.78 by workgroups) 2248 / 2035;
-// float64 21x6x6 bar's step 477 / 433 (three segments 452), coloured 17x17x17 cube
-// (0.56 of a round) 2608 / 2514.  Tiles, steps of uneven bars, four (0.98 of a round
-// by rows) 1386 / 1219, six (1.13) 1443 / 1343.
+// Unsplit / split, condensation and finish, us: band kernel, four vertices a
+// workgroup on 1,024 places, 29x9x7 bars, one (441) 76 / 54, two (882) 90 / 94, three
+// (1,323) 160 / 146; 21x6x6, one (180) 37 / 28, four (720) 48 / 52, six (1,080) 74 / 65;
+// coloured step of ten uneven bars (0.43 of a round by rows, 0.78 by workgroups)
+// 2248 / 2035; float64 21x6x6 bar's step 477 / 433 (three segments 452), coloured
+// 17x17x17 cube (0.56 of a round) 2608 / 2514.  Tiles, steps of uneven bars, four
+// (0.98 of a round by rows) 1386 / 1219, six (1.13) 1443 / 1343.
 static int prep_segments(bool band32, int max_nf, long long rows, int unit, int resident) {
   const long long full = (long long)resident * max_nf;   // every place busy for the longest row's time
   const bool one_round = 2 * rows > full && rows <= full;
@@ -1872,31 +1872,34 @@ int tile_config(const int* nf, const int* band_w, const int* rows, int count) {
 // Whether a launch of `blocks` workgroups (with that many band rows and ring
 // positions between them) is long enough for the tiles: below that, the band
 // kernel's smaller rings fill sooner, and its rows split better.
-// Launches, tiles / band kernel, us: 21x6x6 bars, one 26 / 20, four 47 / 32; 29x9x7,
-// one 47 / 36, two 76 / 58, three (530 of ten vertices) 98 / 93, four (706) 118 / 121;
-// 41x11x11, one (484, rows of 25 rings) 189 / 227; 25x15x15 (1,080 of five, 14 rings)
-// 287 / 273, 41x13x13 (1,352, 18 rings) 647 / 729.  Steps of uneven corotated
-// batches, three bars (425 of ten) 1141 / 1110, four (582) 1226 / 1289, six (720)
-// 1351 / 1414, sixteen 3196 / 3492, 64 13121 / 13613; coloured, sixteen bars (294)
-// 4849 / 4789, thirty (600) 8029 / 8467.
+// Tiles / band kernel, condensation and finish, us: 21x6x6 bars, one 38 / 28, four
+// 72 / 48; 29x9x7, one 72 / 54, two 121 / 90, three (530 workgroups of ten vertices)
+// 156 / 145, four (706) 196 / 198 and corotated 186 / 206; 41x11x11, one (484, rows of
+// 25 rings) 304 / 335; corotated 25x15x15 (1,080 of five, 14 rings) 459 / 476, 41x13x13
+// (1,352, 18 rings) 642 / 741.  Steps of uneven corotated batches, three bars (425 of
+// ten) 1141 / 1110, four (582) 1226 / 1289, six (720) 1351 / 1414, sixteen 3196 / 3492,
+// 64 13121 / 13613; coloured, sixteen bars (294) 4849 / 4789, thirty (600) 8029 / 8467.
 static bool tile_fills(int cfg, int blocks, long long rows, long long rings) {
   if (cfg == 1) return 10 * blocks >= 11 * tile_resident(1) || rows >= 12 * rings;
   return blocks >= 3 * tile_resident(cfg) || (cfg == 3 && blocks >= 700 && rows >= 16 * rings);
 }
 
 // Whether the band kernel is the better one for a mesh's share of such a launch in
-// configuration cfg: where the band kernel has every wave that its registers
-// allow, and rows are short enough for the tile's first ring fill to show.  That
-// fill is not overlapped where one workgroup is on a CU (configuration 2), and
+// configuration cfg, given that it has every wave its registers allow: where rows
+// are short enough for the tile's first ring fill to show, or without corotation,
+// since rotating the gradient costs the band kernel, whose records do not carry it.
+// The fill is not overlapped where one workgroup is on a CU (configuration 2), and
 // costs most where rounding up to whole chunks leaves a quarter of the ring unused
-// (3).  Full launches of equal bars, tile / band kernel, us: section 17x17, nf 4,913
-// 2315 / 2020, 6,647 2565 / 2516, 10,115 2915 / 3046; 18x18 (band kernel short of
-// waves), 5,832 2525 / 3661; 21x21, nf 3,528 411 / 331, steps of three with 8,820
-// 14.4 / 15.4 ms; 12x12 (ring 384), 1,728 725 / 706, 5,760 2236 / 2317; 13x13, 2,028
-// 792 / 806.
-static bool band_better(const MeshView& mv, int cfg) {
+// (3).  Full launches of equal bars, tiles / band kernel, condensation and finish,
+// us, corotated: section 17x17, nf 4,913 2347 / 2023, 6,647 2595 / 2532, 10,115 2955 /
+// 3067; 18x18 (band kernel short of waves), 5,832 2514 / 3692; 21x21, 3,528 653 / 580,
+// 10,584 3248 / 3659; 13x13, 2,028 797 / 810, 6,760 2411 / 2655; step of seventeen
+// 13x12x12 (ring of 384, 272 needed) 3496 / 3401.  Without: 17x17, 10,115 2961 / 2722,
+// 17,340 4514 / 4191; 12x12, 5,760 2318 / 2138; 13x13, 6,760 2591 / 2377.
+static bool band_better(const MeshView& mv, int cfg, bool corotate) {
   const int R = tile_ring(cfg, mv.nf, mv.band_w);
-  if (cfg == 1 || mv.nf >= 10 * R || (cfg == 3 && 4 * (TILE_CH[2] + mv.band_w) > 3 * R)) return false;
+  if (cfg == 1) return false;
+  if (corotate && (mv.nf >= 10 * R || (cfg == 3 && 4 * (TILE_CH[2] + mv.band_w) > 3 * R))) return false;
   const DenseCfg dc = dense_config(&mv.nf, &mv.band_w, 1, 3, 1);
   return dc.tv > 0 && dense_resident(dc, 1) / 256 * (dc.ch / 64) == 4 * dense_reg_waves(1, dc.tv);
 }
@@ -1907,11 +1910,11 @@ bool tile_usable(const MeshView& mv, int prec, int tv_cap, int chunk) {
   return tile_config(&mv.nf, &mv.band_w, &mv.nf, 1) > 0;
 }
 
-bool tile_chosen(const MeshView& mv, int prec, int tv_cap, int chunk, int rows) {
+bool tile_chosen(const MeshView& mv, int prec, int tv_cap, int chunk, bool corotate, int rows) {
   if (!tile_usable(mv, prec, tv_cap, chunk)) return false;
   const int cfg = tile_config(&mv.nf, &mv.band_w, &rows, 1);
   return tile_fills(cfg, nblocks(rows, 5 * TILE_G[cfg - 1]), mv.nf, tile_ring(cfg, mv.nf, mv.band_w)) &&
-         !band_better(mv, cfg);
+         !band_better(mv, cfg, corotate);
 }
 
 #define CC_DISPATCH_TILE(cfg, ...)                                                    \
@@ -2981,7 +2984,7 @@ static void tile_groups(BatchPlan* p) {
       r.blocks += b;
       r.rows += (long long)b * nf[k];
       r.rings += (long long)b * tile_ring(r.g.tile, nf[k], bw[k]);
-      if (band_better(p->items_h[id[k]].mv, r.g.tile)) r.band += b;
+      if (band_better(p->items_h[id[k]].mv, r.g.tile, p->cfg.corotate)) r.band += b;
     }
     return r;
   };
