@@ -290,7 +290,7 @@ def roofline(wl, rec, kern, S, peak_f, dense_rows):
     """Dominant kernel class of the profiled launches against HBM and the
     arithmetic peak of the unit that does its products.  dense_rows: the
     tuning's rows per workgroup of the condensation (0: matrix cores in
-    float32)."""
+    float32, on launches as large as these workloads')."""
     models = [kernel_model(s, S) for s in wl.scenes]
     its_mesh = [0] * len(wl.scenes)
     for k, r in enumerate(rec):

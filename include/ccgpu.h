@@ -166,6 +166,8 @@ cc_status cc_subspace_upload(cc_ctx* ctx, int32_t mesh_id, const int64_t* ptr,
                free unknowns).  Stores n_free^2 blocks in float32, plus a
                float64 copy when that takes at most 4 GiB (larger bases
                then step in CC_FP32_MIXED only; CC_FP64 gives CC_E_STATE).
+   The context keeps up to 256 MiB of that temporary memory for its next build,
+   until cc_destroy; more is given back when the build returns.
    The rest Hessian is evaluated by the library's own GPU kernels in FP64;
    the patch solves run on the host. */
 cc_status cc_subspace_build(cc_ctx* ctx, int32_t mesh_id, int32_t radius, double dt,
@@ -244,10 +246,10 @@ cc_status cc_step_batch(cc_ctx* ctx, int32_t n, const int32_t* mesh_ids, double*
    (ms_out: 3 values for 16, 32, 64; may be NULL). */
 cc_status cc_batch_tuning(cc_ctx* ctx, int32_t lanes, int32_t iters_per_graph);
 /* Rows per workgroup of the exact-basis condensation (every basis row it
-   stages serves that many vertices per H block it loads): 0 = automatic (the
-   matrix-core kernel for float32 3D meshes when the chunk is 0 too, else the
-   most rows whose LDS ring fits, 4 in float32 and 2 in float64 on MI355X), or
-   a cap of 1 to 4; and its chunk of band positions per pass, which is also its workgroup
+   stages serves that many vertices per H block it loads): 0 = automatic (when
+   the chunk is 0 too, the matrix-core kernel for float32 3D launches that fill
+   the GPU, by its own sizes; else the most rows whose LDS ring fits, 4 in
+   float32 and 2 in float64 on MI355X), or a cap of 1 to 4; and its chunk of band positions per pass, which is also its workgroup
    size: 0 = the one that leaves more waves resident per CU, or 128 / 256 /
    512.
    A forced chunk whose ring does not fit sends the mesh to the sparse-row

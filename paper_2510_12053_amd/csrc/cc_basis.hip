@@ -49,7 +49,7 @@ __device__ __forceinline__ dbl4 mfma64(double a, double b, dbl4 c) {
 // m per thread (rows 4 (tid / 16) .., columns 4 (tid % 16) ..; zero past b),
 // written to Pout (b x b).  A step passes the pivot's row and column through
 // LDS, twice buffered, so that it takes one barrier; a serial chain of b steps
-// (about 17 us for b = 64; the block in LDS with five barriers a step took
+// (about 21 us for b = 64; the block in LDS with five barriers a step took
 // 174 us).  row, col: [2][GJ_B] each.
 __device__ __forceinline__ void gj_invert(double (&m)[4][4], int b, double (*row)[GJ_B], double (*col)[GJ_B],
                                           double* __restrict__ Pout, int* __restrict__ bad) {
@@ -126,7 +126,7 @@ __global__ void __launch_bounds__(WG) k_gj_first(const double* __restrict__ A, i
 // that another workgroup writes.  Both products on the float64 matrix cores.
 // The workgroup of the next pivot block (launched first) goes on to invert it
 // (Pnext): that serial chain is the step's length, the other workgroups run
-// beside it.  A step at 780 unknowns: 34 us (17 of them the chain); as pivot,
+// beside it.  A step at 780 unknowns: 36 us (about 21 of them the chain); as pivot,
 // row, update and column kernels with 4 x 4 outputs per thread it took 230 us.
 __global__ void __launch_bounds__(WG) k_gj_step(const double* __restrict__ A, double* __restrict__ out, int N,
                                                 int k0, int b, const double* __restrict__ P,

@@ -682,9 +682,6 @@ struct SlotRegs {
   }
 };
 
-// The end of a dense condensation's workgroup: per vertex, A_i from its basis
-// row in global memory (one wave per vertex), and A_i, Ht_i = Y + Y^T and b_i
-// from the workgroup's sums tot ([vertex][Y, then b]).
 // Segment seg's (1 .. nseg - 1) sums of vertex i: its part of Ht and of b.
 // Segment 0 leaves its own in the K, L slots and the direction.
 template <typename T, int D>
@@ -692,6 +689,9 @@ __device__ __forceinline__ T* seg_sums(const MeshView& mv, int seg, int i) {
   return reinterpret_cast<T*>(mv.segsum) + ((size_t)(seg - 1) * mv.nf + i) * (D * D + D);
 }
 
+// The end of the band kernel's workgroup: per vertex, A_i from its basis row in
+// global memory (one wave per vertex) into its K slot, and Ht_i = Y + Y^T and b_i
+// from the workgroup's sums tot ([vertex][Y, then b]).
 template <typename T, int D>
 __device__ __forceinline__ void band_tail(const MeshView& mv, int i0, int nv, int w, int nw,
                                           const T* __restrict__ hb, T* __restrict__ KL, const T* tot,
@@ -746,7 +746,7 @@ __device__ __forceinline__ void band_tail(const MeshView& mv, int i0, int nv, in
 
 
 template <typename T, int D, int TV, int CH>
-__device__ __forceinline__ void prep_band_body(const MeshView& mv, int method, int i0, int nv,
+__device__ __forceinline__ void prep_band_body(const MeshView& mv, int i0, int nv,
                                                const T* __restrict__ hb, T* __restrict__ KL, T* smem,
                                                const double* __restrict__ g, double* __restrict__ bout, int seg,
                                                int nseg) {
@@ -831,8 +831,8 @@ __device__ __forceinline__ void prep_band_body(const MeshView& mv, int method, i
       // three or four float32 rows U_j is read first and the diagonal product
       // sets W (no clearing of the accumulators, which the compiler emits
       // twice around the loop's guard; three rows then hold two waves per
-      // SIMD instead of three, which their LDS ring allows anyway on the
-      // meshes whose band sends them there); with fewer rows, whose occupancy
+      // SIMD instead of three, which their LDS ring allows anyway on meshes
+      // whose band is too wide for four); with fewer rows, whose occupancy
       // the extra live registers would cut, W is cleared and the diagonal
       // block comes last.  The other upper blocks run in a software pipeline unrolled by
       // two: block q + 1 (its H and column) is loaded while block q's LDS
@@ -1037,10 +1037,12 @@ __device__ __forceinline__ void tile_rows(const MeshView& mv, int i0, int nv, in
 // waits longer than its 8 cycles (a phase of the loop alone: 402 against 467
 // cycles of 2.4 GHz).  The partial sums of a chunk are added up apart, which
 // keeps the rounding of the sums over up to 35,000 positions at that of
-// prep_band_body's many short ones.  Measured against prep_band_body, whole
-// launch: 41x11x11 bar 298 against 431 us, the 64-bar batch 2.94 against
-// 3.13 ms, the 81x21x21 beam's step 91 against 119 ms (from 1,024-thread
-// workgroups: one workgroup per CU fits, and eight waves took 117 ms).
+// prep_band_body's many short ones.  Corotated, active launches against
+// prep_band_body's: 41x11x11 bar 329 against 445 us (357 with its rows split),
+// the 64-bar batch 2.99 against 3.13 ms on average, the 81x21x21 beam 17.9
+// against 23.2 ms (in sixteen waves: one workgroup per CU fits, and with eight a
+// step took 117 ms against 91).  Where it is not the better one: tile_fills,
+// band_better.
 template <int NG, int NS, int CH>
 __device__ __forceinline__ void prep_tile_body(const MeshView& mv, int i0, int nv, const float* __restrict__ hb,
                                                float* __restrict__ KL, float* smem, double* __restrict__ bout,
@@ -1318,13 +1320,13 @@ __global__ void __launch_bounds__(WG) k_cc_dm_finish(MeshView mv, int method, in
 }
 
 template <typename T, int D, int TV, int CH>
-__global__ void __launch_bounds__(CH) k_cc_prep_band(MeshView mv, int method, int v0, int v1,
+__global__ void __launch_bounds__(CH) k_cc_prep_band(MeshView mv, int v0, int v1,
                                                       const T* __restrict__ hb, T* __restrict__ KL,
                                                       const double* __restrict__ g, double* __restrict__ bout,
                                                       int nseg) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int nb = gridDim.x / nseg, i0 = v0 + blockIdx.x % nb * TV;
-  prep_band_body<T, D, TV, CH>(mv, method, i0, min(TV, v1 - i0), hb, KL, reinterpret_cast<T*>(smem_raw), g,
+  prep_band_body<T, D, TV, CH>(mv, i0, min(TV, v1 - i0), hb, KL, reinterpret_cast<T*>(smem_raw), g,
                                bout, blockIdx.x / nb, nseg);
 }
 
@@ -1976,7 +1978,7 @@ static bool prep_dense(const MeshView& mv, int prec, int method, int v0, int v1,
   const int blocks = nblocks(v1 - v0, dc.tv);
   const int nseg = prep_segments(prec == 1, mv.nf, (long long)blocks * mv.nf, dc.ch, dense_resident(dc, prec));
   CC_DISPATCH_TVCH(dc.tv, dc.ch, k_cc_prep_band<T, D, TV, CH><<<blocks * nseg, CH, dc.lds, s>>>(
-                                     mv, method, v0, v1, (const T*)hb, (T*)KL, g, dout, nseg));
+                                     mv, v0, v1, (const T*)hb, (T*)KL, g, dout, nseg));
   k_cc_dm_finish<T, D><<<nblocks(v1 - v0, WG), WG, 0, s>>>(mv, method, v0, v1, (const T*)hb, (T*)KL, fb,
                                                           g, dout, xfrom != nullptr ? xfrom : xmove,
                                                           g != nullptr ? xmove : nullptr, nseg);
@@ -2096,8 +2098,12 @@ void launch_rotations(const MeshView& mv, const double* x, const int* nptr, cons
 // arithmetic per thread (11 to 15 us), so side by side they take little more
 // than the longest.  Block b: rotations first, which take longest, with as few
 // threads per workgroup as the elements, then elements, then gradient.
-// Measured: directions of the corotated 29x9x7 bar 188 us one by one, 164 in one
-// launch; coloured step of sixteen uneven bars 13.69 and 11.48 ms.
+// Measured, one by one and in one launch: directions of the corotated 29x9x7 bar 188
+// and 164 us; coloured step of sixteen uneven bars 13.69 and 11.48 ms.  Launches that
+// fill the chip lose nothing, though the gradient then has the element Hessians'
+// registers: coloured 81x21x21 patch beam, two iterations, float64 2885 and 2819 us,
+// float32 1938 and 1897; 64 patch bars coloured, float64 7.64 and 7.67 ms, float32 4.86
+// and 4.78; corotated Jacobi, float64 3.14 and 3.05.
 template <typename T, int D, bool FCR>
 __device__ __forceinline__ void point_body(const MeshView& mv, int b, const double* __restrict__ x,
                                            const double* __restrict__ xt, const Material& mat, T* __restrict__ est,
@@ -2416,7 +2422,7 @@ __global__ void __launch_bounds__(CH) kb_prep_band(const BatchItem* __restrict__
                                                     const BatchCtl* __restrict__ ctl,
                                                     const int* __restrict__ boff,
                                                     const int* __restrict__ order, int nmesh,
-                                                    int method, int colour, int fuse, int nseg) {
+                                                    int colour, int fuse, int nseg) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int slot = block_mesh(boff, nmesh, blockIdx.x), mi = order[slot];
   if (!ctl[mi].active) return;
@@ -2424,7 +2430,7 @@ __global__ void __launch_bounds__(CH) kb_prep_band(const BatchItem* __restrict__
   int v0, v1;
   vertex_range(it, colour, v0, v1);
   const int lb = blockIdx.x - boff[slot], nb = (boff[slot + 1] - boff[slot]) / nseg, i0 = v0 + lb % nb * TV;
-  prep_band_body<T, D, TV, CH>(it.mv, method, i0, min(TV, v1 - i0), (const T*)it.hb, (T*)it.KL,
+  prep_band_body<T, D, TV, CH>(it.mv, i0, min(TV, v1 - i0), (const T*)it.hb, (T*)it.KL,
                            reinterpret_cast<T*>(smem_raw), fuse ? it.g : nullptr, fuse ? it.d : nullptr, lb / nb,
                            nseg);
 }
@@ -3182,8 +3188,7 @@ static void b_prep(BatchPlan* p, int colour, hipStream_t s, int fuse = 0) {
                                    p->items_d, p->ctl_d, od.d, p->dorder, p->nmesh, colour, fuse, nseg));
     } else {
       CC_DISPATCH_TVCH(p->tv, p->ch, kb_prep_band<T, D, TV, CH><<<gridn(od), CH, g.lds, s>>>(
-                                p->items_d, p->ctl_d, od.d, p->dorder, p->nmesh, p->cfg.method, colour, fuse,
-                                nseg));
+                                p->items_d, p->ctl_d, od.d, p->dorder, p->nmesh, colour, fuse, nseg));
     }
   }
   if (gridn(of) > 0)
@@ -3213,7 +3218,7 @@ static void b_hessian(BatchPlan* p, int which, hipStream_t s, int colour = -1, b
   const bool rot = gridn(p->rotn) > 0;
   // band records carry both vertices' rotations, which change everywhere:
   // with them a colour's assembly takes every block too (sixteen uneven bars:
-  // 21 us, against 18 for the changed blocks and 7 for the other records)
+  // 19 us, against 18 for the changed blocks and 7 for the other records)
   const int ac = rot && p->tv > 0 ? -1 : colour;
   const Offsets& oe = colour < 0 ? p->elem : p->elemc[colour];
   const Offsets& oa = ac < 0 ? p->asmb : p->asmbc[ac];
